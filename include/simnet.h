@@ -202,7 +202,10 @@ SIMNET_API int sim_load_weights(sim_ctx* ctx, const sim_layer* layers, int32_t n
  * a few per compute unit); a slot whose sub-trace finishes takes the next
  * unstarted one, longest first, so with more sub-traces than slots one step
  * advances only the sub-traces currently in slots.  Results do not depend on
- * the slot assignment.  lat_table (DEVICE int32, needed for INJECT and SHADOW) is
+ * the slot assignment.  With a slot for every sub-trace and at most 2,048 of
+ * them, the C3 networks' predicting steps are spread over more compute units,
+ * one launch per step (never more launches than steps are left; under stream
+ * capture the call stays one launch); results are the same.  lat_table (DEVICE int32, needed for INJECT and SHADOW) is
  * indexed by the sub-trace's simulated position: row
  * sum_{k'<k}(warm[k']+len[k']) + p, column o (0 fetch, 1 execution). */
 SIMNET_API int sim_step(sim_ctx* ctx, int32_t n_steps, int32_t lat_mode, const int32_t* lat_table);
@@ -217,7 +220,8 @@ SIMNET_API int sim_run(sim_ctx* ctx, int32_t lat_mode, const int32_t* lat_table,
 /* enable != 0: sim_run replays a graph of its kernels (the persistent step
  * kernel run until every slot is empty, then the reduction of the total),
  * instantiated on first use and rebuilt when lat_mode, lat_table, the
- * logits buffer or the weights change.  The graph holds kernel nodes only. */
+ * logits buffer or the weights change.  The graph holds kernel nodes only.
+ * (Runs of one launch per step, see sim_step, are launched step by step.) */
 SIMNET_API int sim_set_graph(sim_ctx* ctx, int32_t enable);
 
 /* Launch shape of the step kernel as chosen by sim_autotune. */

@@ -57,6 +57,14 @@ struct sim_ctx {
   int32_t n_wg = 0;                 // persistent workgroups; slots = n_wg * MT
   int32_t n_wg_max = 0;             // slots allocated at init
   int32_t variant = 0;              // tuning variant of the step kernel
+  int32_t n_cu = 0;
+  // split step and forward (C3 networks, few windows): buffers, steps taken
+  // since the reset (a lower bound), each tile's longest sub-trace in claim
+  // order
+  void* split_block = nullptr;
+  SplitBufs split{};
+  int64_t steps_done = 0;
+  std::vector<int64_t> tile_len;
   const uint32_t* codes = nullptr;  // packed trace (SIM_FEAT_CODE32)
   const uint2* mem = nullptr;       // addresses for the dependency flags
   float* logits_out = nullptr;
@@ -538,6 +546,63 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
   return SIM_OK;
 }
 
+// The split step's and forward's buffers, made once when a C3 network's
+// weights are loaded (nothing is allocated in a step or a forward).  Without
+// them (an allocation failed) every tile runs on one workgroup.
+static void ensure_split(sim_ctx* c) {
+  if (c->split_block || c->net == 0 || c->net == 5) return;
+  const size_t groups = (size_t)split_groups(c->net, c->cfg.prec);
+  const size_t slots = c->has_trace && c->n_wg_max <= SPLIT_MAX_TILES ? (size_t)c->n_wg_max * MT : 0;
+  const size_t ring = slots * SPLIT_RING, mring = c->cfg.n_out == 3 ? ring : 0;
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  const size_t part = take((size_t)SPLIT_MAX_TILES * groups * MT * NetC3::HID * sizeof(float)),
+               cst = take(slots * sizeof(SlotConst)), sc0 = take(slots * sizeof(SlotScalars)),
+               sc1 = take(slots * sizeof(SlotScalars)), qe = take(ring * 4), qt = take(ring * 8),
+               qr = take(ring * 8), mi = take(mring * 4), me = take(mring * 4),
+               mt = take(mring * 8), mr = take(mring * 8), mx = take(mring * 8);
+  if (hipMalloc(&c->split_block, off) != hipSuccess) {
+    (void)hipGetLastError();
+    c->split_block = nullptr;
+    return;
+  }
+  char* base = static_cast<char*>(c->split_block);
+  SplitBufs& b = c->split;
+  b.part = reinterpret_cast<float*>(base + part);
+  if (slots == 0) return;
+  b.cst = reinterpret_cast<SlotConst*>(base + cst);
+  b.scal[0] = reinterpret_cast<SlotScalars*>(base + sc0);
+  b.scal[1] = reinterpret_cast<SlotScalars*>(base + sc1);
+  b.q_e = reinterpret_cast<int32_t*>(base + qe);
+  b.q_t = reinterpret_cast<int64_t*>(base + qt);
+  b.q_r = reinterpret_cast<int64_t*>(base + qr);
+  b.m_idx = reinterpret_cast<int32_t*>(base + mi);
+  b.m_es = reinterpret_cast<int32_t*>(base + me);
+  b.m_t = reinterpret_cast<int64_t*>(base + mt);
+  b.m_r = reinterpret_cast<int64_t*>(base + mr);
+  b.m_x = reinterpret_cast<int64_t*>(base + mx);
+}
+
+// Shape of a split launch over `tiles` tiles: one unit per group and as many
+// column slices as one workgroup per CU allows (a workgroup's LDS fills a
+// CU); with more tiles, fewer units of several groups.  units < 2: not worth
+// splitting (one workgroup per tile).  More workgroups than CUs lose, each
+// round paying the head and the update again (us per step, BF16: 32 tiles 4
+// units x 2 or 1 slices 28, x 4 38; 85 tiles 3 units 37, 4 units 53, 2 units
+// 43; 128 tiles 2 units 46, 4 units 58; 163 tiles 2 units 81 against 54 on
+// one workgroup per tile).
+static SplitShape split_shape(const sim_ctx* c, int64_t tiles) {
+  if (!c->split_block || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1};
+  const int64_t groups = split_groups(c->net, c->cfg.prec);
+  for (int32_t s : {4, 2, 1})
+    if (tiles * groups * s <= c->n_cu) return SplitShape{(int32_t)groups, s};
+  return SplitShape{(int32_t)std::min<int64_t>(groups, c->n_cu / tiles), 1};
+}
+
 // ------------------------------------------------------------ training ---
 
 constexpr int TRAIN_BINS = 400, TRAIN_OUT = 2 * (TRAIN_BINS + 1);
@@ -713,6 +778,7 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
   c->relu = relu;
   int rc = relayout_train(c);
   if (rc != SIM_OK) return rc;
+  ensure_split(c);
   c->weights = true;
   return SIM_OK;
 }
@@ -869,6 +935,10 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
     }
   }
   if (tr->n_sub == 0) {  // predictor-only: forward/backward on explicit windows
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      c->n_cu = 0;
     c->has_trace = false;
     *out = c;
     return SIM_OK;
@@ -915,6 +985,7 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
   for (int32_t k = 0; k < K; ++k) order[k] = k;
   std::stable_sort(order.begin(), order.end(),
                    [&](int32_t a, int32_t b) { return npos[a] > npos[b]; });
+  for (int32_t i = 0; i < K; i += MT) c->tile_len.push_back(npos[order[i]]);
   int dev = 0, n_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -923,6 +994,7 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
     delete c;
     return SIM_EDEVICE;
   }
+  c->n_cu = n_cu;
   // one persistent workgroup per CU for the large network (LDS-bound), a few
   // per CU for the small one
   const int per_cu = c->net == 0 ? 4 : 1;
@@ -1076,6 +1148,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     c->calibrated = false;
     int rc = upload_weights(c, SIM_FP32, host.data(), nullptr, &c->dev_w32, &c->w32);
     if (rc != SIM_OK) return rc;
+    ensure_split(c);
     c->weights = true;
     return sim_reset(c);
   }
@@ -1089,6 +1162,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     if (e == hipSuccess) e = hipMalloc(&c->rb_logits, sizeof(float) * slots * NetRB7::NOUT);
     if (e != hipSuccess) return hip_fail(c, e, "hipMalloc RB7 step buffers");
   }
+  ensure_split(c);
   c->weights = true;
   return sim_reset(c);
 }
@@ -1100,6 +1174,7 @@ int sim_reset(sim_ctx* c) {
   if (e != hipSuccess) return hip_fail(c, e, "reset");
   c->completed = false;
   c->ran_to_end = false;
+  c->steps_done = 0;
   return SIM_OK;
 }
 
@@ -1261,6 +1336,46 @@ static int rb_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t* t
   return SIM_OK;
 }
 
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Whether a step of this run is split over several workgroups per tile: a C3
+// network running its predictor, every sub-trace in a slot of its own (so
+// that `steps` launches are known to end the run), and not under capture (a
+// graph takes the persistent kernel's one node).
+static bool split_step(const sim_ctx* c, int32_t mode) {
+  return (c->net == 1 || c->net == 3 || c->net == 4) && mode != SIM_LAT_INJECT && c->split.cst &&
+         (int64_t)c->n_wg * MT >= c->n_sub && split_shape(c, c->n_wg).units >= 2 &&
+         !capturing(c->stream);
+}
+
+// n_steps split steps (to the end at most): launch i finishes step i - 1 and
+// begins step i.  Slots run the sub-traces longest first, so tiles end from
+// the last; an ended tile stays for one launch that copies its final scalars
+// to the buffer the next launches read.
+static hipError_t split_steps(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t* table) {
+  const int64_t n = std::min(n_steps, c->max_pos - c->steps_done);
+  if (n <= 0) return hipSuccess;
+  const StepParams p = step_params(c, 1, mode, table);
+  const int all = (int)c->tile_len.size();
+  hipError_t e = launch_split_import(c->st, c->split, all, c->n_sub, c->C, c->cfg.retire_width,
+                                     c->stream);
+  int tiles = all, in = 0;
+  for (int64_t i = 0; i <= n && e == hipSuccess; ++i) {
+    while (tiles > 1 && c->tile_len[tiles - 1] + 1 < c->steps_done + i) --tiles;
+    e = launch_split_step(c->net, c->cfg.prec, c->w, c->relu, c->st, p, c->split,
+                          split_shape(c, tiles), tiles, in, i > 0, i < n, c->stream);
+    if (i > 0) in ^= 1;
+  }
+  if (e == hipSuccess)
+    e = launch_split_export(c->st, c->split, all, in, c->C, c->cfg.retire_width, c->stream);
+  return e;
+}
+
 static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t* table) {
   if (!c->has_trace) return fail(c, SIM_ESTATE, "context has no trace");
   if (c->cfg.col_dep >= 0 && c->net != 1 && mode != SIM_LAT_INJECT)
@@ -1276,11 +1391,20 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
   if (n_steps == 0) return SIM_OK;   // checks only
   if (n_steps >= INT32_MAX) c->ran_to_end = true;
   if (c->net == 5 && mode != SIM_LAT_INJECT) return rb_launch(c, n_steps, mode, table);
+  if (split_step(c, mode)) {
+    const hipError_t e = split_steps(c, n_steps, mode, table);
+    if (e != hipSuccess) return hip_fail(c, e, "split step launch");
+    c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
+    return SIM_OK;
+  }
   const StepParams p = step_params(c, n_steps, mode, table);
   // (injected latencies need no predictor: RB7 shares the hybrid head's step)
   hipError_t e = launch_step(c->net == 5 ? 3 : c->net, c->cfg.prec, c->variant, c->w, c->relu,
                              c->st, p, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "step launch");
+  // (launches under capture may never run, and slots that refill lag)
+  if ((int64_t)c->n_wg * MT >= c->n_sub && !capturing(c->stream))
+    c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
   return SIM_OK;
 }
 
@@ -1295,7 +1419,8 @@ int sim_run(sim_ctx* c, int32_t mode, const int32_t* table, sim_result* res) {
   if (!c) return SIM_EINVAL;
   if (!res) return fail(c, SIM_EINVAL, "null result");
   hipError_t e = hipSuccess;
-  if (c->use_graph && !c->ran_to_end && c->net != 5) {  // (RB7 runs its steps eagerly)
+  // (RB7 and split steps run eagerly)
+  if (c->use_graph && !c->ran_to_end && c->net != 5 && !split_step(c, mode)) {
     // same checks as a step launch, then replay (rebuilt when its inputs change)
     int rc = step_launch(c, 0, mode, table);
     if (rc != SIM_OK) return rc;
@@ -1358,8 +1483,13 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   if (c->net == 2) {
     if (!save_or_null) return fail(c, SIM_EINVAL, "the training form needs a save buffer");
     const SaveBlock sb = save_block(c, save_or_null, B);
-    hipError_t e = launch_forward_save(c->cfg.prec, c->w, c->relu, static_cast<const float*>(x),
-                                       B, sb, c->stream);
+    const SplitShape sh = split_shape(c, (B + MT - 1) / MT);
+    hipError_t e =
+        sh.units >= 2 ? launch_split_forward(2, c->cfg.prec, c->w, c->relu,
+                                             static_cast<const float*>(x), B, nullptr, sb,
+                                             c->split.part, sh, c->stream)
+                      : launch_forward_save(c->cfg.prec, c->w, c->relu,
+                                            static_cast<const float*>(x), B, sb, c->stream);
     TrainState& T = c->tr;
     const int bf = c->cfg.prec == SIM_BF16;
     GemmArgs g = gemm(opnd(sb.h, bf, 512, 1), opnd(T.perm + T.perm_off[4], bf, 1, 512),
@@ -1394,8 +1524,13 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     if (e != hipSuccess) return hip_fail(c, e, "RB7 forward");
     return SIM_OK;
   }
-  hipError_t e = launch_forward(c->net, c->cfg.prec, c->w, c->relu, static_cast<const float*>(x),
-                                B, logits, c->stream);
+  const SplitShape sh = c->net != 0 ? split_shape(c, (B + MT - 1) / MT) : SplitShape{1, 1};
+  hipError_t e = sh.units >= 2
+                     ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu,
+                                            static_cast<const float*>(x), B, logits, SaveBlock{},
+                                            c->split.part, sh, c->stream)
+                     : launch_forward(c->net, c->cfg.prec, c->w, c->relu,
+                                      static_cast<const float*>(x), B, logits, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "forward launch");
   return SIM_OK;
 }
@@ -1722,6 +1857,7 @@ void sim_destroy(sim_ctx* c) {
   if (c->tr.side) (void)hipStreamDestroy(c->tr.side);
   if (c->tr.work) (void)hipFree(c->tr.work);
   if (c->dev_block) (void)hipFree(c->dev_block);
+  if (c->split_block) (void)hipFree(c->split_block);
   if (c->rb_trunk) (void)hipFree(c->rb_trunk);
   if (c->rb_active) (void)hipFree(c->rb_active);
   if (c->rb_logits) (void)hipFree(c->rb_logits);

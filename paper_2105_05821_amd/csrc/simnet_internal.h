@@ -355,6 +355,57 @@ hipError_t launch_rb_head(int prec, const DevWeights& w, uint32_t relu, const vo
 hipError_t launch_rb_trunk(int prec, const DevWeights& w, uint32_t relu, const float* x, int64_t B,
                            void* out, hipStream_t stream);
 
+// Split step and forward (C3 networks, few windows; split.hip): a tile's
+// block groups over `units` workgroups (contiguous shares), the hidden FC's
+// columns over `slices` (1, 2 or 4).
+struct SplitShape {
+  int32_t units, slices;
+};
+constexpr int SPLIT_RING = 128;       // queue entries per slot, position mod 128
+constexpr int SPLIT_MAX_TILES = 128;  // tiles of MT windows the buffers hold
+struct alignas(16) SlotConst {
+  int64_t first, n_pos, pred_off;
+  int32_t warm, kid;
+};
+struct alignas(16) SlotScalars {
+  int64_t cur, t_w, r_prev, pos, x_prev;
+  int32_t count;
+  int32_t m_n, m_count, m_inpq;  // stores pushed, in the memory write queue, of them still in the processor queue
+  uint32_t ctr[NCOUNTERS];       // counted since the import
+};
+// Per slot: constants, scalars (two buffers, read and written by alternate
+// launches), the queue ring and (store latencies) the stores' ring by
+// sequence number mod SPLIT_RING; per tile and group the hidden layer's sums.
+struct SplitBufs {
+  SlotConst* cst;
+  SlotScalars* scal[2];
+  int32_t* q_e;
+  int64_t *q_t, *q_r;
+  int32_t *m_idx, *m_es;
+  int64_t *m_t, *m_r, *m_x;
+  float* part;
+};
+// Groups of blocks per window of a C3 network (net 4: with the memory write
+// queue) in a form.
+int split_groups(int net, int prec);
+// Sub-trace state to and from the split form: slot i runs sub-trace order[i].
+hipError_t launch_split_import(const DevState& s, const SplitBufs& sp, int tiles, int32_t n_sub,
+                               int32_t C, int32_t W, hipStream_t stream);
+hipError_t launch_split_export(const DevState& s, const SplitBufs& sp, int tiles, int in,
+                               int32_t C, int32_t W, hipStream_t stream);
+// One launch of the first `tiles` tiles: finish = head and update of the
+// previous launch's sums (scalars from buffer in to the other), predict = the
+// next step's sums.
+hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t relu,
+                             const DevState& s, const StepParams& p, const SplitBufs& sp,
+                             SplitShape sh, int tiles, int in, int finish, int predict,
+                             hipStream_t stream);
+// Forward over at most SPLIT_MAX_TILES tiles of explicit windows (net 2:
+// training form, activations kept in sb, no logits).
+hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t relu,
+                                const float* x, int64_t B, float* logits, const SaveBlock& sb,
+                                float* sums, SplitShape sh, hipStream_t stream);
+
 // BF16 copy of an FP32 trace [n][D] into out [n][staged_feat(D)].
 hipError_t launch_stage_bf16(const float* feat, int64_t n, int D, uint16_t* out,
                              hipStream_t stream);

@@ -1,0 +1,649 @@
+// The C3 networks' step and forward for few windows (gfx950): one tile of
+// MT windows spread over several workgroups.
+//
+// The persistent step (kernels.hip) gives a tile to one workgroup, whose
+// time per step is that of streaming 3.4 MB (BF16) of hidden-FC weights
+// through one CU's L2 port after four groups' convolutions, ~52 us, however
+// many CUs idle.  Here a step is one launch of tiles x units x slices
+// workgroups: unit u gathers and convolves a contiguous share of the
+// window's block groups and multiplies their hidden-FC inputs by one of CS
+// column slices of the weights, leaving each group's FP32 sums in memory.
+// The next launch's workgroups all begin by adding the groups' sums in order,
+// then run the head and the clock and queue update on the tile (redundantly,
+// so that no second launch and no wait between workgroups is needed; unit 0
+// slice 0 writes the new state, into the other of two buffers, so no
+// workgroup of the launch reads what it writes).  The sums are those of the
+// one-workgroup step in the same order, so the results are identical.
+//
+// Time per step, one workgroup per tile -> split (uniform sub-traces):
+// BF16 16 sub-traces 47 -> 17 us, 512 49 -> 28, 1,024 51 -> 33, 2,048 54 ->
+// 47; FP32 16 221 -> 36, 512 224 -> 58, 2,048 224 -> 144; a forward of one
+// window BF16 47 -> 15, FP32 207 -> 28.  What bounds a small step now: ~4.5
+// us to launch, ~4 us for the sums, head and update, then one group's
+// convolutions (~6 us) and its weights' latency.
+//
+// The queue is a ring of QN = 128 entries indexed by position mod 128: an
+// entry outlives its place among the newest C = 110 by 17 pushes, so the
+// push of a launch never lands on an entry that launch reads, the row of
+// window slot w is instruction first + pos - w, and r_{i-W} of the retire
+// rule is the ring's entry of position i - W.
+#include "predict.h"
+
+namespace simnet {
+
+// Groups of blocks of a form (as predict_tile runs them).
+template <class Net, class P>
+struct Groups {
+  static constexpr int NG = Geo<Net, P>::NG, NFULL = Net::NB / NG, TAIL = Net::NB % NG;
+  static constexpr int N = NFULL + (TAIL > 0);
+  __device__ static int blocks(int g) { return g < NFULL ? NG : TAIL; }
+};
+
+int split_groups(int net, int prec) {
+  if (net == 4)
+    return prec == 0 ? Groups<NetC3S, PF32>::N : Groups<NetC3S, PBF16>::N;
+  return prec == 0 ? Groups<NetC3, PF32>::N
+         : prec == 1 ? Groups<NetC3, PBF16>::N : Groups<NetC3, PFP8>::N;
+}
+
+// A group's sums of tile `tile` in memory: [tile][group][hidden tile][lane],
+// four columns each, as the MFMA accumulators hold them.
+template <class Net, class P>
+__device__ __forceinline__ float4* group_sums(float4* part, int tile, int g) {
+  return part + ((size_t)tile * Groups<Net, P>::N + g) * (Net::HID / 16) * 64;
+}
+
+// The tile's hidden-layer sums: every group's, added in group order (wave w's
+// tiles).
+template <class Net, class P>
+__device__ __forceinline__ void add_groups(const float4* part, int tile, v4f* hacc, int wave,
+                                           int lane) {
+  constexpr int HT = (Net::HID / 16) / Net::WAVES;
+#pragma unroll
+  for (int j = 0; j < HT; ++j) hacc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int g = 0; g < Groups<Net, P>::N; ++g) {
+    const float4* src = group_sums<Net, P>(const_cast<float4*>(part), tile, g) +
+                        (size_t)wave * HT * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < HT; ++j) {
+      const float4 v = src[j * 64];
+      hacc[j] += v4f{v.x, v.y, v.z, v.w};
+    }
+  }
+}
+
+// This workgroup's groups [gb, ge): convolutions and one slice of the hidden
+// FC, each group's sums to memory.  load and commit as in predict_tile.
+template <class Net, class P, int CS, bool SAVE, class Load, class Commit>
+__device__ __forceinline__ void run_units(const DevWeights& wt, uint32_t relu_mask,
+                                          NetSmem<Net, P>& sm, int tile, int gb, int ge, int slice,
+                                          float4* part, SavePtrs<typename P::T> sv, Load&& load,
+                                          Commit&& commit) {
+  using GR = Groups<Net, P>;
+  constexpr int NG = GR::NG, HT = (Net::HID / 16) / Net::WAVES / CS;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  v4f hacc[HT];
+  float unused = 0.f;
+  auto store = [&](int g) {
+    float4* dst = group_sums<Net, P>(part, tile, g) +
+                  (size_t)FcShape<Net, P, NG, CS>::tile0(slice, wave) * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < HT; ++j)
+      dst[j * 64] = make_float4(hacc[j][0], hacc[j][1], hacc[j][2], hacc[j][3]);
+  };
+  auto clear = [&]() {
+#pragma unroll
+    for (int j = 0; j < HT; ++j) hacc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+  };
+  {
+    auto regs = load(gb * NG, GR::blocks(gb));
+    commit(gb * NG, GR::blocks(gb), regs, sm.x());
+  }
+  for (int g = gb; g < (ge < GR::NFULL ? ge : GR::NFULL); ++g) {
+    lds_barrier();
+    const int nj = (g + 1) * NG, nnb = g + 1 < ge ? GR::blocks(g + 1) : 0;
+    clear();
+    run_group<Net, P, NG, false, SAVE, false, CS>(
+        wt, relu_mask, sm, g * NG, nullptr, nullptr, sv, hacc, unused,
+        [&]() { return load(nj, nnb); },
+        [&](const auto& regs) {
+          if (nnb > 0) commit(nj, nnb, regs, sm.x());
+        },
+        slice);
+    store(g);
+  }
+  if constexpr (GR::TAIL > 0) {
+    if (ge == GR::N) {
+      lds_barrier();
+      clear();
+      run_group<Net, P, GR::TAIL, false, SAVE, false, CS>(
+          wt, relu_mask, sm, GR::NFULL * NG, nullptr, nullptr, sv, hacc, unused,
+          []() { return 0; }, [](int) {}, slice);
+      store(GR::NFULL);
+    }
+  }
+}
+
+// Unit u's groups: equal contiguous shares of all N.
+template <class Net, class P>
+__device__ __forceinline__ int unit_begin(int u, int units) {
+  return u * Groups<Net, P>::N / units;
+}
+
+// ------------------------------------------------------------ simulation ---
+
+template <class Net, class P>
+struct SplitSmem {
+  NetSmem<Net, P> net;
+  int64_t first[MT], pos[MT], cur[MT];
+  int32_t count[MT], active[MT];
+  int32_t lat_e[MT], lat_s[MT];     // the instruction just pushed
+  int32_t m_new[MT], m_vis[MT];     // stores shown: m_vis of them, up to sequence number m_new
+};
+
+// One step of every tile: (finish) the previous launch's sums through the
+// head and the update, from scalars sp.scal[in] to the other buffer;
+// (predict) this step's sums.  Grid: tiles x units x CS.
+template <class Net, class P, bool DEP, int CS>
+__global__ void __launch_bounds__(Net::WAVES * 64)
+    split_step_kernel(DevWeights wt, uint32_t relu_mask, DevState st, StepParams p, SplitBufs sp,
+                      int units, int in, int finish, int predict) {
+  using G = Geo<Net, P>;
+  using GA = Gather<Net, P>;
+  using T = typename P::T;
+  constexpr int C = Net::C, BS = Net::BS, QN = SPLIT_RING;
+  static_assert(G::NT == MT * 32 && QN > C + WMAX, "32 threads per slot");
+  __shared__ SplitSmem<Net, P> sm;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int per = units * CS, tile = blockIdx.x / per, uc = blockIdx.x % per;
+  const int unit = uc / CS, slice = uc % CS;
+  const bool writer = uc == 0;
+  // this half-wave's slot
+  const int s = tid >> 5, l = tid & 31, hbase = lane & 32;
+  const size_t slot = (size_t)tile * MT + s;
+  const SlotConst c = sp.cst[slot];
+  SlotScalars z = sp.scal[in][slot];
+  const bool act = z.pos < c.n_pos;
+  if (!__syncthreads_or(act)) {  // nothing left in the tile: the scalars move on
+    if (writer && finish && l == 0) sp.scal[in ^ 1][slot] = z;
+    return;
+  }
+  if constexpr (P::SCALED)
+    for (int i = tid; i < Net::D; i += G::NT) sm.net.x_inv[i] = wt.x_inv[i];
+  int32_t lat[3] = {0, 0, 0};
+  if (finish) {
+    int64_t qr[4], mx[4], mr[4];  // this slot's rings, entries l + 32 i
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      qr[i] = sp.q_r[slot * QN + l + 32 * i];
+      mx[i] = Net::MWQ ? sp.m_x[slot * QN + l + 32 * i] : 0;
+      mr[i] = Net::MWQ ? sp.m_r[slot * QN + l + 32 * i] : 0;
+    }
+    const int64_t ii = c.first + z.pos;  // the instruction predicted
+    bool is_store = false;
+    if constexpr (Net::MWQ)
+      if (act)
+        is_store = p.codes ? code_feature(p.codes[ii], p.store_col) != 0.f
+                           : p.feat[ii * Net::D + p.store_col] != 0.f;
+    v4f hacc[(Net::HID / 16) / Net::WAVES];
+    add_groups<Net, P>(reinterpret_cast<const float4*>(sp.part), tile, hacc, wave, lane);
+    sm.net.stage_head(wt, tid, G::NT);
+    __syncthreads();
+    head_tile<Net, P, false, false>(wt, relu_mask, sm.net, hacc, nullptr, nullptr, {});
+    __syncthreads();
+    // round and update (Sec. 3.2, as step_kernel's), every lane of the
+    // half-wave on the same values
+    const float* o = sm.net.logit[s];
+    const int64_t g = c.pred_off + z.pos;
+    uint32_t clamped = 0, nonfinite = 0, mismatch = 0;
+#pragma unroll
+    for (int i = 0; i < Net::NLAT; ++i) {
+      if constexpr (Net::HEAD == 1)
+        lat[i] = hybrid_latency(o + i * HYB_PER_TYPE, p.lat_max, clamped, nonfinite);
+      else
+        lat[i] = round_latency(o[i], p.lat_max, clamped, nonfinite);
+    }
+    if (p.lat_mode != 0 && act) {
+#pragma unroll
+      for (int i = 0; i < Net::NLAT; ++i) {
+        const int32_t inj = p.lat_table[g * Net::NLAT + i];
+        if (inj != lat[i]) ++mismatch;
+        lat[i] = inj;
+      }
+    }
+    const int64_t Tn = z.cur + lat[0];
+    // entries of the queue still in flight at Tn (r is monotone, so they are
+    // its newest)
+    int n_live = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      // the newest position the entry can hold
+      const int64_t q = z.pos - 1 - ((z.pos - 1 - (l + 32 * i)) & (QN - 1));
+      const bool live = act && q >= z.pos - z.count && qr[i] > Tn;
+      n_live += __popc((uint32_t)(__ballot(live) >> hbase));
+    }
+    int64_t r = Tn + lat[1] + 1;
+    r = r > z.r_prev ? r : z.r_prev;
+    {
+      const int e = (int)((z.pos - p.W) & (QN - 1));
+      const int64_t v = e < 32 ? qr[0] : e < 64 ? qr[1] : e < 96 ? qr[2] : qr[3];
+      const int64_t rb = __shfl(v, hbase | (e & 31)) + 1;
+      if (z.pos >= p.W) r = r > rb ? r : rb;
+    }
+    int64_t final_t = r;
+    const int64_t pos = z.pos;
+    if constexpr (Net::MWQ) {
+      // memory write queue: sequence numbers [m_n - m_count, m_n)
+      int n_x = 0, n_r = 0;
+      int32_t mc = z.m_count;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int32_t q = z.m_n - 1 - ((z.m_n - 1 - (l + 32 * i)) & (QN - 1));
+        n_x += __popc((uint32_t)(__ballot(act && q >= z.m_n - mc && mx[i] > Tn) >> hbase));
+      }
+      mc = n_x;  // (x is monotone: those gone by Tn are the oldest)
+      int64_t x = Tn + lat[2] + 1;
+      x = x > r ? x : r;
+      x = x > z.x_prev ? x : z.x_prev;
+      if (is_store && mc == C) --mc;  // the newest C stores suffice for the window
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int32_t q = z.m_n - 1 - ((z.m_n - 1 - (l + 32 * i)) & (QN - 1));
+        n_r += __popc((uint32_t)(__ballot(act && q >= z.m_n - mc && mr[i] > Tn) >> hbase));
+      }
+      if (act) {
+        if (is_store) {
+          if (writer && l == 0) {
+            const size_t at = slot * QN + (z.m_n & (QN - 1));
+            sp.m_idx[at] = (int32_t)ii;
+            sp.m_es[at] = pack_es(lat[1], lat[2]);
+            sp.m_t[at] = Tn;
+            sp.m_r[at] = r;
+            sp.m_x[at] = x;
+          }
+          z.x_prev = x;
+          ++z.m_n;
+          ++mc;
+          ++n_r;
+        }
+        z.m_count = mc;
+        z.m_inpq = n_r;
+        final_t = r > z.x_prev ? r : z.x_prev;
+      }
+    }
+    if (act) {
+      z.cur = Tn;
+      z.r_prev = r;
+      z.pos = pos + 1;
+      z.count = n_live + 1 < C ? n_live + 1 : C;  // only the newest C stay visible
+      if (pos + 1 == c.warm) z.t_w = Tn;
+      z.ctr[0] += clamped;
+      z.ctr[1] += nonfinite;
+      z.ctr[2] += mismatch;
+      ++z.ctr[3];
+    }
+    if (writer && l == 0) {
+      sp.scal[in ^ 1][slot] = z;
+      if (act) {
+        const size_t at = slot * QN + (pos & (QN - 1));
+        sp.q_e[at] = Net::MWQ ? pack_es(lat[1], lat[Net::NLAT - 1]) : lat[1];
+        sp.q_t[at] = Tn;
+        sp.q_r[at] = r;
+        if (p.logits_out)
+          for (int i = 0; i < Net::NOUT; ++i) p.logits_out[g * Net::NOUT + i] = o[i];
+        if (pos + 1 == c.n_pos) {  // last instruction: the drain ends (Eq. 1)
+          st.fetch[c.kid] = Tn - z.t_w;
+          st.drain[c.kid] = final_t - Tn;
+          st.final_tick[c.kid] = final_t;
+          st.warm_tick[c.kid] = z.t_w;
+        }
+      }
+    }
+  }
+  if (!predict) return;
+  if (l == 0) {
+    sm.first[s] = c.first;
+    sm.pos[s] = z.pos;
+    sm.cur[s] = z.cur;
+    sm.count[s] = z.count;
+    sm.active[s] = z.pos < c.n_pos;
+    sm.lat_e[s] = lat[1];
+    sm.lat_s[s] = lat[2];
+    // the stores shown: those that have left the processor queue and not
+    // the memory write queue
+    sm.m_new[s] = z.m_n - z.m_inpq;
+    sm.m_vis[s] = z.m_count - z.m_inpq;
+  }
+  if (!__syncthreads_or(z.pos < c.n_pos)) return;
+
+  constexpr int GSL = GA::GSL, TPR = GA::TPR;
+  const int grow = tid / TPR, part = tid % TPR;
+  const int gs = grow / GSL, gt = grow % GSL;
+  auto load = [&](int j0, int nb) {
+    typename GA::Regs r;
+    const int w = j0 * BS + gt;
+    int64_t idx = -1;
+    r.res = 0.f;
+    r.ex = 0.f;
+    r.sto = 0.f;
+    const size_t ring = ((size_t)tile * MT + gs) * QN;
+    const int64_t i = sm.first[gs] + sm.pos[gs];
+    if (gt < nb * BS && sm.active[gs]) {
+      if (w <= sm.count[gs]) {  // (w = 0: the instruction itself)
+        idx = i - w;
+        if (w == 1 && finish) {  // pushed by this launch, at this tick
+          r.ex = (float)sm.lat_e[gs];
+          if (Net::MWQ) r.sto = (float)sm.lat_s[gs];
+        } else if (w > 0) {
+          const size_t e = ring + ((sm.pos[gs] - w) & (QN - 1));
+          r.res = (float)(sm.cur[gs] - sp.q_t[e]);
+          const int32_t es = sp.q_e[e];
+          r.ex = (float)(Net::MWQ ? es & 0xffff : es);
+          if (Net::MWQ) r.sto = (float)((uint32_t)es >> 16);
+        }
+      } else if (Net::MWQ && w <= sm.count[gs] + sm.m_vis[gs]) {
+        const size_t e = ring + ((sm.m_new[gs] - (w - sm.count[gs])) & (QN - 1));
+        idx = sp.m_idx[e];
+        r.res = (float)(sm.cur[gs] - sp.m_t[e]);
+        r.ex = (float)(sp.m_es[e] & 0xffff);
+        r.sto = (float)((uint32_t)sp.m_es[e] >> 16);
+      }
+    }
+    request_row<Net, P, DEP>(p, idx, w == 0, sm.active[gs] ? i : 0, part, r);
+    return r;
+  };
+  auto commit = [&](int j0, int nb, const typename GA::Regs& r, T* X) {
+    (void)j0;
+    if (gt < nb * BS)
+      commit_row<Net, P, false, DEP>(p, sm.net.x_inv, gs, gt, part, r, X, nullptr);
+  };
+  run_units<Net, P, CS, false>(wt, relu_mask, sm.net, tile, unit_begin<Net, P>(unit, units),
+                               unit_begin<Net, P>(unit + 1, units), slice,
+                               reinterpret_cast<float4*>(sp.part), {}, load, commit);
+}
+
+// Sub-trace state -> split form: slot i runs sub-trace order[i] (every
+// sub-trace has a slot; longest first, so tiles finish from the last).
+__global__ void __launch_bounds__(MT * 32)
+    split_import_kernel(DevState st, SplitBufs sp, int32_t n_sub, int32_t C, int32_t W) {
+  constexpr int QN = SPLIT_RING;
+  const int s = threadIdx.x >> 5, l = threadIdx.x & 31;
+  const size_t slot = (size_t)blockIdx.x * MT + s;
+  const int k = slot < (size_t)n_sub ? st.order[slot] : -1;
+  if (slot == 0 && l == 0) *st.next = (unsigned)n_sub;  // all claimed
+  SlotConst c{};
+  SlotScalars z{};
+  c.kid = k;
+  if (k >= 0) {
+    c.first = st.first[k];
+    c.n_pos = st.n_pos[k];
+    c.pred_off = st.pred_off[k];
+    c.warm = st.warm[k];
+    z.cur = st.cur[k];
+    z.t_w = st.t_w[k];
+    z.r_prev = st.r_prev[k];
+    z.pos = st.pos[k];
+    z.count = st.count[k];
+    if (st.m_head) {
+      z.m_count = z.m_n = st.m_count[k];
+      z.m_inpq = st.m_inpq[k];
+      z.x_prev = st.x_prev[k];
+    }
+    // the ring: the retire times of the last W positions, then the queue
+    for (int j = l; j < W && j < z.pos; j += 32) {
+      const int64_t q = z.pos - 1 - j;
+      if (q < z.pos - z.count) sp.q_r[slot * QN + (q & (QN - 1))] = st.rw[(size_t)k * WMAX + q % W];
+    }
+    const int head = st.head[k];
+    for (int j = l; j < z.count; j += 32) {
+      const int e = head + j < C ? head + j : head + j - C;
+      const size_t from = (size_t)k * C + e;
+      const size_t to = slot * QN + ((z.pos - z.count + j) & (QN - 1));
+      sp.q_e[to] = st.q_e[from];
+      sp.q_t[to] = st.q_t[from];
+      sp.q_r[to] = st.q_r[from];
+    }
+    if (st.m_head) {
+      const int mh = st.m_head[k];
+      for (int j = l; j < z.m_count; j += 32) {
+        const int e = mh + j < C ? mh + j : mh + j - C;
+        const size_t from = (size_t)k * C + e, to = slot * QN + j;
+        sp.m_idx[to] = st.m_idx[from];
+        sp.m_es[to] = st.m_es[from];
+        sp.m_t[to] = st.m_t[from];
+        sp.m_r[to] = st.m_r[from];
+        sp.m_x[to] = st.m_x[from];
+      }
+    }
+  }
+  if (l == 0) {
+    sp.cst[slot] = c;
+    sp.scal[0][slot] = z;  // (both: a tile with nothing left is in no launch)
+    sp.scal[1][slot] = z;
+  }
+}
+
+// Split form (scalars sp.scal[in]) -> sub-trace state, rings from entry 0;
+// the counters added; finished sub-traces leave their slots.
+__global__ void __launch_bounds__(MT * 32)
+    split_export_kernel(DevState st, SplitBufs sp, int in, int32_t C, int32_t W) {
+  constexpr int QN = SPLIT_RING;
+  const int s = threadIdx.x >> 5, l = threadIdx.x & 31;
+  const size_t slot = (size_t)blockIdx.x * MT + s;
+  const SlotConst c = sp.cst[slot];
+  const SlotScalars z = sp.scal[in][slot];
+  const int k = c.kid;
+  if (l == 0) {
+    st.slot_kid[slot] = k >= 0 && z.pos < c.n_pos ? k : -1;
+    for (int i = 0; i < NCOUNTERS; ++i)
+      if (z.ctr[i]) atomicAdd(&st.counters[i], (unsigned long long)z.ctr[i]);
+  }
+  if (k < 0) return;
+  for (int j = l; j < W && j < z.pos; j += 32) {
+    const int64_t q = z.pos - 1 - j;
+    st.rw[(size_t)k * WMAX + q % W] = sp.q_r[slot * QN + (q & (QN - 1))];
+  }
+  for (int j = l; j < z.count; j += 32) {
+    const int64_t q = z.pos - z.count + j;
+    const size_t from = slot * QN + (q & (QN - 1)), to = (size_t)k * C + j;
+    st.q_idx[to] = (int32_t)(c.first + q);
+    st.q_e[to] = sp.q_e[from];
+    st.q_t[to] = sp.q_t[from];
+    st.q_r[to] = sp.q_r[from];
+  }
+  if (st.m_head)
+    for (int j = l; j < z.m_count; j += 32) {
+      const size_t from = slot * QN + ((z.m_n - z.m_count + j) & (QN - 1)), to = (size_t)k * C + j;
+      st.m_idx[to] = sp.m_idx[from];
+      st.m_es[to] = sp.m_es[from];
+      st.m_t[to] = sp.m_t[from];
+      st.m_r[to] = sp.m_r[from];
+      st.m_x[to] = sp.m_x[from];
+    }
+  if (l == 0) {
+    st.cur[k] = z.cur;
+    st.t_w[k] = z.t_w;
+    st.r_prev[k] = z.r_prev;
+    st.pos[k] = z.pos;
+    st.head[k] = 0;
+    st.count[k] = z.count;
+    if (st.m_head) {
+      st.m_head[k] = 0;
+      st.m_count[k] = z.m_count;
+      st.m_inpq[k] = z.m_inpq;
+      st.x_prev[k] = z.x_prev;
+    }
+  }
+}
+
+hipError_t launch_split_import(const DevState& s, const SplitBufs& sp, int tiles, int32_t n_sub,
+                               int32_t C, int32_t W, hipStream_t stream) {
+  hipLaunchKernelGGL(split_import_kernel, dim3(tiles), dim3(MT * 32), 0, stream, s, sp, n_sub, C,
+                     W);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_export(const DevState& s, const SplitBufs& sp, int tiles, int in,
+                               int32_t C, int32_t W, hipStream_t stream) {
+  hipLaunchKernelGGL(split_export_kernel, dim3(tiles), dim3(MT * 32), 0, stream, s, sp, in, C, W);
+  return hipGetLastError();
+}
+
+template <class Net, class P, bool DEP>
+static hipError_t launch_split_step_t(const DevWeights& w, uint32_t relu, const DevState& s,
+                                      const StepParams& p, const SplitBufs& sp, SplitShape sh,
+                                      int tiles, int in, int finish, int predict,
+                                      hipStream_t stream) {
+  const dim3 block(Geo<Net, P>::NT);
+  if (!predict) sh = SplitShape{1, 1};  // the head and the update only
+  const dim3 grid((unsigned)(tiles * sh.units * sh.slices));
+  if (sh.slices == 4)
+    hipLaunchKernelGGL((split_step_kernel<Net, P, DEP, 4>), grid, block, 0, stream, w, relu, s, p,
+                       sp, sh.units, in, finish, predict);
+  else if (sh.slices == 2)
+    hipLaunchKernelGGL((split_step_kernel<Net, P, DEP, 2>), grid, block, 0, stream, w, relu, s, p,
+                       sp, sh.units, in, finish, predict);
+  else
+    hipLaunchKernelGGL((split_step_kernel<Net, P, DEP, 1>), grid, block, 0, stream, w, relu, s, p,
+                       sp, sh.units, in, finish, predict);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t relu,
+                             const DevState& s, const StepParams& p, const SplitBufs& sp,
+                             SplitShape sh, int tiles, int in, int finish, int predict,
+                             hipStream_t stream) {
+  auto go = [&](auto net_tag, auto form_tag, auto dep_tag) {
+    return launch_split_step_t<decltype(net_tag), decltype(form_tag), decltype(dep_tag)::value>(
+        w, relu, s, p, sp, sh, tiles, in, finish, predict, stream);
+  };
+  using No = std::false_type;
+  using Yes = std::true_type;
+  if (net == 1 && p.col_dep >= 0)
+    return prec == 0   ? go(NetC3V3{}, PF32{}, Yes{})
+           : prec == 1 ? go(NetC3V3{}, PBF16{}, Yes{}) : go(NetC3V3{}, PFP8{}, Yes{});
+  if (net == 1)
+    return prec == 0   ? go(NetC3V3{}, PF32{}, No{})
+           : prec == 1 ? go(NetC3V3{}, PBF16{}, No{}) : go(NetC3V3{}, PFP8{}, No{});
+  if (net == 3 && prec <= 1)
+    return prec == 0 ? go(NetC3Hyb{}, PF32{}, No{}) : go(NetC3Hyb{}, PBF16{}, No{});
+  if (net == 4 && prec <= 1)
+    return prec == 0 ? go(NetC3S{}, PF32{}, No{}) : go(NetC3S{}, PBF16{}, No{});
+  return hipErrorInvalidValue;
+}
+
+// --------------------------------------------------------------- forward ---
+
+// Explicit windows x [B][L][D]: each group's sums, as split_step_kernel;
+// SAVE (training form): the convolutions' outputs kept too (by slice 0).
+template <class Net, class P, int CS, bool SAVE>
+__global__ void __launch_bounds__(Net::WAVES * 64)
+    split_forward_kernel(DevWeights wt, uint32_t relu_mask, const float* __restrict__ x, int64_t B,
+                         float* __restrict__ sums, int units, SaveBlock sb) {
+  using G = Geo<Net, P>;
+  using GA = Gather<Net, P>;
+  using T = typename P::T;
+  constexpr int BS = Net::BS, GSL = GA::GSL, TPR = GA::TPR, CPT = GA::CPT;
+  __shared__ NetSmem<Net, P> sm;
+  const int tid = threadIdx.x;
+  const int per = units * CS, tile = blockIdx.x / per, uc = blockIdx.x % per;
+  const int unit = uc / CS, slice = uc % CS;
+  const int64_t b0 = (int64_t)tile * MT;
+  const int row = tid / TPR, part = tid % TPR;
+  const int s = row / GSL, t = row % GSL;
+  if constexpr (P::SCALED) {
+    for (int i = tid; i < Net::D; i += G::NT) sm.x_inv[i] = wt.x_inv[i];
+    __syncthreads();
+  }
+  auto load = [&](int j0, int nb) {
+    return request_window_row<Net, CPT, TPR>(x, B, b0 + s, j0 * BS + t, t < nb * BS, part);
+  };
+  auto commit = [&](int j0, int nb, const RowRegs<CPT>& r, T* X) {
+    (void)j0;
+    if (t < nb * BS) commit_window_row<Net, P>(sm.x_inv, s, t, part, r, X);
+  };
+  SavePtrs<T> sv{};
+  if constexpr (SAVE) {
+    sv.a1 = static_cast<T*>(sb.a1) + b0 * (Net::NB * BS / 2) * Net::CH1;
+    sv.a2 = static_cast<T*>(sb.a2) + b0 * (Net::NB * BS / 4) * Net::CH2;
+    sv.a3 = static_cast<T*>(sb.a3) + b0 * Net::NB * Net::CH3;
+    sv.rows = slice == 0 ? (int)(B - b0 < MT ? B - b0 : MT) : 0;
+  }
+  run_units<Net, P, CS, SAVE>(wt, relu_mask, sm, tile, unit_begin<Net, P>(unit, units),
+                              unit_begin<Net, P>(unit + 1, units), slice,
+                              reinterpret_cast<float4*>(sums), sv, load, commit);
+}
+
+// The head on a tile's sums: raw outputs, or (SAVE) the hidden layer.
+template <class Net, class P, bool SAVE>
+__global__ void __launch_bounds__(Net::WAVES * 64)
+    split_head_kernel(DevWeights wt, uint32_t relu_mask, const float* __restrict__ sums, int64_t B,
+                      float* __restrict__ logits, void* __restrict__ h) {
+  using T = typename P::T;
+  __shared__ NetSmem<Net, P> sm;
+  const int tid = threadIdx.x, tile = blockIdx.x;
+  const int64_t b0 = (int64_t)tile * MT;
+  v4f hacc[(Net::HID / 16) / Net::WAVES];
+  add_groups<Net, P>(reinterpret_cast<const float4*>(sums), tile, hacc, tid >> 6, tid & 63);
+  SavePtrs<T> sv{};
+  if constexpr (SAVE) {
+    sv.h = static_cast<T*>(h) + b0 * Net::HID;
+    sv.rows = (int)(B - b0 < MT ? B - b0 : MT);
+  } else {
+    sm.stage_head(wt, tid, Net::WAVES * 64);
+    __syncthreads();
+  }
+  head_tile<Net, P, false, SAVE>(wt, relu_mask, sm, hacc, nullptr, nullptr, sv);
+  if constexpr (!SAVE) {
+    __syncthreads();
+    if (tid < MT * Net::NOUT) {
+      const int s = tid / Net::NOUT, o = tid % Net::NOUT;
+      if (b0 + s < B) logits[(b0 + s) * Net::NOUT + o] = sm.logit[s][o];
+    }
+  }
+}
+
+template <class Net, class P, bool SAVE>
+static hipError_t launch_split_forward_t(const DevWeights& w, uint32_t relu, const float* x,
+                                         int64_t B, float* logits, const SaveBlock& sb,
+                                         float* sums, SplitShape sh, hipStream_t stream) {
+  const unsigned tiles = (unsigned)((B + MT - 1) / MT);
+  const dim3 block(Geo<Net, P>::NT), grid(tiles * sh.units * sh.slices);
+  if (sh.slices == 4)
+    hipLaunchKernelGGL((split_forward_kernel<Net, P, 4, SAVE>), grid, block, 0, stream, w, relu,
+                       x, B, sums, sh.units, sb);
+  else if (sh.slices == 2)
+    hipLaunchKernelGGL((split_forward_kernel<Net, P, 2, SAVE>), grid, block, 0, stream, w, relu,
+                       x, B, sums, sh.units, sb);
+  else
+    hipLaunchKernelGGL((split_forward_kernel<Net, P, 1, SAVE>), grid, block, 0, stream, w, relu,
+                       x, B, sums, sh.units, sb);
+  hipLaunchKernelGGL((split_head_kernel<Net, P, SAVE>), dim3(tiles), block, 0, stream, w, relu,
+                     sums, B, logits, sb.h);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t relu,
+                                const float* x, int64_t B, float* logits, const SaveBlock& sb,
+                                float* sums, SplitShape sh, hipStream_t stream) {
+  auto go = [&](auto net_tag, auto form_tag, auto save_tag) {
+    return launch_split_forward_t<decltype(net_tag), decltype(form_tag),
+                                  decltype(save_tag)::value>(w, relu, x, B, logits, sb, sums, sh,
+                                                             stream);
+  };
+  using No = std::false_type;
+  using Yes = std::true_type;
+  if (net == 1)
+    return prec == 0   ? go(NetC3V3{}, PF32{}, No{})
+           : prec == 1 ? go(NetC3V3{}, PBF16{}, No{}) : go(NetC3V3{}, PFP8{}, No{});
+  if (net == 2 && prec <= 1)
+    return prec == 0 ? go(NetC3V3{}, PF32{}, Yes{}) : go(NetC3V3{}, PBF16{}, Yes{});
+  if (net == 3 && prec <= 1)
+    return prec == 0 ? go(NetC3Hyb{}, PF32{}, No{}) : go(NetC3Hyb{}, PBF16{}, No{});
+  if (net == 4 && prec <= 1)
+    return prec == 0 ? go(NetC3S{}, PF32{}, No{}) : go(NetC3S{}, PBF16{}, No{});
+  return hipErrorInvalidValue;
+}
+
+}  // namespace simnet

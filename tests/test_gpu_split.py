@@ -1,0 +1,149 @@
+"""Few windows spread over several workgroups per tile (the split step and
+forward) against the one-workgroup-per-tile kernels, which the other tests
+hold to the oracle: the same products summed in the same order, so every
+output, cycle and counter is identical.  With fewer slots than sub-traces a
+run takes the one-workgroup step; with a slot for each it is split (2, 66 and
+128 tiles: column slices, one unit per group or several groups per unit).
+Batches above 2,048 windows take the one-workgroup forward."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+D, L = 50, 111
+COLS = synth.dynamic_columns(D)
+KEYS = ("fetch", "drain", "final", "warm_tick", "total", "n_clamped", "n_nonfinite")
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+@pytest.fixture(scope="module")
+def sn():
+    import paper_2105_05821_amd as m
+    m.lib()
+    return m
+
+
+NETS = {"c3": (synth.net_c3, synth.OUT_BIAS), "dep": (synth.net_c3, synth.OUT_BIAS),
+        "hyb": (synth.net_c3_hybrid_infer, synth.HYB_BIAS),
+        "st": (synth.net_c3_store, synth.OUT_BIAS_STORE)}
+
+
+def streams(n_sub, seed):
+    length = synth.loguniform_lengths(seed, n_sub, 1, 24)
+    start = np.concatenate([[0], np.cumsum(length)[:-1]]).astype(np.int64)
+    return start, length, np.minimum(start, length % 7).astype(np.int32)
+
+
+def simulator(sn, torch, net, prec, start, length, warm, codes=False):
+    n = int(start[-1] + length[-1])
+    feat = (synth.trace_codes(1, n).view(np.int32) if codes
+            else synth.trace_features(1, n, D))
+    mem = (torch.from_numpy(synth.trace_mem(1, n).view(np.int32)).cuda() if net == "dep"
+           else None)
+    s = sn.Simulator(torch.from_numpy(feat).cuda(), L, COLS, start, length, warm, prec=prec,
+                     n_feat=D, n_out=3 if net == "st" else 2, store_col=synth.STORE_COL,
+                     mem=mem, col_dep=synth.DEP_COLS if net == "dep" else -1)
+    layers, bias = NETS[net][0](), NETS[net][1]
+    s.load_weights(layers, sn.flat_params(*synth.init_weights(2, layers, out_bias=bias)))
+    if prec == sn.SIM_FP8E4M3:
+        s.calibrate(4)
+    return s
+
+
+def same(a, b):
+    for k in KEYS:
+        np.testing.assert_array_equal(a[k], b[k], err_msg=k)
+
+
+@pytest.mark.parametrize("net,prec,n_sub,codes", [
+    ("c3", 1, 17, False), ("c3", 1, 1041, True), ("c3", 1, 2048, False), ("c3", 0, 17, True),
+    ("c3", 0, 600, False), ("c3", 2, 300, False), ("dep", 1, 40, False), ("dep", 0, 40, True),
+    ("hyb", 1, 530, True), ("hyb", 0, 33, False), ("st", 1, 290, False), ("st", 0, 290, True)])
+def test_split_step_equals_one_workgroup(torch, sn, net, prec, n_sub, codes):
+    start, length, warm = streams(n_sub, 3)
+    s = simulator(sn, torch, net, prec, start, length, warm, codes)
+    n_out = NETS[net][0]()[-1].c_out
+    got = torch.zeros((s.n_pred, n_out), device="cuda")
+    want = torch.full_like(got, np.nan)
+    s.record_logits(got)
+    a = s.run()                     # split
+    s.reset()
+    got2 = torch.zeros_like(got)
+    s.record_logits(got2)
+    for n in (1, 5, 2):             # in pieces
+        s.step(n)
+    b = s.run()
+    s.set_tuning(0, (n_sub + 15) // 16 - 1)
+    s.record_logits(want)
+    c = s.run()                     # one workgroup per tile, slots refilled
+    same(a, c)
+    same(b, c)
+    assert torch.equal(got, want) and torch.equal(got2, want)
+    s.close()
+
+
+@pytest.mark.parametrize("net,prec", [("c3", 1), ("st", 1), ("st", 0), ("hyb", 0)])
+def test_split_and_injected_steps_alternate(torch, sn, net, prec):
+    """Steps of both kinds share one state: injected latencies run on the
+    one-workgroup step, shadow steps with the same latencies are split; long
+    fetch-free runs fill the processor queue past its 110 entries."""
+    n_sub, n = 18, 400
+    start = np.arange(n_sub, dtype=np.int64) * n
+    length = np.full(n_sub, n, np.int64)
+    length[3], length[7] = 150, 9
+    s = simulator(sn, torch, net, prec, start, length, np.zeros(n_sub, np.int32))
+    t = synth.latency_table(4, s.n_pred, 3 if net == "st" else 2, e_max=300, heavy=0.05)
+    t[::1, 0] *= np.random.default_rng(1).random(len(t)) < 0.3
+    table = torch.from_numpy(t).cuda()
+    want = s.run(sn.SIM_LAT_INJECT, table)
+    s.reset()
+    for i, m in enumerate((3, 130, 1, 7, 25, 60, 2)):
+        s.step(m, sn.SIM_LAT_INJECT if i % 2 == 0 else sn.SIM_LAT_SHADOW, table)
+    got = s.run(sn.SIM_LAT_SHADOW, table)
+    for k in ("fetch", "drain", "final", "warm_tick", "total"):
+        np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+    s.close()
+
+
+@pytest.mark.parametrize("net,prec", [("c3", 0), ("c3", 1), ("c3", 2), ("hyb", 0), ("hyb", 1),
+                                      ("st", 0), ("st", 1)])
+def test_split_forward_equals_one_workgroup(torch, sn, net, prec):
+    s = simulator(sn, torch, net, prec, np.array([0]), np.array([8]), np.array([0], np.int32))
+    x = torch.randn((2049, L, D), generator=torch.Generator().manual_seed(3)).cuda()
+    want = s.forward(x)
+    for B in (1, 16, 17, 600, 1030, 2048):
+        assert torch.equal(s.forward(x[:B].contiguous()), want[:B]), B
+    s.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_split_training_forward_equals_one_workgroup(torch, sn, prec):
+    layers = synth.net_c3_hybrid()
+    ws, bs = synth.init_weights(2, layers, out_bias=None, out_gain=1.0)
+    pred = sn.Predictor(layers, prec)
+    pred.load_weights(layers, sn.flat_params(ws, bs))
+    x = torch.randn((2049, L, D), generator=torch.Generator().manual_seed(3)).cuda()
+    sizes = (52 * 64, 26 * 128, 13 * 256, 512)
+
+    def parts(save, B):
+        v = save[:pred.save_bytes(B)].view(torch.float32 if prec == 0 else torch.int16)
+        at = np.cumsum([0] + [B * n for n in sizes])
+        return [v[at[i]:at[i + 1]].view(B, n) for i, n in enumerate(sizes)]
+
+    z, save = pred.forward(x)
+    want = parts(save, 2049)
+    for B in (1, 17, 1030, 2048):
+        zb, sb = pred.forward(x[:B].contiguous())
+        assert torch.equal(zb, z[:B]), B
+        for g, w in zip(parts(sb, B), want):
+            assert torch.equal(g, w[:B]), B
+    pred.close()
