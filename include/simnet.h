@@ -184,9 +184,10 @@ SIMNET_API int sim_init(const sim_config* cfg, const sim_trace* trace, sim_ctx**
  * residual network, FP32 and BF16 forms): the three C3 convolutions, seven
  * residual blocks (kind 2: 256 -> 1920 with ReLU, kind 3: 1920 -> 256 with
  * ReLU), fc 3328 -> 512 (ReLU), fc 512 -> 22 (the hybrid head); its steps
- * run as four launches each (sim_step stays asynchronous; sim_run checks
- * progress between batches of steps, and with a graph requested still runs
- * them eagerly).  SIM_EUNSUPPORTED if no kernel exists for the shape,
+ * run as three or four launches each (sim_step stays asynchronous; with more
+ * sub-traces than sim_step spreads over the compute units sim_run checks
+ * progress between batches of steps; with a graph requested they still run
+ * eagerly).  SIM_EUNSUPPORTED if no kernel exists for the shape,
  * SIM_ENONFINITE on NaN/Inf.  Resets the simulation state. */
 SIMNET_API int sim_load_weights(sim_ctx* ctx, const sim_layer* layers, int32_t n_layers,
                      const float* params, int32_t on_device);

@@ -550,7 +550,7 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
 // weights are loaded (nothing is allocated in a step or a forward).  Without
 // them (an allocation failed) every tile runs on one workgroup.
 static void ensure_split(sim_ctx* c) {
-  if (c->split_block || c->net == 0 || c->net == 5) return;
+  if (c->split_block || c->net == 0) return;
   const size_t groups = (size_t)split_groups(c->net, c->cfg.prec);
   const size_t slots = c->has_trace && c->n_wg_max <= SPLIT_MAX_TILES ? (size_t)c->n_wg_max * MT : 0;
   const size_t ring = slots * SPLIT_RING, mring = c->cfg.n_out == 3 ? ring : 0;
@@ -1303,7 +1303,7 @@ static hipError_t rb_step(sim_ctx* c, int32_t mode, const int32_t* table) {
   hipError_t e = launch_rb_stage(c->cfg.prec, 1, c->w, c->relu, c->st, p, c->stream);
   if (e == hipSuccess)
     e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_trunk, slots * NetRB7::NB,
-                         c->rb_active, c->stream);
+                         c->rb_active, c->n_cu, c->stream);
   if (e == hipSuccess)
     e = launch_rb_head(c->cfg.prec, c->w, c->relu, c->rb_trunk, slots, c->rb_active,
                        c->rb_logits, c->stream);
@@ -1348,7 +1348,7 @@ static bool capturing(hipStream_t s) {
 // that `steps` launches are known to end the run), and not under capture (a
 // graph takes the persistent kernel's one node).
 static bool split_step(const sim_ctx* c, int32_t mode) {
-  return (c->net == 1 || c->net == 3 || c->net == 4) && mode != SIM_LAT_INJECT && c->split.cst &&
+  return (c->net == 1 || c->net >= 3) && mode != SIM_LAT_INJECT && c->split.cst &&
          (int64_t)c->n_wg * MT >= c->n_sub && split_shape(c, c->n_wg).units >= 2 &&
          !capturing(c->stream);
 }
@@ -1370,6 +1370,14 @@ static hipError_t split_steps(sim_ctx* c, int64_t n_steps, int32_t mode, const i
     e = launch_split_step(c->net, c->cfg.prec, c->w, c->relu, c->st, p, c->split,
                           split_shape(c, tiles), tiles, in, i > 0, i < n, c->stream);
     if (i > 0) in ^= 1;
+    if (c->net == 5 && i < n && e == hipSuccess) {  // the blocks, then FC 512's sums
+      const int64_t win = std::min<int64_t>((int64_t)tiles * MT, c->n_sub);
+      e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_trunk, win * NetRB7::NB,
+                           c->rb_active, c->n_cu, c->stream);
+      if (e == hipSuccess)
+        e = launch_split_fc(c->cfg.prec, c->w, c->rb_trunk, win, c->rb_active, c->split.part,
+                            split_shape(c, tiles), c->stream);
+    }
   }
   if (e == hipSuccess)
     e = launch_split_export(c->st, c->split, all, in, c->C, c->cfg.retire_width, c->stream);
@@ -1390,13 +1398,13 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
   if (c->ran_to_end) return SIM_OK;  // every sub-trace has already finished
   if (n_steps == 0) return SIM_OK;   // checks only
   if (n_steps >= INT32_MAX) c->ran_to_end = true;
-  if (c->net == 5 && mode != SIM_LAT_INJECT) return rb_launch(c, n_steps, mode, table);
   if (split_step(c, mode)) {
     const hipError_t e = split_steps(c, n_steps, mode, table);
     if (e != hipSuccess) return hip_fail(c, e, "split step launch");
     c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
     return SIM_OK;
   }
+  if (c->net == 5 && mode != SIM_LAT_INJECT) return rb_launch(c, n_steps, mode, table);
   const StepParams p = step_params(c, n_steps, mode, table);
   // (injected latencies need no predictor: RB7 shares the hybrid head's step)
   hipError_t e = launch_step(c->net == 5 ? 3 : c->net, c->cfg.prec, c->variant, c->w, c->relu,
@@ -1514,13 +1522,23 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
       if (e != hipSuccess) return hip_fail(c, e, "hipMalloc RB7 workspace");
       c->rb_ws_B = B;
     }
-    hipError_t e = launch_rb_trunk(c->cfg.prec, c->w, c->relu, static_cast<const float*>(x), B,
-                                   c->rb_ws, c->stream);
+    const SplitShape sh = split_shape(c, (B + MT - 1) / MT);
+    const bool split = sh.units >= 2;
+    hipError_t e = split ? launch_split_trunk(c->cfg.prec, c->w, c->relu,
+                                              static_cast<const float*>(x), B, c->rb_ws, sh,
+                                              c->stream)
+                         : launch_rb_trunk(c->cfg.prec, c->w, c->relu,
+                                           static_cast<const float*>(x), B, c->rb_ws, c->stream);
     if (e == hipSuccess)
-      e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_ws, B * NetRB7::NB, nullptr,
+      e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_ws, B * NetRB7::NB, nullptr, c->n_cu,
                            c->stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && split) {
+      e = launch_split_fc(c->cfg.prec, c->w, c->rb_ws, B, nullptr, c->split.part, sh, c->stream);
+      if (e == hipSuccess)
+        e = launch_split_rb_head(c->cfg.prec, c->w, c->relu, c->split.part, B, logits, c->stream);
+    } else if (e == hipSuccess) {
       e = launch_rb_head(c->cfg.prec, c->w, c->relu, c->rb_ws, B, nullptr, logits, c->stream);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "RB7 forward");
     return SIM_OK;
   }

@@ -23,7 +23,8 @@
 // launch and are written back to HBM when the launch ends.  RB7, whose
 // residual blocks do not fit this loop, runs each step as four launches
 // (the step kernel's stages 1 and 2 around resblock_kernel and
-// rb_head_kernel).
+// rb_head_kernel).  Few sub-traces (a slot for each, at most 2,048) take the
+// split step of split.hip instead.
 //
 // Precision forms: weights and activations in FP32, BF16 or FP8 (OCP e4m3,
 // per-channel power-of-two scales), products accumulated in FP32 in every
@@ -1063,6 +1064,9 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
 // while the following chunk is expanded; the projection's TM x CH3
 // accumulators stay in registers for the whole block; then bias, the block
 // input and the ReLU, rounded to the form, replace the tile.
+// Bound by each CU's weight stream and LDS reads beside the MFMAs: BF16, 128
+// rows 360 us (0.69 of the 32x32x16 instruction's sustained rate), 64 rows
+// 205, 32 rows 172 (the weights' 100 us at the port's rate and their latency).
 
 // The matrix instruction of a form in the residual blocks: BF16 on
 // 32x32x16 tiles, FP32 on 16x16x4.
@@ -1075,27 +1079,32 @@ struct ResMma<PBF16> {
   using M = PBF16W;
 };
 
-template <class P>
+// Rows per tile TM and the waves' split: WNW along N (4: two along M, each
+// weight fragment then requested by two waves; 8: one along M, each fragment
+// requested once).  Chunks of EC expansion channels; the last may be shorter
+// (ET), its expansion on the waves it reaches.
+template <class P, int ROWS, int WN>
 struct ResGeo {
   using T = typename P::T;
   using M = typename ResMma<P>::M;
-  static constexpr int C = NetRB7::CH3, E = NetRB7::EXPAND, EC = 128;
-  static constexpr int TM = P::ID == 0 ? 64 : 128, TILE = M::TILE, MTL = TM / TILE;
+  static constexpr int C = NetRB7::CH3, E = NetRB7::EXPAND;
+  static constexpr int TM = ROWS, TILE = M::TILE, MTL = TM / TILE;
+  static constexpr int EC = TILE * WN > 128 ? TILE * WN : 128, ET = E % EC;
+  static constexpr int NCH = (E + EC - 1) / EC;
   static constexpr int PAD = 16 / sizeof(T);
   static constexpr int SXR = C + PAD, SHR = EC + PAD;  // padded LDS rows
-  // waves 4 along N x 2 along M in both products
-  static constexpr int WAVES = 8, NT = WAVES * 64, WNW = 4, WMW = WAVES / WNW;
+  static constexpr int WAVES = 8, NT = WAVES * 64, WNW = WN, WMW = WAVES / WNW;
   static constexpr int MPW = MTL / WMW, NPE = EC / TILE / WNW, NPP = C / TILE / WNW;
-  static_assert(E % EC == 0 && MTL % WMW == 0 && NPE * WNW * TILE == EC &&
-                    NPP * WNW * TILE == C,
+  static_assert(MPW >= 1 && MTL % WMW == 0 && NPE * WNW * TILE == EC && NPP * WNW * TILE == C &&
+                    E % (NPE * TILE) == 0 && ET % M::KG == 0,
                 "wave split");
 };
 
-template <class P>
-__global__ void __launch_bounds__(ResGeo<P>::NT)
+template <class P, int ROWS, int WN>
+__global__ void __launch_bounds__((ResGeo<P, ROWS, WN>::NT))
     resblock_kernel(DevWeights wt, uint32_t relu_mask, typename P::T* __restrict__ x, int64_t rows,
                     const int32_t* __restrict__ active) {
-  using RG = ResGeo<P>;
+  using RG = ResGeo<P, ROWS, WN>;
   using M = typename RG::M;
   using T = typename P::T;
   using Acc = typename M::Acc;
@@ -1104,7 +1113,7 @@ __global__ void __launch_bounds__(ResGeo<P>::NT)
   constexpr int MPW = RG::MPW, NPE = RG::NPE, NPP = RG::NPP;
   constexpr int NG4 = TILE * TILE / 256;  // 4-column groups per lane and tile
   constexpr int CV = C * (int)sizeof(T) / 16, EPV = 16 / (int)sizeof(T);
-  constexpr int KGE = C / M::KG, KGP = EC / M::KG, NCH = E / EC, NTE = E / TILE, NTP = C / TILE;
+  constexpr int KGE = C / M::KG, KGP = EC / M::KG, NCH = RG::NCH, NTE = E / TILE, NTP = C / TILE;
   __shared__ alignas(16) T xs[TM * RG::SXR];
   __shared__ alignas(16) T hs[2 * TM * RG::SHR];  // two expansion chunks
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -1143,6 +1152,7 @@ __global__ void __launch_bounds__(ResGeo<P>::NT)
   // Expansion of chunk u into hs buffer u & 1: bias, ReLU, rounded to the form.
   auto expand = [&](int u) {
     const int blk = u / NCH, ch = u % NCH;
+    if (RG::ET && ch * EC + wn * NPE * TILE >= E) return;  // (past a short last chunk)
     const uint4* We = reinterpret_cast<const uint4*>(static_cast<const char*>(wt.res_w) +
                                                      (size_t)blk * wt.res_stride);
     const float* be = wt.res_b + (size_t)blk * (E + C);
@@ -1190,6 +1200,11 @@ __global__ void __launch_bounds__(ResGeo<P>::NT)
     const T* aphu[MPW];
 #pragma unroll
     for (int i = 0; i < MPW; ++i) aphu[i] = aph[i] + ho;
+    if constexpr (RG::ET > 0)
+      if (ch == NCH - 1) {
+        mma_stream<M, RG::ET / M::KG, NTP, NPP, MPW>(yacc, aphu, Wp, wn * NPP, lane);
+        return;
+      }
     mma_stream<M, KGP, NTP, NPP, MPW>(yacc, aphu, Wp, wn * NPP, lane);
   };
   // Chunk u+1's expansion and chunk u's projection share a phase (one
@@ -1672,22 +1687,60 @@ hipError_t launch_rb_stage(int prec, int stage, const DevWeights& w, uint32_t re
   return hipErrorInvalidValue;
 }
 
-template <class P>
+template <class P, int ROWS, int WN>
 static hipError_t launch_resblocks_t(const DevWeights& w, uint32_t relu, void* x, int64_t rows,
                                      const int32_t* active, hipStream_t stream) {
-  const int64_t tiles = (rows + ResGeo<P>::TM - 1) / ResGeo<P>::TM;
+  const int64_t tiles = (rows + ROWS - 1) / ROWS;
   if (tiles > INT32_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((resblock_kernel<P>), dim3((unsigned)tiles), dim3(ResGeo<P>::NT), 0, stream,
-                     w, relu, static_cast<typename P::T*>(x), rows, active);
+  hipLaunchKernelGGL((resblock_kernel<P, ROWS, WN>), dim3((unsigned)tiles),
+                     dim3((ResGeo<P, ROWS, WN>::NT)), 0, stream, w, relu,
+                     static_cast<typename P::T*>(x), rows, active);
   return hipGetLastError();
 }
 
+// Rows per tile.  BF16: a workgroup (one per CU) streams all 13.8 MB of
+// weights whatever its rows, so few rows run on small tiles spread over the
+// chip and many on large ones: the tile with the least rounds of workgroups x
+// measured time per round (13,000 rows, 1,000 windows: 128-row tiles 357 us,
+// 64-row 205; 39,000 rows: 128 x 2 rounds 735, 96 x 2 544).  FP32: 16-row
+// tiles, two of which share a CU and hide each other's latency (3,328 rows
+// 740 us against 1,860 with 64-row tiles; 53,248 rows 5.65 ms against 6.82),
+// but 64-row ones where one round of those holds the rows and 48 per CU do
+// not (13,000 rows: 1.89 ms against 2.0).
+struct ResTile {
+  int rows, us;
+};
+
+static int res_tile_bf16(int64_t rows, int n_cu) {
+  constexpr ResTile t[] = {{128, 360}, {96, 275}, {64, 205}, {32, 172}};
+  int best = 0;
+  int64_t least = 0;
+  for (const ResTile& r : t) {
+    const int64_t cu = n_cu > 0 ? n_cu : 1, tiles = (rows + r.rows - 1) / r.rows;
+    const int64_t us = (tiles + cu - 1) / cu * r.us;
+    if (best == 0 || us < least) {
+      least = us;
+      best = r.rows;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_resblocks(int prec, const DevWeights& w, uint32_t relu, void* x, int64_t rows,
-                            const int32_t* active, hipStream_t stream) {
+                            const int32_t* active, int n_cu, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  if (prec == 0) return launch_resblocks_t<PF32>(w, relu, x, rows, active, stream);
-  if (prec == 1) return launch_resblocks_t<PBF16>(w, relu, x, rows, active, stream);
-  return hipErrorInvalidValue;
+  if (prec == 0) {
+    if (rows > (int64_t)48 * n_cu && rows <= (int64_t)64 * n_cu)
+      return launch_resblocks_t<PF32, 64, 4>(w, relu, x, rows, active, stream);
+    return launch_resblocks_t<PF32, 16, 8>(w, relu, x, rows, active, stream);
+  }
+  if (prec != 1) return hipErrorInvalidValue;
+  switch (res_tile_bf16(rows, n_cu)) {
+    case 32: return launch_resblocks_t<PBF16, 32, 8>(w, relu, x, rows, active, stream);
+    case 64: return launch_resblocks_t<PBF16, 64, 8>(w, relu, x, rows, active, stream);
+    case 96: return launch_resblocks_t<PBF16, 96, 8>(w, relu, x, rows, active, stream);
+    default: return launch_resblocks_t<PBF16, 128, 4>(w, relu, x, rows, active, stream);
+  }
 }
 
 hipError_t launch_rb_head(int prec, const DevWeights& w, uint32_t relu, const void* x, int64_t B,

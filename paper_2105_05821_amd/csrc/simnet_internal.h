@@ -347,7 +347,7 @@ hipError_t launch_rb_stage(int prec, int stage, const DevWeights& w, uint32_t re
 // rows whose windows (row / NB) all have active[window] == 0 is skipped
 // (active may be NULL: every row).
 hipError_t launch_resblocks(int prec, const DevWeights& w, uint32_t relu, void* x, int64_t rows,
-                            const int32_t* active, hipStream_t stream);
+                            const int32_t* active, int n_cu, hipStream_t stream);
 // FC 512 and the hybrid head on x [B][NB][CH3] -> logits [B][NOUT].
 hipError_t launch_rb_head(int prec, const DevWeights& w, uint32_t relu, const void* x, int64_t B,
                           const int32_t* active, float* logits, hipStream_t stream);
@@ -405,6 +405,16 @@ hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t re
 hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t relu,
                                 const float* x, int64_t B, float* logits, const SaveBlock& sb,
                                 float* sums, SplitShape sh, hipStream_t stream);
+// RB7 over few windows: the convolutions (launch_split_step with net 5 in a
+// simulation), then launch_resblocks, then FC 512's group sums, then the head
+// (in a simulation the next launch_split_step).
+hipError_t launch_split_trunk(int prec, const DevWeights& w, uint32_t relu, const float* x,
+                              int64_t B, void* out, SplitShape sh, hipStream_t stream);
+hipError_t launch_split_fc(int prec, const DevWeights& w, const void* x, int64_t B,
+                           const int32_t* active, float* sums, SplitShape sh,
+                           hipStream_t stream);
+hipError_t launch_split_rb_head(int prec, const DevWeights& w, uint32_t relu, const float* sums,
+                                int64_t B, float* logits, hipStream_t stream);
 
 // BF16 copy of an FP32 trace [n][D] into out [n][staged_feat(D)].
 hipError_t launch_stage_bf16(const float* feat, int64_t n, int D, uint16_t* out,

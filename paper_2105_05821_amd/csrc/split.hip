@@ -22,6 +22,10 @@
 // us to launch, ~4 us for the sums, head and update, then one group's
 // convolutions (~6 us) and its weights' latency.
 //
+// RB7's step is three launches: this kernel with the convolutions only, the
+// residual blocks, FC 512's group sums (1,000 windows BF16: 28 + 357 + 38 +
+// 10 us in four launches -> 15 + 205 + 15).
+//
 // The queue is a ring of QN = 128 entries indexed by position mod 128: an
 // entry outlives its place among the newest C = 110 by 17 pushes, so the
 // push of a launch never lands on an entry that launch reads, the row of
@@ -75,7 +79,8 @@ __device__ __forceinline__ void add_groups(const float4* part, int tile, v4f* ha
 
 // This workgroup's groups [gb, ge): convolutions and one slice of the hidden
 // FC, each group's sums to memory.  load and commit as in predict_tile.
-template <class Net, class P, int CS, bool SAVE, class Load, class Commit>
+// TRUNK: the convolutions only, the last one's output to sv.a3.
+template <class Net, class P, int CS, bool SAVE, bool TRUNK, class Load, class Commit>
 __device__ __forceinline__ void run_units(const DevWeights& wt, uint32_t relu_mask,
                                           NetSmem<Net, P>& sm, int tile, int gb, int ge, int slice,
                                           float4* part, SavePtrs<typename P::T> sv, Load&& load,
@@ -86,6 +91,7 @@ __device__ __forceinline__ void run_units(const DevWeights& wt, uint32_t relu_ma
   v4f hacc[HT];
   float unused = 0.f;
   auto store = [&](int g) {
+    if constexpr (TRUNK) return;
     float4* dst = group_sums<Net, P>(part, tile, g) +
                   (size_t)FcShape<Net, P, NG, CS>::tile0(slice, wave) * 64 + lane;
 #pragma unroll
@@ -104,7 +110,7 @@ __device__ __forceinline__ void run_units(const DevWeights& wt, uint32_t relu_ma
     lds_barrier();
     const int nj = (g + 1) * NG, nnb = g + 1 < ge ? GR::blocks(g + 1) : 0;
     clear();
-    run_group<Net, P, NG, false, SAVE, false, CS>(
+    run_group<Net, P, NG, false, SAVE, TRUNK, CS>(
         wt, relu_mask, sm, g * NG, nullptr, nullptr, sv, hacc, unused,
         [&]() { return load(nj, nnb); },
         [&](const auto& regs) {
@@ -117,7 +123,7 @@ __device__ __forceinline__ void run_units(const DevWeights& wt, uint32_t relu_ma
     if (ge == GR::N) {
       lds_barrier();
       clear();
-      run_group<Net, P, GR::TAIL, false, SAVE, false, CS>(
+      run_group<Net, P, GR::TAIL, false, SAVE, TRUNK, CS>(
           wt, relu_mask, sm, GR::NFULL * NG, nullptr, nullptr, sv, hacc, unused,
           []() { return 0; }, [](int) {}, slice);
       store(GR::NFULL);
@@ -167,6 +173,7 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
   const bool act = z.pos < c.n_pos;
   if (!__syncthreads_or(act)) {  // nothing left in the tile: the scalars move on
     if (writer && finish && l == 0) sp.scal[in ^ 1][slot] = z;
+    if (Net::NRES > 0 && writer && l == 0) p.active_out[slot] = 0;
     return;
   }
   if constexpr (P::SCALED)
@@ -315,7 +322,10 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
     sm.m_new[s] = z.m_n - z.m_inpq;
     sm.m_vis[s] = z.m_count - z.m_inpq;
   }
-  if (!__syncthreads_or(z.pos < c.n_pos)) return;
+  if (!__syncthreads_or(z.pos < c.n_pos)) {
+    if (Net::NRES > 0 && writer && l == 0) p.active_out[slot] = 0;
+    return;
+  }
 
   constexpr int GSL = GA::GSL, TPR = GA::TPR;
   const int grow = tid / TPR, part = tid % TPR;
@@ -358,9 +368,17 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
     if (gt < nb * BS)
       commit_row<Net, P, false, DEP>(p, sm.net.x_inv, gs, gt, part, r, X, nullptr);
   };
-  run_units<Net, P, CS, false>(wt, relu_mask, sm.net, tile, unit_begin<Net, P>(unit, units),
-                               unit_begin<Net, P>(unit + 1, units), slice,
-                               reinterpret_cast<float4*>(sp.part), {}, load, commit);
+  SavePtrs<T> sv{};
+  constexpr bool TRUNK = Net::NRES > 0;  // (RB7: the rest of the network in its own kernels)
+  if constexpr (TRUNK) {
+    sv.a3 = static_cast<T*>(p.trunk_out) + (size_t)tile * MT * Net::NB * Net::CH3;
+    sv.rows = MT;
+    if (writer && l == 0) p.active_out[slot] = z.pos < c.n_pos;
+  }
+  run_units<Net, P, CS, TRUNK, TRUNK>(wt, relu_mask, sm.net, tile,
+                                      unit_begin<Net, P>(unit, units),
+                                      unit_begin<Net, P>(unit + 1, units), slice,
+                                      reinterpret_cast<float4*>(sp.part), sv, load, commit);
 }
 
 // Sub-trace state -> split form: slot i runs sub-trace order[i] (every
@@ -490,6 +508,82 @@ hipError_t launch_split_export(const DevState& s, const SplitBufs& sp, int tiles
   return hipGetLastError();
 }
 
+// FC 512 of RB7's windows from x [windows][NB][CH3] (the blocks' output):
+// each group's sums, a group staged into LDS where the fused step keeps its
+// last conv output.  Tiles with no active window (NULL: all) are left out.
+template <class P, int CS>
+__global__ void __launch_bounds__(NetRB7::WAVES * 64)
+    split_fc_kernel(DevWeights wt, const typename P::T* __restrict__ x, int64_t B,
+                    const int32_t* __restrict__ active, float* __restrict__ sums, int units) {
+  using Net = NetRB7;
+  using G = Geo<Net, P>;
+  using GR = Groups<Net, P>;
+  constexpr int NG = GR::NG, HT = (Net::HID / 16) / Net::WAVES / CS;
+  constexpr int EV = 16 / (int)sizeof(typename P::T), V = Net::CH3 / EV;
+  __shared__ alignas(16) typename P::T a3[MT * G::SAL];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int per = units * CS, tile = blockIdx.x / per, uc = blockIdx.x % per;
+  const int unit = uc / CS, slice = uc % CS;
+  const int64_t b0 = (int64_t)tile * MT;
+  if (active) {
+    const int a = tid < MT && b0 + tid < B ? active[b0 + tid] : 0;
+    if (!__syncthreads_or(a)) return;
+  }
+  auto group = [&](int g, auto nb_tag) {
+    constexpr int NBG = decltype(nb_tag)::value;
+    auto head = fc_head<Net, P, NBG, CS>(wt, g * NG, wave, lane, slice);
+    for (int i = tid; i < MT * NBG * V; i += G::NT) {
+      const int s = i / (NBG * V), r = i % (NBG * V), jb = r / V, v = r % V;
+      uint4 val = make_uint4(0u, 0u, 0u, 0u);
+      if (b0 + s < B)
+        val = reinterpret_cast<const uint4*>(x + ((b0 + s) * Net::NB + g * NG + jb) * Net::CH3)[v];
+      *reinterpret_cast<uint4*>(a3 + s * G::SAL + jb * Net::CH3 + v * EV) = val;
+    }
+    lds_barrier();
+    v4f hacc[HT];
+#pragma unroll
+    for (int j = 0; j < HT; ++j) hacc[j] = v4f{0.f, 0.f, 0.f, 0.f};
+    hidden_fc<Net, P, NBG, true, CS>(wt, a3, g * NG, hacc, wave, lane, &head, slice);
+    float4* dst = group_sums<Net, P>(reinterpret_cast<float4*>(sums), tile, g) +
+                  (size_t)FcShape<Net, P, NBG, CS>::tile0(slice, wave) * 64 + lane;
+#pragma unroll
+    for (int j = 0; j < HT; ++j)
+      dst[j * 64] = make_float4(hacc[j][0], hacc[j][1], hacc[j][2], hacc[j][3]);
+    lds_barrier();
+  };
+  const int gb = unit_begin<Net, P>(unit, units), ge = unit_begin<Net, P>(unit + 1, units);
+  for (int g = gb; g < (ge < GR::NFULL ? ge : GR::NFULL); ++g)
+    group(g, std::integral_constant<int, NG>{});
+  if constexpr (GR::TAIL > 0)
+    if (ge == GR::N) group(GR::NFULL, std::integral_constant<int, GR::TAIL>{});
+}
+
+template <class P>
+static hipError_t launch_split_fc_t(const DevWeights& w, const void* x, int64_t B,
+                                    const int32_t* active, float* sums, SplitShape sh,
+                                    hipStream_t stream) {
+  const dim3 grid((unsigned)((B + MT - 1) / MT * sh.units * sh.slices)), block(NetRB7::WAVES * 64);
+  const auto* xt = static_cast<const typename P::T*>(x);
+  if (sh.slices == 4)
+    hipLaunchKernelGGL((split_fc_kernel<P, 4>), grid, block, 0, stream, w, xt, B, active, sums,
+                       sh.units);
+  else if (sh.slices == 2)
+    hipLaunchKernelGGL((split_fc_kernel<P, 2>), grid, block, 0, stream, w, xt, B, active, sums,
+                       sh.units);
+  else
+    hipLaunchKernelGGL((split_fc_kernel<P, 1>), grid, block, 0, stream, w, xt, B, active, sums,
+                       sh.units);
+  return hipGetLastError();
+}
+
+hipError_t launch_split_fc(int prec, const DevWeights& w, const void* x, int64_t B,
+                           const int32_t* active, float* sums, SplitShape sh,
+                           hipStream_t stream) {
+  if (prec == 0) return launch_split_fc_t<PF32>(w, x, B, active, sums, sh, stream);
+  if (prec == 1) return launch_split_fc_t<PBF16>(w, x, B, active, sums, sh, stream);
+  return hipErrorInvalidValue;
+}
+
 template <class Net, class P, bool DEP>
 static hipError_t launch_split_step_t(const DevWeights& w, uint32_t relu, const DevState& s,
                                       const StepParams& p, const SplitBufs& sp, SplitShape sh,
@@ -497,8 +591,13 @@ static hipError_t launch_split_step_t(const DevWeights& w, uint32_t relu, const 
                                       hipStream_t stream) {
   const dim3 block(Geo<Net, P>::NT);
   if (!predict) sh = SplitShape{1, 1};  // the head and the update only
+  if (Net::NRES > 0) sh.slices = 1;      // no hidden FC here
   const dim3 grid((unsigned)(tiles * sh.units * sh.slices));
-  if (sh.slices == 4)
+  if constexpr (Net::NRES > 0) {
+    hipLaunchKernelGGL((split_step_kernel<Net, P, DEP, 1>), grid, block, 0, stream, w, relu, s, p,
+                       sp, sh.units, in, finish, predict);
+    return hipGetLastError();
+  } else if (sh.slices == 4)
     hipLaunchKernelGGL((split_step_kernel<Net, P, DEP, 4>), grid, block, 0, stream, w, relu, s, p,
                        sp, sh.units, in, finish, predict);
   else if (sh.slices == 2)
@@ -530,13 +629,16 @@ hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t re
     return prec == 0 ? go(NetC3Hyb{}, PF32{}, No{}) : go(NetC3Hyb{}, PBF16{}, No{});
   if (net == 4 && prec <= 1)
     return prec == 0 ? go(NetC3S{}, PF32{}, No{}) : go(NetC3S{}, PBF16{}, No{});
+  if (net == 5 && prec <= 1)
+    return prec == 0 ? go(NetRB7{}, PF32{}, No{}) : go(NetRB7{}, PBF16{}, No{});
   return hipErrorInvalidValue;
 }
 
 // --------------------------------------------------------------- forward ---
 
 // Explicit windows x [B][L][D]: each group's sums, as split_step_kernel;
-// SAVE (training form): the convolutions' outputs kept too (by slice 0).
+// SAVE (training form): the convolutions' outputs kept too (by slice 0);
+// RB7: the last conv's output to sb.a3 only.
 template <class Net, class P, int CS, bool SAVE>
 __global__ void __launch_bounds__(Net::WAVES * 64)
     split_forward_kernel(DevWeights wt, uint32_t relu_mask, const float* __restrict__ x, int64_t B,
@@ -563,16 +665,21 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
     (void)j0;
     if (t < nb * BS) commit_window_row<Net, P>(sm.x_inv, s, t, part, r, X);
   };
+  constexpr bool TRUNK = Net::NRES > 0;
   SavePtrs<T> sv{};
-  if constexpr (SAVE) {
+  if constexpr (TRUNK) {
+    sv.a3 = static_cast<T*>(sb.a3) + b0 * Net::NB * Net::CH3;
+    sv.rows = (int)(B - b0 < MT ? B - b0 : MT);
+  } else if constexpr (SAVE) {
     sv.a1 = static_cast<T*>(sb.a1) + b0 * (Net::NB * BS / 2) * Net::CH1;
     sv.a2 = static_cast<T*>(sb.a2) + b0 * (Net::NB * BS / 4) * Net::CH2;
     sv.a3 = static_cast<T*>(sb.a3) + b0 * Net::NB * Net::CH3;
     sv.rows = slice == 0 ? (int)(B - b0 < MT ? B - b0 : MT) : 0;
   }
-  run_units<Net, P, CS, SAVE>(wt, relu_mask, sm, tile, unit_begin<Net, P>(unit, units),
-                              unit_begin<Net, P>(unit + 1, units), slice,
-                              reinterpret_cast<float4*>(sums), sv, load, commit);
+  run_units<Net, P, CS, SAVE || TRUNK, TRUNK>(
+      wt, relu_mask, sm, tile, unit_begin<Net, P>(unit, units),
+      unit_begin<Net, P>(unit + 1, units), slice, reinterpret_cast<float4*>(sums), sv, load,
+      commit);
 }
 
 // The head on a tile's sums: raw outputs, or (SAVE) the hidden layer.
@@ -605,6 +712,40 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
 }
 
 template <class Net, class P, bool SAVE>
+static hipError_t launch_split_head_t(const DevWeights& w, uint32_t relu, const float* sums,
+                                      int64_t B, float* logits, void* h, hipStream_t stream) {
+  hipLaunchKernelGGL((split_head_kernel<Net, P, SAVE>), dim3((unsigned)((B + MT - 1) / MT)),
+                     dim3(Geo<Net, P>::NT), 0, stream, w, relu, sums, B, logits, h);
+  return hipGetLastError();
+}
+
+// RB7: convolutions of explicit windows to out [B][NB][CH3].
+template <class P>
+static hipError_t launch_split_trunk_t(const DevWeights& w, uint32_t relu, const float* x,
+                                       int64_t B, void* out, SplitShape sh, hipStream_t stream) {
+  const dim3 grid((unsigned)((B + MT - 1) / MT * sh.units)), block(NetRB7::WAVES * 64);
+  hipLaunchKernelGGL((split_forward_kernel<NetRB7, P, 1, false>), grid, block, 0, stream, w, relu,
+                     x, B, nullptr, sh.units, SaveBlock{nullptr, nullptr, out, nullptr});
+  return hipGetLastError();
+}
+
+hipError_t launch_split_trunk(int prec, const DevWeights& w, uint32_t relu, const float* x,
+                              int64_t B, void* out, SplitShape sh, hipStream_t stream) {
+  if (prec == 0) return launch_split_trunk_t<PF32>(w, relu, x, B, out, sh, stream);
+  if (prec == 1) return launch_split_trunk_t<PBF16>(w, relu, x, B, out, sh, stream);
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_split_rb_head(int prec, const DevWeights& w, uint32_t relu, const float* sums,
+                                int64_t B, float* logits, hipStream_t stream) {
+  if (prec == 0)
+    return launch_split_head_t<NetRB7, PF32, false>(w, relu, sums, B, logits, nullptr, stream);
+  if (prec == 1)
+    return launch_split_head_t<NetRB7, PBF16, false>(w, relu, sums, B, logits, nullptr, stream);
+  return hipErrorInvalidValue;
+}
+
+template <class Net, class P, bool SAVE>
 static hipError_t launch_split_forward_t(const DevWeights& w, uint32_t relu, const float* x,
                                          int64_t B, float* logits, const SaveBlock& sb,
                                          float* sums, SplitShape sh, hipStream_t stream) {
@@ -619,9 +760,7 @@ static hipError_t launch_split_forward_t(const DevWeights& w, uint32_t relu, con
   else
     hipLaunchKernelGGL((split_forward_kernel<Net, P, 1, SAVE>), grid, block, 0, stream, w, relu,
                        x, B, sums, sh.units, sb);
-  hipLaunchKernelGGL((split_head_kernel<Net, P, SAVE>), dim3(tiles), block, 0, stream, w, relu,
-                     sums, B, logits, sb.h);
-  return hipGetLastError();
+  return launch_split_head_t<Net, P, SAVE>(w, relu, sums, B, logits, sb.h, stream);
 }
 
 hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t relu,

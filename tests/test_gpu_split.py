@@ -4,7 +4,8 @@ hold to the oracle: the same products summed in the same order, so every
 output, cycle and counter is identical.  With fewer slots than sub-traces a
 run takes the one-workgroup step; with a slot for each it is split (2, 66 and
 128 tiles: column slices, one unit per group or several groups per unit).
-Batches above 2,048 windows take the one-workgroup forward."""
+Batches above 2,048 windows take the one-workgroup forward.  RB7's residual
+blocks run on tiles of another size per row count."""
 import numpy as np
 import pytest
 
@@ -34,7 +35,8 @@ def sn():
 
 NETS = {"c3": (synth.net_c3, synth.OUT_BIAS), "dep": (synth.net_c3, synth.OUT_BIAS),
         "hyb": (synth.net_c3_hybrid_infer, synth.HYB_BIAS),
-        "st": (synth.net_c3_store, synth.OUT_BIAS_STORE)}
+        "st": (synth.net_c3_store, synth.OUT_BIAS_STORE),
+        "rb7": (synth.net_rb7, synth.HYB_BIAS)}
 
 
 def streams(n_sub, seed):
@@ -67,7 +69,8 @@ def same(a, b):
 @pytest.mark.parametrize("net,prec,n_sub,codes", [
     ("c3", 1, 17, False), ("c3", 1, 1041, True), ("c3", 1, 2048, False), ("c3", 0, 17, True),
     ("c3", 0, 600, False), ("c3", 2, 300, False), ("dep", 1, 40, False), ("dep", 0, 40, True),
-    ("hyb", 1, 530, True), ("hyb", 0, 33, False), ("st", 1, 290, False), ("st", 0, 290, True)])
+    ("hyb", 1, 530, True), ("hyb", 0, 33, False), ("st", 1, 290, False), ("st", 0, 290, True),
+    ("rb7", 1, 33, False), ("rb7", 0, 17, True)])
 def test_split_step_equals_one_workgroup(torch, sn, net, prec, n_sub, codes):
     start, length, warm = streams(n_sub, 3)
     s = simulator(sn, torch, net, prec, start, length, warm, codes)
@@ -115,12 +118,12 @@ def test_split_and_injected_steps_alternate(torch, sn, net, prec):
 
 
 @pytest.mark.parametrize("net,prec", [("c3", 0), ("c3", 1), ("c3", 2), ("hyb", 0), ("hyb", 1),
-                                      ("st", 0), ("st", 1)])
+                                      ("st", 0), ("st", 1), ("rb7", 0), ("rb7", 1)])
 def test_split_forward_equals_one_workgroup(torch, sn, net, prec):
     s = simulator(sn, torch, net, prec, np.array([0]), np.array([8]), np.array([0], np.int32))
     x = torch.randn((2049, L, D), generator=torch.Generator().manual_seed(3)).cuda()
     want = s.forward(x)
-    for B in (1, 16, 17, 600, 1030, 2048):
+    for B in (1, 16, 17, 600, 1000, 1030, 1500, 2048):
         assert torch.equal(s.forward(x[:B].contiguous()), want[:B]), B
     s.close()
 
