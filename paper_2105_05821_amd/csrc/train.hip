@@ -1,19 +1,21 @@
 // Training-form kernels of libsimnet.so (gfx950): the pieces of a predictor
 // training step that are not the fused trunk forward.
 //
-//   gemm kernels     C = op(A) x op(B): FP32 form on FP32 MFMA (64x64
-//                    tiles), BF16 form on BF16 MFMA (128x128 tiles, operands
-//                    rounded to BF16 in LDS); operands in FP32 or BF16 with
-//                    arbitrary strides; split-K with an ordered reduction
-//                    when the output is small; epilogue with bias, ReLU mask
-//                    (a saved activation > 0), accumulation and a column
-//                    permutation of C (weight gradients stored in the
-//                    parameters' own layout).  Used for the head and for
-//                    every input-gradient and weight-gradient product of the
-//                    backward pass (a kernel-2 stride-2 convolution is a
-//                    GEMM over position pairs); the pipelined BF16 kernel
-//                    also sums its left operand's rows (the trunk's bias
-//                    gradients).
+//   gemm kernels     C = op(A) x op(B), operands in FP32 or BF16, split-K with
+//                    an ordered reduction when the output is small; epilogue
+//                    with bias, ReLU mask (a saved activation > 0),
+//                    accumulation and a column permutation of C (weight
+//                    gradients stored in the parameters' own layout).  Used
+//                    for the head and for every input-gradient and
+//                    weight-gradient product of the backward pass (a kernel-2
+//                    stride-2 convolution is a GEMM over position pairs).
+//                    Operands in aligned rows go straight to LDS and are
+//                    transposed on their way out (gemm_bf16_dma_kernel,
+//                    gemm_f32_dma_kernel, which also sum their left operand's
+//                    rows: the trunk's bias gradients); operands of arbitrary
+//                    strides and alignment take gemm_bf16_kernel (128x128
+//                    tiles, rounded to BF16 in LDS) and gemm_kernel (FP32
+//                    MFMA, 64x64 tiles).
 //   reductions       split-K partials summed in order with the epilogue.
 //   loss_kernel      hybrid loss per window (400-bin cross-entropy + L1 on
 //                    log1p(latency) per latency type) and its gradient
@@ -79,14 +81,15 @@ __device__ __forceinline__ void gemm_store(const GemmArgs& g, int64_t m, int64_t
   *c = g.beta ? *c + v : v;
 }
 
-// The same for the four columns n0 + 16*j (j < 4) of one row m, with the
-// row's addresses computed once; the caller has added the bias.
-__device__ __forceinline__ void gemm_store_row4(const GemmArgs& g, int64_t m, int64_t n0,
-                                                const float (&v)[4]) {
+// The same for the columns n0 + 16*j (j < NJ) of one row m, with the row's
+// addresses computed once; the caller has added the bias.
+template <int NJ>
+__device__ __forceinline__ void gemm_store_row(const GemmArgs& g, int64_t m, int64_t n0,
+                                               const float (&v)[NJ]) {
   const int64_t crow = grouped_row(m, g.cgrp, g.cgs, g.ldc);
   const int64_t mrow = g.mask.p ? grouped_row(m, g.mask.grp, g.mask.gs, g.mask.rs) : 0;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     const int64_t n = n0 + 16 * j;
     if (n >= g.N) continue;
     float x = v[j];
@@ -343,94 +346,114 @@ __device__ __forceinline__ void stage_store(uint16_t (*S)[HLD], int mode, int ti
   }
 }
 
-// The BF16 kernels' output: the tile's accumulators (wave (wm, wn) holds
-// rows wm*64 .., columns wn*64 ..) to C through the epilogue (bias, ReLU
-// mask, accumulate, BF16 output), or to the split-K partials.  E: LDS
-// scratch of at least 32 x (HB + 4) floats, free once the products end.
-__device__ __forceinline__ void gemm_bf16_epilogue(const GemmArgs& g, v4f (&acc)[4][4], float* E,
+// The tile kernels' output: a TM x TN tile's accumulators (2 x 2 waves, wave
+// (wm, wn) holding rows wm * TM/2 .., columns wn * TN/2 ..) to C through the
+// epilogue (bias, ReLU mask, accumulate, BF16 output), or to the split-K
+// partials.  E: LDS scratch of epilogue_floats<TN>(), free once the products
+// end.
+template <int TN>
+constexpr int epilogue_floats() {
+  return 32 * (TN + 4);
+}
+
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs& g,
+                                                   v4f (&acc)[TM / 32][TN / 32], float* E,
                                                    int64_t m0, int64_t n0, int wm, int wn, int tid,
                                                    int lane) {
+  constexpr int MI = TM / 32, NI = TN / 32;
   if (g.evec) {
-    // whole 16-byte rows: the tile goes through LDS a quarter at a time (32
-    // rows x 128 columns), and each thread finishes 16 consecutive columns
-    // of one row with vector reads of the mask and previous C and vector
-    // stores (full cache lines per row instead of 64-byte pieces)
-    constexpr int ES = HB + 4;  // row stride of the staged quarter, in floats
-    const int er = tid / 8, ec = (tid % 8) * 16;
-    const int64_t m = m0 + (er / 16) * 64 + (er % 16);  // + i * 16
+    // whole 16-byte rows: the tile goes through LDS 32 rows x TN columns at a
+    // time, and each thread finishes CW consecutive columns of one row with
+    // vector reads of the mask and previous C and vector stores (full cache
+    // lines per row instead of 64-byte pieces)
+    constexpr int ES = TN + 4;  // row stride of the staged rows, in floats
+    constexpr int CW = TN / 8;
+    const int er = tid / 8, ec = (tid % 8) * CW;
+    const int64_t m = m0 + (er / 16) * (TM / 2) + (er % 16);  // + i * 16
+    const int64_t n = n0 + ec;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < MI; ++i) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          E[(wm * 16 + 4 * (lane >> 4) + r) * ES + wn * 64 + j * 16 + (lane & 15)] = acc[i][j][r];
+          E[(wm * 16 + 4 * (lane >> 4) + r) * ES + wn * (TN / 2) + j * 16 + (lane & 15)] =
+              acc[i][j][r];
       __syncthreads();
-      const int64_t mi = m + i * 16, n = n0 + ec;
+      const int64_t mi = m + i * 16;
       if (mi < g.M && n < g.N) {
-        float v[16];
+        float v[CW];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < CW / 4; ++q) {
           const float4 t = *reinterpret_cast<const float4*>(&E[er * ES + ec + 4 * q]);
           v[4 * q] = t.x;
           v[4 * q + 1] = t.y;
           v[4 * q + 2] = t.z;
           v[4 * q + 3] = t.w;
         }
-        if (g.mask.p) {
-          const int64_t a = grouped_row(mi, g.mask.grp, g.mask.gs, g.mask.rs) + n;
-          float mk[16];
-          if (g.mask.bf16) {
-            const uint4* mp =
-                reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g.mask.p) + a);
+        if (g.ksplit > 1) {
+          float4* cp = reinterpret_cast<float4*>(
+              g.part + ((int64_t)blockIdx.z * g.M + mi) * g.N + n);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const uint4 w = mp[h];
-              const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+          for (int q = 0; q < CW / 4; ++q)
+            cp[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+        } else {
+          if (g.mask.p) {
+            const int64_t a = grouped_row(mi, g.mask.grp, g.mask.gs, g.mask.rs) + n;
+            float mk[CW];
+            if (g.mask.bf16) {
+              const uint4* mp =
+                  reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(g.mask.p) + a);
 #pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                mk[8 * h + 2 * q] = __uint_as_float(ws[q] << 16);
-                mk[8 * h + 2 * q + 1] = __uint_as_float(ws[q] & 0xffff0000u);
+              for (int h = 0; h < CW / 8; ++h) {
+                const uint4 w = mp[h];
+                const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                  mk[8 * h + 2 * q] = __uint_as_float(ws[q] << 16);
+                  mk[8 * h + 2 * q + 1] = __uint_as_float(ws[q] & 0xffff0000u);
+                }
+              }
+            } else {
+              const float4* mp =
+                  reinterpret_cast<const float4*>(static_cast<const float*>(g.mask.p) + a);
+#pragma unroll
+              for (int q = 0; q < CW / 4; ++q) {
+                const float4 w = mp[q];
+                mk[4 * q] = w.x;
+                mk[4 * q + 1] = w.y;
+                mk[4 * q + 2] = w.z;
+                mk[4 * q + 3] = w.w;
               }
             }
+#pragma unroll
+            for (int e = 0; e < CW; ++e)
+              if (!(mk[e] > 0.f)) v[e] = 0.f;
+          }
+          const int64_t at = grouped_row(mi, g.cgrp, g.cgs, g.ldc) + n;
+          if (g.c_bf16) {
+            uint4* cp = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(g.C) + at);
+#pragma unroll
+            for (int h = 0; h < CW / 8; ++h) {
+              uint32_t w[4];
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                w[q] = (uint32_t)to_bf16(v[8 * h + 2 * q]) |
+                       ((uint32_t)to_bf16(v[8 * h + 2 * q + 1]) << 16);
+              cp[h] = uint4{w[0], w[1], w[2], w[3]};
+            }
           } else {
-            const float4* mp =
-                reinterpret_cast<const float4*>(static_cast<const float*>(g.mask.p) + a);
+            float4* cp = reinterpret_cast<float4*>(g.C + at);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const float4 w = mp[q];
-              mk[4 * q] = w.x;
-              mk[4 * q + 1] = w.y;
-              mk[4 * q + 2] = w.z;
-              mk[4 * q + 3] = w.w;
+            for (int q = 0; q < CW / 4; ++q) {
+              float4 o = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+              if (g.beta) {
+                const float4 c = cp[q];
+                o = make_float4(c.x + o.x, c.y + o.y, c.z + o.z, c.w + o.w);
+              }
+              cp[q] = o;
             }
-          }
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (!(mk[e] > 0.f)) v[e] = 0.f;
-        }
-        const int64_t at = grouped_row(mi, g.cgrp, g.cgs, g.ldc) + n;
-        if (g.c_bf16) {
-          uint4* cp = reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(g.C) + at);
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            uint32_t w[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              w[q] = (uint32_t)to_bf16(v[8 * h + 2 * q]) |
-                     ((uint32_t)to_bf16(v[8 * h + 2 * q + 1]) << 16);
-            cp[h] = uint4{w[0], w[1], w[2], w[3]};
-          }
-        } else {
-          float4* cp = reinterpret_cast<float4*>(g.C + at);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            float4 o = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
-            if (g.beta) {
-              const float4 c = cp[q];
-              o = make_float4(c.x + o.x, c.y + o.y, c.z + o.z, c.w + o.w);
-            }
-            cp[q] = o;
           }
         }
       }
@@ -438,29 +461,29 @@ __device__ __forceinline__ void gemm_bf16_epilogue(const GemmArgs& g, v4f (&acc)
     }
     return;
   }
-  const int64_t nb = n0 + wn * 64 + (lane & 15);
-  // the bias of this lane's four columns, read once (per row the compiler
-  // would read it again after every store to C)
-  float bj[4] = {0.f, 0.f, 0.f, 0.f};
-  if (g.ksplit <= 1 && g.bias)
+  const int64_t nb = n0 + wn * (TN / 2) + (lane & 15);
+  // the bias of this lane's columns, read once (per row the compiler would
+  // read it again after every store to C)
+  float bj[NI];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (nb + 16 * j < g.N) bj[j] = g.bias[nb + 16 * j];
+  for (int j = 0; j < NI; ++j)
+    bj[j] = g.ksplit <= 1 && g.bias && nb + 16 * j < g.N ? g.bias[nb + 16 * j] : 0.f;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t m = m0 + wm * 64 + i * 16 + 4 * (lane >> 4) + r;
+      const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * (lane >> 4) + r;
       if (m >= g.M) continue;
-      const float v[4] = {acc[i][0][r] + bj[0], acc[i][1][r] + bj[1], acc[i][2][r] + bj[2],
-                          acc[i][3][r] + bj[3]};
+      float v[NI];
+#pragma unroll
+      for (int j = 0; j < NI; ++j) v[j] = acc[i][j][r] + bj[j];
       if (g.ksplit > 1) {
         float* prow = g.part + ((int64_t)blockIdx.z * g.M + m) * g.N;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NI; ++j)
           if (nb + 16 * j < g.N) prow[nb + 16 * j] = v[j];
       } else {
-        gemm_store_row4(g, m, nb, v);
+        gemm_store_row(g, m, nb, v);
       }
     }
 }
@@ -516,7 +539,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
     __syncthreads();
     cur ^= 1;
   }
-  gemm_bf16_epilogue(g, acc, reinterpret_cast<float*>(&As[0][0][0]), m0, n0, wm, wn, tid, lane);
+  gemm_tile_epilogue<HB, HB>(g, acc, reinterpret_cast<float*>(&As[0][0][0]), m0, n0, wm, wn, tid,
+                             lane);
 }
 
 // out[n] = sum_{c < cnt} src[c * stride + n] for n < N, in a fixed order:
@@ -697,164 +721,6 @@ static void launch_reduce(const float* src, int64_t cnt, int64_t stride, int64_t
   }
 }
 
-// The BF16 kernel for operands that need no edge handling along k: the
-// left one in BF16 with 16-byte runs along its contiguous dimension, the
-// right one so too or FP32 along n (mode 3 below), rows not grouped (but
-// mode 3's), each split-K range a whole number of HK-deep steps, tails of M
-// and N filled as fast_op describes.  A thread's requests are then the same
-// vectors per operand in every k-step, at addresses that step uniformly, so
-// they run NS k-steps ahead of their use in a ring of NS register stages (past
-// the end they repeat the last k-step's addresses: a uniform count of
-// requests keeps every wait exact; the general kernel's per-thread paths
-// force a wait for all of them), and the values go to LDS as loaded.
-// AM, BM: the operands' modes (1 = contiguous along k, 2 = along the outer
-// dimension, as in gemm_bf16_kernel; 3 = FP32 along n).  Same products in
-// the same order as gemm_bf16_kernel, so the same results.  (NS = 3 here.)
-
-// One thread's share of an operand, 16 elements per k-step.  Modes 1 and 2:
-// BF16 in 16-byte runs, rows a fixed distance apart (the uint4s between
-// consecutive k-steps in `step`).  Mode 3 (the right operand only): FP32
-// runs along n in 8-byte pieces, rows (k) possibly grouped, rounded to BF16
-// (nearest even, as gemm_bf16_kernel does) on their way to LDS, which then
-// takes them as mode 2.  Past the matrix's outer size `dim` the tile is
-// filled from rows (mode 1) or runs (modes 2, 3) that exist, the last row or
-// the last whole run below the readable extent: they only reach outputs past
-// M or N, which the epilogue does not store.
-template <int MODE>
-struct FastOp {
-  static constexpr int W = 8;  // 32-bit words staged per k-step
-  const uint4* p;
-  int64_t step;
-  __device__ __forceinline__ void load(int64_t i, uint32_t (&w)[W]) const {
-    const uint4* q = p + i * step;
-    const uint4 a = q[0], b = q[1];
-    w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
-    w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
-  }
-};
-
-template <>
-struct FastOp<3> {
-  static constexpr int W = 16;
-  const float* p;  // the run's first column, row offset 0
-  int64_t k0, grp, gs, rs;
-  __device__ __forceinline__ void load(int64_t i, uint32_t (&w)[W]) const {
-    const uint2* q = reinterpret_cast<const uint2*>(p + grouped_row(k0 + i * HK, grp, gs, rs));
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      const uint2 v = q[h];
-      w[2 * h] = v.x;
-      w[2 * h + 1] = v.y;
-    }
-  }
-};
-
-template <int MODE>
-__device__ __forceinline__ FastOp<MODE> fast_op(const GemmOperand& o, bool is_b, int64_t outer0,
-                                                int64_t dim, int64_t kb, int tid) {
-  int64_t outer;
-  if constexpr (MODE >= 2) {
-    const int64_t cap = o.ext ? o.ext : dim;  // a multiple of 16, at least dim
-    outer = outer0 + (tid % 8) * 16;
-    if (outer > cap - 16) outer = cap - 16;
-  } else {
-    outer = outer0 + tid / 2;
-    if (outer > dim - 1) outer = dim - 1;
-  }
-  const int64_t k = MODE >= 2 ? kb + tid / 8 : kb + (tid % 2) * 16;
-  FastOp<MODE> f;
-  if constexpr (MODE == 3) {
-    f.p = static_cast<const float*>(o.p) + outer;
-    f.k0 = k;
-    f.grp = o.grp;
-    f.gs = o.gs;
-    f.rs = o.rs;
-  } else {
-    f.step = HK * (is_b ? o.rs : o.cs) / 8;
-    f.p = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(o.p) +
-                                         elem_addr(o, is_b, outer, k));
-  }
-  return f;
-}
-
-template <int MODE>
-__device__ __forceinline__ void fast_store(uint16_t (*S)[HLD], int tid,
-                                           const uint32_t (&w)[FastOp<MODE>::W]) {
-  if constexpr (MODE == 3) {
-    uint32_t h[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      h[e] = (uint32_t)to_bf16(__uint_as_float(w[2 * e])) |
-             ((uint32_t)to_bf16(__uint_as_float(w[2 * e + 1])) << 16);
-    fast_store<2>(S, tid, h);
-  } else if constexpr (MODE == 2) {
-    const int k = tid / 8, outer = (tid % 8) * 16;
-#pragma unroll
-    for (int e = 0; e < 16; ++e)
-      S[outer + e][8 * chunk_at(outer + e, k >> 3) + (k & 7)] =
-          (uint16_t)(e & 1 ? w[e / 2] >> 16 : w[e / 2] & 0xffffu);
-  } else {
-    const int outer = tid / 2, c0 = (tid % 2) * 2;
-    *reinterpret_cast<uint4*>(&S[outer][8 * chunk_at(outer, c0)]) = uint4{w[0], w[1], w[2], w[3]};
-    *reinterpret_cast<uint4*>(&S[outer][8 * chunk_at(outer, c0 + 1)]) =
-        uint4{w[4], w[5], w[6], w[7]};
-  }
-}
-
-// k-step i of gemm_bf16_fast_kernel: request step i + 3 into the stage (la,
-// lb) that held step i's operands, multiply LDS buffer CUR, store step i +
-// 1's stage (sa, sb), requested two steps ago, into the other buffer.
-template <int AM, int BM, int CUR>
-__device__ __forceinline__ void fast_step(int64_t i, int64_t n_steps, v4f (&acc)[4][4],
-                                          uint16_t (*As)[HB][HLD], uint16_t (*Bs)[HB][HLD],
-                                          const FastOp<AM>& pa, const FastOp<BM>& pb,
-                                          uint32_t (&la)[FastOp<AM>::W],
-                                          uint32_t (&lb)[FastOp<BM>::W],
-                                          const uint32_t (&sa)[FastOp<AM>::W],
-                                          const uint32_t (&sb)[FastOp<BM>::W], int wm, int wn,
-                                          int lane, int tid, bool do_rs, float& rs) {
-  const int64_t r = i + 3 < n_steps ? i + 3 : n_steps - 1;  // past the end: the last again
-  pa.load(r, la);
-  pb.load(r, lb);
-  uint4 af[4], bfr[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int row = wm * 64 + a * 16 + (lane & 15);
-    af[a] = *reinterpret_cast<const uint4*>(&As[CUR][row][8 * chunk_at(row, lane >> 4)]);
-  }
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const int row = wn * 64 + b * 16 + (lane & 15);
-    bfr[b] = *reinterpret_cast<const uint4*>(&Bs[CUR][row][8 * chunk_at(row, lane >> 4)]);
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-      acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_t, af[a]),
-                                                         __builtin_bit_cast(v8bf_t, bfr[b]),
-                                                         acc[a][b], 0, 0, 0);
-  if (do_rs) {  // this thread's half of row tid / 2 of the A tile, in k order
-    const int row = tid >> 1, h = tid & 1;
-    const uint4 x0 = *reinterpret_cast<const uint4*>(&As[CUR][row][8 * chunk_at(row, 2 * h)]);
-    const uint4 x1 =
-        *reinterpret_cast<const uint4*>(&As[CUR][row][8 * chunk_at(row, 2 * h + 1)]);
-    const uint32_t w[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-    float t = 0.f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      t += __uint_as_float(w[q] << 16);
-      t += __uint_as_float(w[q] & 0xffff0000u);
-    }
-    rs += t;
-  }
-  if (i + 1 < n_steps) {
-    fast_store<AM>(As[CUR ^ 1], tid, sa);
-    fast_store<BM>(Bs[CUR ^ 1], tid, sb);
-  }
-  __syncthreads();
-}
-
 // The tile of this workgroup.  Workgroups go to the 8 XCDs in turn (id %
 // 8), each XCD with its own L2: when the tiles of a k-split divide evenly,
 // XCD x takes the x-th eighth of them in row-major order along the longer
@@ -876,74 +742,489 @@ __device__ __forceinline__ void xcd_tile(int64_t* tm, int64_t* tn) {
   }
 }
 
-template <int AM, int BM>
-__global__ void __launch_bounds__(256, 2) gemm_bf16_fast_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[2][HB][HLD];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[2][HB][HLD];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  int64_t tm, tn;
-  xcd_tile(&tm, &tn);
-  const int64_t m0 = tm * HB, n0 = tn * HB;
-  const int wm = wave >> 1, wn = wave & 1;
-  int64_t kb, ke;
-  k_range(g, HK, &kb, &ke);
-  v4f acc[4][4];
+// The BF16 kernel for BF16 operands whose rows are 16-byte aligned: both
+// operands go from memory to LDS as they are (global_load_lds, no registers,
+// no conversion), three k-steps in flight in LDS stages of their own, one
+// barrier per k-step.  An operand contiguous along k (mode 1) is staged
+// [outer][32 k] and its fragments read as 16-byte runs; one contiguous along
+// the outer dimension (mode 2, the weight gradients' operands) is staged
+// [32 k][outer] and transposed on its way out of LDS (ds_read_b64_tr_b16:
+// lane i of 16 gets element i of the four 16-element rows that the 16 lanes
+// address).  Both layouts are permuted by the lanes' source addresses so that
+// a fragment read spreads over the LDS banks.  Past M or N the tile is filled
+// from rows or runs that exist (they reach only outputs that are not stored);
+// a last k-step shorter than 32 (mode 2 only) is zeroed in LDS.  The same
+// products in the same order as gemm_bf16_kernel.  Row sums of A (the bias
+// gradients) are products with a fragment of ones.
+// (The register-staged kernel before it wrote mode 2 to LDS element by
+// element.)  us at 4,096 windows, before -> now: dA3 = dH W1 33 -> 28, dW1
+// 49 -> 38, dW3 32 -> 29, dH 18 -> 11, conv1's weight gradient 31 -> 28; at
+// 1,000 windows, where the batch's odd contractions took the general kernel:
+// dW1 31 -> 22, dWh 29 -> 12, dW3 26 -> 21.  The 27 MB masks and outputs
+// bound the conv input gradients (20 and 18 us against 17), the partials and
+// LDS latency the weight gradients.
+// Tiles of 128 x 128, for small outputs 64 x 64, for an FP32 right operand
+// 64 x 128 (conv1's weight gradient, 64 x 100: one tile); waves 2 x 2.
+// LDS byte address of a shared array (applied to the array itself).
+template <class T>
+__device__ __forceinline__ uint32_t lds_addr(T* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)p;
+}
+
+// 16 bytes per lane from src straight to LDS, at byte address dst (the same
+// in every lane) + 16 * lane.  In asm because the builtin makes the compiler
+// wait for every such load in flight before most LDS reads; nothing here
+// waits for it but dma_barrier (no register is written).
+__device__ __forceinline__ void dma16(const void* src, uint32_t dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
+                   __builtin_amdgcn_readfirstlane(dst)),
+               "v"(src)
+               : "memory");
+}
+template <int MODE, int T>
+struct DmaOp {
+  static constexpr int J = MODE == 3 ? 0 : T / 64;  // 16-byte loads per thread and k-step
+  static constexpr int RPI = 1024 / (2 * T);     // mode 2: k rows per wave and load
+  static constexpr int LPR = 64 / RPI, SEG = T / 16;
+  const char* p[T / 64];
+  int64_t ld;  // mode 2: bytes per k row; mode 1: per k-step
+  int64_t k0;  // mode 2: this lane's k row of load 0 in k-step 0
+  __device__ __forceinline__ void init(const GemmOperand& o, bool is_b, int64_t outer0,
+                                       int64_t dim, int64_t kb, int w, int lane) {
+    const uint16_t* base = static_cast<const uint16_t*>(o.p);
+    if constexpr (MODE == 1) {
+      const int64_t os = is_b ? o.cs : o.rs;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+      for (int j = 0; j < J; ++j) {
+        const int r = (j * 4 + w) * 16 + (lane >> 2);
+        const int64_t outer = outer0 + r < dim ? outer0 + r : dim - 1;
+        p[j] = reinterpret_cast<const char*>(base + outer * os + kb +
+                                             8 * ((lane & 3) ^ ((r >> 1) & 3)));
+      }
+      ld = 2 * HK;
+    } else {
+      const int64_t cap = o.ext ? o.ext : dim;  // a multiple of 8, at least dim
+      ld = 2 * (is_b ? o.rs : o.cs);
+      k0 = kb + w * RPI + lane / LPR;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
-  const int64_t n = (ke - kb) / HK;
-  // the workgroups of the first column of tiles also sum A's rows
-  const bool do_rs = g.rowsum != nullptr && tn == 0;
-  float rs = 0.f;
-  if (n > 0) {
-    const FastOp<AM> pa = fast_op<AM>(g.A, false, m0, g.M, kb, tid);
-    const FastOp<BM> pb = fast_op<BM>(g.B, true, n0, g.N, kb, tid);
-    // three register stages; k-step i's operands are requested into stage
-    // i % 3 at the start of step i - 3 (the first three here)
-    uint32_t a0[FastOp<AM>::W], a1[FastOp<AM>::W], a2[FastOp<AM>::W];
-    uint32_t b0[FastOp<BM>::W], b1[FastOp<BM>::W], b2[FastOp<BM>::W];
-    pa.load(0, a0);
-    pb.load(0, b0);
-    pa.load(n > 1 ? 1 : 0, a1);
-    pb.load(n > 1 ? 1 : 0, b1);
-    pa.load(n > 2 ? 2 : n - 1, a2);
-    pb.load(n > 2 ? 2 : n - 1, b2);
-    fast_store<AM>(As[0], tid, a0);
-    fast_store<BM>(Bs[0], tid, b0);
-    __syncthreads();
-    // six steps per iteration, so that stages (i % 3) and LDS buffers (i % 2)
-    // are fixed registers and fixed addresses
-    // (the guards are nested: a step runs only after the one before it, so
-    // the compiler counts the requests in flight exactly)
-    for (int64_t i = 0; i < n; i += 6) {
-      fast_step<AM, BM, 0>(i, n, acc, As, Bs, pa, pb, a0, b0, a1, b1, wm, wn, lane, tid, do_rs, rs);
-      if (i + 1 < n) {
-        fast_step<AM, BM, 1>(i + 1, n, acc, As, Bs, pa, pb, a1, b1, a2, b2, wm, wn, lane, tid, do_rs, rs);
-        if (i + 2 < n) {
-          fast_step<AM, BM, 0>(i + 2, n, acc, As, Bs, pa, pb, a2, b2, a0, b0, wm, wn,
-                               lane, tid, do_rs, rs);
-          if (i + 3 < n) {
-            fast_step<AM, BM, 1>(i + 3, n, acc, As, Bs, pa, pb, a0, b0, a1, b1, wm, wn,
-                                 lane, tid, do_rs, rs);
-            if (i + 4 < n) {
-              fast_step<AM, BM, 0>(i + 4, n, acc, As, Bs, pa, pb, a1, b1, a2, b2, wm, wn,
-                                   lane, tid, do_rs, rs);
-              if (i + 5 < n)
-                fast_step<AM, BM, 1>(i + 5, n, acc, As, Bs, pa, pb, a2, b2, a0, b0, wm,
-                                     wn, lane, tid, do_rs, rs);
-            }
-          }
-        }
+      for (int j = 0; j < J; ++j) {
+        const int k = (j * 4 + w) * RPI + lane / LPR, c = lane % LPR;
+        int64_t outer = outer0 + (((c >> 1) ^ (k & (SEG - 1))) * 16) + (c & 1) * 8;
+        if (outer > cap - 8) outer = cap - 8;
+        p[j] = reinterpret_cast<const char*>(base + outer);
       }
     }
   }
-  if (do_rs) {  // the two halves of each row, then one row sum per row below M
-    const float other = __shfl_xor(rs, 1);
-    const int64_t m = m0 + (tid >> 1);
-    if ((tid & 1) == 0 && m < g.M) g.rowsum[(int64_t)blockIdx.z * g.M + m] = rs + other;
+  // k-step i into the stage at LDS address `stage` (rows at or past ke: the
+  // last row again)
+  __device__ __forceinline__ void issue(uint32_t stage, int i, int64_t ke, int w) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const char* src;
+      if constexpr (MODE == 1) {
+        src = p[j] + i * ld;
+      } else {
+        int64_t k = k0 + i * HK + j * 4 * RPI;
+        if (k > ke - 1) k = ke - 1;
+        src = p[j] + k * ld;
+      }
+      dma16(src, stage + (j * 4 + w) * 1024);
+    }
   }
-  gemm_bf16_epilogue(g, acc, reinterpret_cast<float*>(&As[0][0][0]), m0, n0, wm, wn, tid, lane);
+  // fragment of the 16 outer elements of tile t: 8 consecutive k per lane
+  static __device__ __forceinline__ uint4 frag(const uint16_t* stage, int t, int lane) {
+    if constexpr (MODE == 1) {
+      const int r = t * 16 + (lane & 15);
+      return *reinterpret_cast<const uint4*>(stage + r * HK + 8 * ((lane >> 4) ^ ((r >> 1) & 3)));
+    } else {
+      typedef short v4s __attribute__((ext_vector_type(4)));
+      const int k = 8 * (lane >> 4) + ((lane & 15) >> 2), c = (lane & 3) * 4;
+      uint2 h[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int kk = k + 4 * u;
+        h[u] = __builtin_bit_cast(
+            uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                       (__attribute__((address_space(3))) v4s*)(stage + kk * T +
+                                                                ((t ^ (kk & (SEG - 1))) * 16) + c)));
+      }
+      return uint4{h[0].x, h[0].y, h[1].x, h[1].y};
+    }
+  }
+  // k rows [rem, 32) of the stage zeroed
+  static __device__ __forceinline__ void zero_tail(uint16_t* stage, int rem, int tid) {
+    if constexpr (MODE == 2)
+      for (int i = rem * (T / 8) + tid; i < HK * (T / 8); i += 256)
+        reinterpret_cast<uint4*>(stage)[i] = uint4{0u, 0u, 0u, 0u};
+  }
+};
+
+// A right operand in FP32 contiguous along n in 8-byte pieces, rows (k)
+// possibly grouped (mode 3: the windows), for T-wide tiles: a thread's T / 8
+// elements of a k-step (k row tid / 8) through registers, loaded two k-steps
+// ahead, zeros at or past ke; stored as mode 2's layout of the kernel's type
+// (BF16: rounded to nearest even).
+template <int T>
+struct RegB {
+  static constexpr int CW = T / 8, SEG = T / 16;
+  const float* p;
+  int64_t k0, grp, gs, rs;
+  float2 v[CW / 2];
+  int k, c;
+  __device__ __forceinline__ void init(const GemmOperand& o, int64_t outer0, int64_t dim,
+                                       int64_t kb, int tid) {
+    const int64_t cap = o.ext ? o.ext : dim;  // a multiple of CW, at least dim
+    k = tid >> 3;
+    c = (tid & 7) * CW;
+    int64_t outer = outer0 + c;
+    if (outer > cap - CW) outer = cap - CW;
+    p = static_cast<const float*>(o.p) + outer;
+    k0 = kb + k;
+    grp = o.grp;
+    gs = o.gs;
+    rs = o.rs;
+  }
+  __device__ __forceinline__ void load(int i, int64_t ke) {
+    const int64_t r = k0 + (int64_t)i * HK;
+    const float2* q =
+        reinterpret_cast<const float2*>(p + grouped_row(r < ke ? r : ke - 1, grp, gs, rs));
+#pragma unroll
+    for (int h = 0; h < CW / 2; ++h) v[h] = q[h];
+    if (r >= ke)
+#pragma unroll
+      for (int h = 0; h < CW / 2; ++h) v[h] = make_float2(0.f, 0.f);
+  }
+  __device__ __forceinline__ void store(float* stage) const {
+    static_assert(T == 64, "FP32 tiles");
+    float* d = stage + k * T + (((c >> 4) ^ ((k >> 2) & 3)) * 16) + (c & 15);
+    *reinterpret_cast<float4*>(d) = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+    *reinterpret_cast<float4*>(d + 4) = make_float4(v[2].x, v[2].y, v[3].x, v[3].y);
+  }
+  __device__ __forceinline__ void store(uint16_t* stage) const {
+    uint32_t w[CW / 2];
+#pragma unroll
+    for (int h = 0; h < CW / 2; ++h)
+      w[h] = (uint32_t)to_bf16(v[h].x) | ((uint32_t)to_bf16(v[h].y) << 16);
+    uint4* d = reinterpret_cast<uint4*>(stage + k * T + (((c >> 4) ^ (k & (SEG - 1))) * 16) +
+                                        (c & 15));
+#pragma unroll
+    for (int q = 0; q < CW / 8; ++q)
+      d[q] = uint4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+  }
+};
+
+// Waits until at most VM of this wave's memory requests are in flight, then
+// the workgroup barrier; this wave's LDS reads have returned.
+template <int VM>
+__device__ __forceinline__ void dma_barrier() {
+  static_assert(VM >= 0 && VM <= 4, "requests per k-step");
+  if constexpr (VM == 0)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else if constexpr (VM == 1)
+    asm volatile("s_waitcnt vmcnt(1) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else if constexpr (VM == 3)
+    asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else if constexpr (VM == 2)
+    asm volatile("s_waitcnt vmcnt(2) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  else
+    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+template <int AM, int BM, int TM, int TN>
+__global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(GemmArgs g) {
+  using OA = DmaOp<AM, TM>;
+  using OB = DmaOp<BM, TN>;
+  constexpr int MI = TM / 32, NI = TN / 32;  // 16-wide tiles per wave
+  // three stages (A's tile, then B's); afterwards the epilogue's scratch
+  constexpr int SN = (TM + TN) * HK;
+  static_assert(3 * SN >= 2 * epilogue_floats<TN>(), "epilogue scratch");
+  __shared__ __attribute__((aligned(1024))) uint16_t st[3 * SN];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int64_t tm, tn;
+  xcd_tile(&tm, &tn);
+  const int64_t m0 = tm * TM, n0 = tn * TN;
+  const int wm = wave >> 1, wn = wave & 1;
+  int64_t kb, ke;
+  k_range(g, HK, &kb, &ke);
+  v4f acc[MI][NI], rs[MI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    rs[i] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NI; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  const int n = (int)((ke - kb + HK - 1) / HK);
+  // the workgroups of the first column of tiles also sum A's rows
+  const bool do_rs = g.rowsum != nullptr && tn == 0 && wn == 0;
+  if (n > 0) {
+    OA pa;
+    OB pb;
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    pa.init(g.A, false, m0, g.M, kb, w, lane);
+    RegB<TN> r3;
+    if constexpr (BM == 3)
+      r3.init(g.B, n0, g.N, kb, tid);
+    else
+      pb.init(g.B, true, n0, g.N, kb, w, lane);
+    const uint32_t lds = lds_addr(st);
+    auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+      pa.issue(lds + stage * 2 * SN, i, ke, w);
+      if constexpr (BM != 3) pb.issue(lds + stage * 2 * SN + 2 * TM * HK, i, ke, w);
+    };
+    auto compute = [&](const uint16_t* s) __attribute__((always_inline)) {
+      uint4 af[MI], bf[NI];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) af[i] = OA::frag(s, wm * MI + i, lane);
+#pragma unroll
+      for (int j = 0; j < NI; ++j) bf[j] = OB::frag(s + TM * HK, wn * NI + j, lane);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_t, af[i]),
+                                                             __builtin_bit_cast(v8bf_t, bf[j]),
+                                                             acc[i][j], 0, 0, 0);
+      if (do_rs) {
+        const uint4 one = uint4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+          rs[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_t, af[i]),
+                                                         __builtin_bit_cast(v8bf_t, one), rs[i],
+                                                         0, 0, 0);
+      }
+    };
+    // k-step i reads stage i % 3 (cur) once its loads have landed everywhere;
+    // then the stage of step i - 1 (nxt), which every wave has read, takes
+    // step i + 2's
+    constexpr int L = OA::J + OB::J;  // loads per thread and k-step
+    const int rem = (int)(ke - kb - (int64_t)(n - 1) * HK);
+    auto step = [&](int i, uint16_t* cur, int nxt) __attribute__((always_inline)) {
+      if (i + 1 < n) {
+        dma_barrier<L>();
+        if (i + 2 < n) issue(i + 2, nxt);
+        if constexpr (BM == 3) {
+          // (every wave has read the last use of the stage after cur)
+          r3.store(st + (nxt == 0 ? 2 : nxt == 1 ? 0 : 1) * SN + TM * HK);
+          if (i + 2 < n) r3.load(i + 2, ke);
+        }
+      } else {
+        dma_barrier<0>();
+        if (rem < HK) {
+          OA::zero_tail(cur, rem, tid);
+          if constexpr (BM != 3) OB::zero_tail(cur + TM * HK, rem, tid);
+          __syncthreads();
+        }
+      }
+      compute(cur);
+    };
+    if constexpr (BM == 3) {
+      r3.load(0, ke);
+      r3.store(st + TM * HK);
+      if (n > 1) r3.load(1, ke);
+    }
+    issue(0, 0);
+    if (n > 1) issue(1, 1);
+    for (int i = 0; i < n; i += 3) {
+      step(i, st, 2);
+      if (i + 1 < n) {
+        step(i + 1, st + SN, 0);
+        if (i + 2 < n) step(i + 2, st + 2 * SN, 1);
+      }
+    }
+    __syncthreads();
+  }
+  if (do_rs && (lane & 15) == 0) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * (lane >> 4) + r;
+        if (m < g.M) g.rowsum[(int64_t)blockIdx.z * g.M + m] = rs[i][r];
+      }
+  }
+  gemm_tile_epilogue<TM, TN>(g, acc, reinterpret_cast<float*>(st), m0, n0, wm, wn, tid, lane);
+}
+
+// The FP32 kernel for operands in 16-byte aligned rows, staged straight into
+// LDS like gemm_bf16_dma_kernel's: 64 x 64 tiles, 32 k per step, 2 x 2 waves
+// of 32 x 32 on mfma_f32_16x16x4.  Mode 1 is staged [outer][32 k] and read in
+// 16-byte runs, mode 2 [32 k][outer] and read by the element; mode 3 (the
+// right operand: contiguous along n in 8-byte pieces, rows possibly grouped,
+// e.g. the windows) as mode 2 but through registers, a k-step ahead (4-byte
+// loads straight to LDS took 84 us for conv1's weight gradient of 4,096
+// windows).  In a 16-deep block
+// lane group g holds k = 4 g + t for the t-th MFMA, in both operands alike.
+// Bound by the FP32 matrix rate (at 4,096 windows dA3 = dH W1 376 -> 130 us,
+// 108 TFLOP/s; dW1 340 -> 162, its 416 tiles two to some CUs) and at small
+// batches by the latency of a k-step (64 windows: head 39 -> 15 us); before
+// are gemm_kernel's times.
+constexpr int FT = 64;
+template <int MODE>
+struct DmaF32 {
+  static constexpr int J = MODE == 3 ? 0 : 2;  // loads to LDS per thread and k-step
+  const char* p[2];
+  int64_t ld, k0;
+  __device__ __forceinline__ void init(const GemmOperand& o, bool is_b, int64_t outer0,
+                                       int64_t dim, int64_t kb, int w, int lane) {
+    const float* base = static_cast<const float*>(o.p);
+    if constexpr (MODE == 1) {
+      const int64_t os = is_b ? o.cs : o.rs;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {  // 8 rows of 128 bytes per wave and load
+        const int r = (j * 4 + w) * 8 + (lane >> 3);
+        const int64_t outer = outer0 + r < dim ? outer0 + r : dim - 1;
+        p[j] = reinterpret_cast<const char*>(base + outer * os + kb + 4 * ((lane & 7) ^ (r & 7)));
+      }
+      ld = 4 * HK;
+    } else {
+      static_assert(MODE == 2, "mode 3 is staged by RegB");
+      const int64_t cap = o.ext ? o.ext : dim;  // a multiple of 4, at least dim
+      ld = 4 * (is_b ? o.rs : o.cs);
+      k0 = kb + w * 4 + (lane >> 4);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {  // 4 k rows of 256 bytes per wave and load
+        const int k = (j * 4 + w) * 4 + (lane >> 4), c = lane & 15;
+        int64_t outer = outer0 + (((c >> 2) ^ ((k >> 2) & 3)) * 16) + (c & 3) * 4;
+        if (outer > cap - 4) outer = cap - 4;
+        p[j] = reinterpret_cast<const char*>(base + outer);
+      }
+    }
+  }
+  __device__ __forceinline__ void issue(uint32_t stage, int i, int64_t ke, int w) const {
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      if constexpr (MODE == 1) {
+        dma16(p[j] + i * ld, stage + (j * 4 + w) * 1024);
+      } else {
+        int64_t k = k0 + i * HK + j * 16;
+        if (k > ke - 1) k = ke - 1;
+        dma16(p[j] + k * ld, stage + (j * 4 + w) * 1024);
+      }
+    }
+  }
+  // elements t = 0 .. 3 of block b (16 k) of outer tile `tile`
+  static __device__ __forceinline__ v4f frag(const float* stage, int tile, int b, int lane) {
+    if constexpr (MODE == 1) {
+      const int r = tile * 16 + (lane & 15);
+      return *reinterpret_cast<const v4f*>(stage + r * HK + 4 * ((4 * b + (lane >> 4)) ^ (r & 7)));
+    } else {
+      const int g = lane >> 4;
+      const float* q = stage + (16 * b + 4 * g) * FT + ((tile ^ g) * 16) + (lane & 15);
+      return v4f{q[0], q[FT], q[2 * FT], q[3 * FT]};
+    }
+  }
+  static __device__ __forceinline__ void zero_tail(float* stage, int rem, int tid) {
+    if constexpr (MODE != 1)
+      for (int i = rem * (FT / 4) + tid; i < HK * (FT / 4); i += 256)
+        reinterpret_cast<uint4*>(stage)[i] = uint4{0u, 0u, 0u, 0u};
+  }
+};
+
+template <int AM, int BM>
+__global__ void __launch_bounds__(256, 3) gemm_f32_dma_kernel(GemmArgs g) {
+  using OA = DmaF32<AM>;
+  using OB = DmaF32<BM>;
+  constexpr int TI = FT / 32, SN = 2 * FT * HK;
+  __shared__ __attribute__((aligned(1024))) float st[3 * SN];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  int64_t tm, tn;
+  xcd_tile(&tm, &tn);
+  const int64_t m0 = tm * FT, n0 = tn * FT;
+  const int wm = wave >> 1, wn = wave & 1;
+  int64_t kb, ke;
+  k_range(g, HK, &kb, &ke);
+  v4f acc[TI][TI];
+  float rs[TI] = {};
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TI; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  const int n = (int)((ke - kb + HK - 1) / HK);
+  const bool do_rs = g.rowsum != nullptr && tn == 0 && wn == 0;
+  if (n > 0) {
+    OA pa;
+    OB pb;
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    pa.init(g.A, false, m0, g.M, kb, w, lane);
+    RegB<FT> r3;
+    if constexpr (BM == 3)
+      r3.init(g.B, n0, g.N, kb, tid);
+    else
+      pb.init(g.B, true, n0, g.N, kb, w, lane);
+    const uint32_t lds = lds_addr(st);
+    auto issue = [&](int i, int stage) __attribute__((always_inline)) {
+      pa.issue(lds + stage * 4 * SN, i, ke, w);
+      if constexpr (BM != 3) pb.issue(lds + stage * 4 * SN + 4 * FT * HK, i, ke, w);
+    };
+    auto compute = [&](const float* s) __attribute__((always_inline)) {
+#pragma unroll
+      for (int b = 0; b < HK / 16; ++b) {
+        v4f af[TI], bf[TI];
+#pragma unroll
+        for (int i = 0; i < TI; ++i) af[i] = OA::frag(s, wm * TI + i, b, lane);
+#pragma unroll
+        for (int j = 0; j < TI; ++j) bf[j] = OB::frag(s + FT * HK, wn * TI + j, b, lane);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TI; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i][t], bf[j][t], acc[i][j], 0, 0,
+                                                               0);
+        if (do_rs)
+#pragma unroll
+          for (int i = 0; i < TI; ++i) rs[i] += (af[i][0] + af[i][1]) + (af[i][2] + af[i][3]);
+      }
+    };
+    constexpr int L = OA::J + OB::J;
+    const int rem = (int)(ke - kb - (int64_t)(n - 1) * HK);
+    auto step = [&](int i, float* cur, int nxt) __attribute__((always_inline)) {
+      if (i + 1 < n) {
+        dma_barrier<L>();
+        if (i + 2 < n) issue(i + 2, nxt);
+        if constexpr (BM == 3) {
+          // (every wave has read the last use of the stage after cur)
+          r3.store(st + (nxt == 0 ? 2 : nxt == 1 ? 0 : 1) * SN + FT * HK);
+          if (i + 2 < n) r3.load(i + 2, ke);
+        }
+      } else {
+        dma_barrier<0>();
+        if (rem < HK) {
+          OA::zero_tail(cur, rem, tid);
+          if constexpr (BM != 3) OB::zero_tail(cur + FT * HK, rem, tid);
+          __syncthreads();
+        }
+      }
+      compute(cur);
+    };
+    if constexpr (BM == 3) {
+      r3.load(0, ke);
+      r3.store(st + FT * HK);
+      if (n > 1) r3.load(1, ke);
+    }
+    issue(0, 0);
+    if (n > 1) issue(1, 1);
+    for (int i = 0; i < n; i += 3) {
+      step(i, st, 2);
+      if (i + 1 < n) {
+        step(i + 1, st + SN, 0);
+        if (i + 2 < n) step(i + 2, st + 2 * SN, 1);
+      }
+    }
+    __syncthreads();
+  }
+  if (do_rs) {
+#pragma unroll
+    for (int i = 0; i < TI; ++i) {
+      float v = rs[i];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      const int64_t m = m0 + wm * (FT / 2) + i * 16 + lane;
+      if (lane < 16 && m < g.M) g.rowsum[(int64_t)blockIdx.z * g.M + m] = v;
+    }
+  }
+  gemm_tile_epilogue<FT, FT>(g, acc, st, m0, n0, wm, wn, tid, lane);
 }
 
 // Operand access mode for the BF16 kernel (see gemm_bf16_kernel) and the
@@ -972,32 +1253,61 @@ static void operand_mode(const GemmOperand& o, bool is_b, int32_t* mode, int32_t
 hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
                        hipStream_t stream, int64_t* rowsum_parts) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  const int TB = bf16_mma ? HB : GB;
-  const int64_t tiles = ((g.M + TB - 1) / TB) * ((g.N + TB - 1) / TB);
-  // split K when the output is too small to fill the chip: aim at one round
-  // of workgroups (512: two per CU), at least 8 k-steps each, within the
-  // partial buffer
-  int64_t ks = 1;
-  if (part && tiles < 128) {
-    ks = 512 / tiles;
-    const int64_t steps = g.K / ((bf16_mma ? HK : GK) * 8);
-    if (ks > steps) ks = steps;
-    if (ks > part_cap / (g.M * g.N)) ks = part_cap / (g.M * g.N);
-    if (ks > 65535) ks = 65535;
-    if (ks < 2) ks = 1;
-  }
   // grouped rows are divided in 32 bits
   const int64_t big = (int64_t)1 << 32;
   if ((g.A.grp < NO_GROUP && g.M >= big) || (g.B.grp < NO_GROUP && g.K >= big) ||
       (g.mask.p && g.mask.grp < NO_GROUP && g.M >= big) || (g.cgrp < NO_GROUP && g.M >= big) ||
       (g.ccg != 0 && (g.ccg < 0 || g.N >= big)))
     return hipErrorInvalidValue;
-  g.ksplit = (int32_t)ks;
-  g.part = part;
   operand_mode(g.A, false, &g.amode, &g.avec);
   operand_mode(g.B, true, &g.bmode, &g.bvec);
-  // the BF16 kernel's vector epilogue: no split, no bias, N whole 16-column
-  // runs, C and the mask in 16-byte aligned rows contiguous along n
+  // BF16 operands in aligned rows: staged straight into LDS (runs of 8 along
+  // the outer dimension within a readable extent; k in whole steps where an
+  // operand is contiguous along it)
+  auto direct = [&](const GemmOperand& o, int32_t mode, int32_t vec, int64_t dim) {
+    const int64_t cap = o.ext ? o.ext : dim;
+    return (o.bf16 != 0) == (bf16_mma != 0) && vec == 2 && o.grp >= NO_GROUP &&
+           ((mode == 1 && g.K % HK == 0) ||
+            (mode == 2 && cap % (o.bf16 ? 8 : 4) == 0 && cap >= dim));
+  };
+  // (the right operand also FP32 in 8-byte pieces along n, rows possibly
+  // grouped: the windows)
+  const int64_t bcap = g.B.ext ? g.B.ext : g.N;
+  const bool dir_a = direct(g.A, g.amode, g.avec, g.M);
+  const bool dir_b = direct(g.B, g.bmode, g.bvec, g.N);
+  const bool b3 = dir_a && !dir_b && !g.B.bf16 && g.bmode == 2 && g.bvec >= 1 &&
+                  bcap % (bf16_mma ? 16 : 8) == 0 && bcap >= g.N;
+  const bool dma = dir_a && (dir_b || b3);
+  auto tiles_of = [&](int64_t tm, int64_t tn) {
+    return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn);
+  };
+  // (64 x 64 tiles where 128 x 128 ones would not fill the chip and k is too
+  // short to split)
+  const bool small = dma && !b3 && tiles_of(HB, HB) < 192 && !(part && g.K >= 4096);
+  const int TM = !bf16_mma ? GB : b3 || small ? 64 : HB;
+  const int TN = !bf16_mma ? GB : small ? 64 : HB;
+  const int64_t tiles = tiles_of(TM, TN);
+  // split K when the output is too small to fill the chip, at least 8 k-steps
+  // each, within the partial buffer: two workgroups per CU, or one where the
+  // partials would cost more than the second hides (BF16, few tiles: conv3's
+  // weight gradient of 4,096 windows 28.6 us with 256 workgroups, 35.8 with
+  // 512; the hidden layer's 104 tiles 38.9 with 416, 42.3 with 208; FP32 74
+  // with 512, 89 with 256)
+  int64_t ks = 1;
+  const int64_t target = dma && bf16_mma && !b3 && tiles < 64 ? 256 : 512;
+  if (part && tiles < 128) {
+    ks = target / tiles;
+    const int64_t steps = g.K / ((bf16_mma || dma ? HK : GK) * 8);
+    if (ks > steps) ks = steps;
+    if (ks > part_cap / (g.M * g.N)) ks = part_cap / (g.M * g.N);
+    if (ks > 65535) ks = 65535;
+    if (ks < 2) ks = 1;
+  }
+  g.ksplit = (int32_t)ks;
+  g.part = part;
+  // the BF16 kernels' vector epilogue: split-K partials in whole 16-byte
+  // runs; else no bias, N whole 16-column runs, C and the mask in 16-byte
+  // aligned rows contiguous along n
   {
     const int64_t mq = g.mask.bf16 ? 8 : 4;
     const int64_t cq = g.c_bf16 ? 8 : 4;  // elements per 16 bytes of C
@@ -1007,42 +1317,46 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
                                     reinterpret_cast<uintptr_t>(g.mask.p) % 16 == 0 &&
                                     g.mask.rs % mq == 0 &&
                                     (g.mask.grp >= NO_GROUP || g.mask.gs % mq == 0));
-    g.evec = bf16_mma && ks == 1 && !g.bias && g.ccg == 0 && g.N % 16 == 0 && c_ok && m_ok;
+    g.evec = (bf16_mma || dma) && g.N % 16 == 0 &&
+             (ks > 1 ? reinterpret_cast<uintptr_t>(part) % 16 == 0
+                     : !g.bias && g.ccg == 0 && c_ok && m_ok);
   }
-  const dim3 grid((unsigned)((g.N + TB - 1) / TB), (unsigned)((g.M + TB - 1) / TB), (unsigned)ks);
-  // operands with nothing to guard along k: the pipelined kernel (rows
-  // along the outer dimension are clamped; runs of 16 along it need a
-  // readable extent of whole runs)
-  auto whole_runs = [](const GemmOperand& o, int32_t mode, int64_t dim) {
-    const int64_t cap = o.ext ? o.ext : dim;
-    return mode == 1 || (cap % 16 == 0 && cap >= dim);
+  const dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)ks);
+  if (rowsum_parts) *rowsum_parts = dma && g.rowsum ? ks : 0;
+  if (!dma) g.rowsum = nullptr;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, g);
   };
-  const bool fast_a = bf16_mma && g.A.bf16 && g.avec == 2 && g.amode != 0 &&
-                      g.A.grp >= NO_GROUP && whole_runs(g.A, g.amode, g.M) && g.K % HK == 0;
-  const bool fast_b = g.B.bf16 && g.bvec == 2 && g.bmode != 0 && g.B.grp >= NO_GROUP &&
-                      whole_runs(g.B, g.bmode, g.N);
-  // FP32 along n in 8-byte pieces, rows possibly grouped (e.g. the windows)
-  const bool fast_b32 = !g.B.bf16 && g.bvec >= 1 && g.bmode == 2 && whole_runs(g.B, 2, g.N);
-  if (rowsum_parts) *rowsum_parts = (fast_a && (fast_b32 || fast_b) && g.rowsum) ? ks : 0;
-  if (!(fast_a && (fast_b32 || fast_b))) g.rowsum = nullptr;
-  if (fast_a && fast_b32) {
+  if (dma && !bf16_mma) {
     if (g.amode == 1)
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<1, 3>), grid, dim3(256), 0, stream, g);
+      b3             ? launch(gemm_f32_dma_kernel<1, 3>)
+      : g.bmode == 1 ? launch(gemm_f32_dma_kernel<1, 1>)
+                     : launch(gemm_f32_dma_kernel<1, 2>);
     else
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<2, 3>), grid, dim3(256), 0, stream, g);
-  } else if (fast_a && fast_b) {
-    if (g.amode == 1 && g.bmode == 1)
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<1, 1>), grid, dim3(256), 0, stream, g);
-    else if (g.amode == 1)
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<1, 2>), grid, dim3(256), 0, stream, g);
-    else if (g.bmode == 1)
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<2, 1>), grid, dim3(256), 0, stream, g);
+      b3             ? launch(gemm_f32_dma_kernel<2, 3>)
+      : g.bmode == 1 ? launch(gemm_f32_dma_kernel<2, 1>)
+                     : launch(gemm_f32_dma_kernel<2, 2>);
+  } else if (b3) {
+    g.amode == 1 ? launch(gemm_bf16_dma_kernel<1, 3, 64, 128>)
+                 : launch(gemm_bf16_dma_kernel<2, 3, 64, 128>);
+  } else if (small) {
+    if (g.amode == 1)
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64>)
+                   : launch(gemm_bf16_dma_kernel<1, 2, 64, 64>);
     else
-      hipLaunchKernelGGL((gemm_bf16_fast_kernel<2, 2>), grid, dim3(256), 0, stream, g);
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, 64, 64>)
+                   : launch(gemm_bf16_dma_kernel<2, 2, 64, 64>);
+  } else if (dma) {
+    if (g.amode == 1)
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, HB, HB>)
+                   : launch(gemm_bf16_dma_kernel<1, 2, HB, HB>);
+    else
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, HB, HB>)
+                   : launch(gemm_bf16_dma_kernel<2, 2, HB, HB>);
   } else if (bf16_mma) {
-    hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, stream, g);
+    launch(gemm_bf16_kernel);
   } else {
-    hipLaunchKernelGGL(gemm_kernel, grid, dim3(256), 0, stream, g);
+    launch(gemm_kernel);
   }
   if (ks > 1) {
     const int64_t MN = g.M * g.N;

@@ -1,0 +1,105 @@
+"""The training products at the sizes where their kernels change or have
+edges: batches whose contractions end in a short k-step, 64- and 128-wide
+tiles, split and unsplit K, one stream and two, and a save buffer that is not
+16-byte aligned (the general kernels).
+
+The reference is the backward pass in float64 on the GPU's own saved
+activations and loss gradient (so no ReLU sits on another side), with the
+BF16 form's roundings where that form rounds.  Bars: FP32 a normwise relative
+error of max(5e-5, 4 u sqrt(52 B)) per tensor (u = 6e-8, the square root of
+the longest sum, a depth margin); BF16 2^-8 (a value whose FP32 sum falls on
+the other side of a rounding boundary moves by one unit)."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+D, L = 50, 111
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    if not t.cuda.is_available():
+        pytest.skip("no GPU")
+    return t
+
+
+@pytest.fixture(scope="module")
+def sn():
+    import paper_2105_05821_amd as m
+    m.lib()
+    return m
+
+
+def reference(torch, ws, x, acts, dz, prec):
+    """Parameter and window gradients in float64; acts = a1, a2, a3, h."""
+    def rnd(t):
+        return t.float().to(torch.bfloat16).double() if prec == 1 else t
+
+    B = x.shape[0]
+    W = [rnd(torch.from_numpy(np.ascontiguousarray(w)).cuda().double()) for w in ws]
+    a1, a2, a3, h = acts
+    dzr = rnd(dz)
+    g = [None] * 5
+    g[4] = (dzr.t() @ h, dz.sum(0))
+    dh = rnd((dzr @ W[4]) * (h > 0))
+    g[3] = (dh.t() @ a3.transpose(1, 2).reshape(B, -1), dh.sum(0))
+    dy = rnd((dh @ W[3]).view(B, 256, 13).transpose(1, 2) * (a3 > 0)).reshape(B * 13, 256)
+    xin = rnd(x[:, :104].double()).reshape(B * 52, 100)
+    for l, (rows, n) in {2: (a2, 256), 1: (a1, 128), 0: (xin, 100)}.items():
+        rows = rows.reshape(-1, n)
+        w = W[l].permute(0, 2, 1).reshape(W[l].shape[0], n)  # columns t * c_in + c
+        gw = dy.t() @ rows
+        g[l] = (gw.view(-1, 2, n // 2).permute(0, 2, 1).reshape(gw.shape), dy.sum(0))
+        dy = dy @ w
+        if l:
+            dy = rnd(dy * (rows > 0)).reshape(-1, n // 2)
+    dx = torch.zeros((B, L, D), dtype=torch.float64, device="cuda")
+    dx[:, :104] = dy.view(B, 104, 50)
+    return g, dx
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("B,shift", [(1, 0), (5, 0), (33, 0), (64, 0), (257, 0), (1030, 0),
+                                     (37, 8)])
+def test_training_products(torch, sn, prec, B, shift):
+    layers = synth.net_c3_hybrid()
+    ws, bs = synth.init_weights(3, layers, out_bias=None, out_gain=1.0)
+    pred = sn.Predictor(layers, prec)
+    pred.load_weights(layers, sn.flat_params(ws, bs))
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn((B, L, D), generator=gen, device="cuda")
+    y = torch.randint(0, 420, (B, 2), generator=gen, device="cuda").int()
+    z, save = pred.forward(x)
+    _, dz = pred.loss(z, y)
+    n = pred.save_bytes(B)
+    moved = torch.empty(n + shift, dtype=torch.uint8, device="cuda")[shift:]
+    moved.copy_(save[:n])
+    dp = torch.empty(2_204_642, device="cuda")
+    dx = pred.backward(x, moved, dz, dp, want_dx=True)
+    v = save[:n].view(torch.float32 if prec == 0 else torch.bfloat16).double()
+    sizes = (52 * 64, 26 * 128, 13 * 256, 512)
+    at = np.cumsum([0] + [B * s for s in sizes])
+    a1, a2, a3, h = (v[at[i]:at[i + 1]].view(B, s) for i, s in enumerate(sizes))
+    want, want_dx = reference(torch, ws, x, (a1, a2, a3.reshape(B, 13, 256), h), dz.double(), prec)
+    bar = max(5e-5, 4 * 6e-8 * np.sqrt(52.0 * B)) if prec == 0 else 2.0 ** -8
+
+    def check(name, got, ref):
+        err = float((got.double() - ref).norm() / ref.norm().clamp_min(1e-300))
+        assert err <= bar, (name, err)
+
+    off = 0
+    for l, (gw, gb) in enumerate(want):
+        check(f"layer {l} weights", dp[off:off + gw.numel()].view(gw.shape), gw)
+        off += gw.numel()
+        check(f"layer {l} biases", dp[off:off + gb.numel()], gb)
+        off += gb.numel()
+    check("dx", dx, want_dx)
+    # accumulated onto what is there
+    dp2 = torch.ones_like(dp)
+    pred.backward(x, moved, dz, dp2, accumulate=True)
+    assert torch.allclose(dp2 - 1, dp, rtol=0, atol=3e-7 * max(1.0, float(dp.abs().max())))
+    pred.close()
