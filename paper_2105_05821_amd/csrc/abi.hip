@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/simnet.h"
@@ -61,7 +62,6 @@ struct sim_ctx {
   // split step and forward (C3 networks, few windows): buffers, steps taken
   // since the reset (a lower bound), each tile's longest sub-trace in claim
   // order
-  void* split_block = nullptr;
   SplitBufs split{};
   int64_t steps_done = 0;
   std::vector<int64_t> tile_len;
@@ -263,6 +263,16 @@ template <class F>
 void pack_b_tile(int prec, int K, int N, int KG, int TILE, F&& B, uint8_t* out) {
   const int KGS = K / KG, NTL = N / TILE, E = KG * TILE / 64;
   const size_t es = elem_size(prec);
+  if (prec == 1) {  // (the common case, without a copy call per element)
+    uint16_t* dst = reinterpret_cast<uint16_t*>(out);
+    for (int kg = 0; kg < KGS; ++kg)
+      for (int nt = 0; nt < NTL; ++nt)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int k = kg * KG + E * (lane / TILE), n = nt * TILE + lane % TILE;
+          for (int e = 0; e < E; ++e) *dst++ = bf16_bits(B(k + e, n));
+        }
+    return;
+  }
   for (int kg = 0; kg < KGS; ++kg)
     for (int nt = 0; nt < NTL; ++nt)
       for (int lane = 0; lane < 64; ++lane)
@@ -360,7 +370,8 @@ std::vector<uint8_t> relayout(int prec, const float* params,
     };
     const std::vector<float> ws = wscale(l, K, N, wv);
     L->conv_w[l] = reserve((size_t)K * N * es);
-    pack_b(prec, K, N, [&](int k, int n) { return wv(k, n) / ws[n]; }, out.data() + L->conv_w[l]);
+    pack_b(prec, K, N, [&](int k, int n) { return fp8 ? wv(k, n) / ws[n] : wv(k, n); },
+           out.data() + L->conv_w[l]);
     L->conv_b[l] = put_floats(std::vector<float>(b[l], b[l] + N));
     L->conv_ws[l] = put_floats(ws);
     std::vector<float> ai(N, 1.f);
@@ -417,7 +428,11 @@ std::vector<uint8_t> relayout(int prec, const float* params,
     const size_t per = (size_t)K * N * es;
     L->hid_w = reserve(per * NB);
     for (int j = 0; j < NB; ++j)
-      pack_b(prec, K, N, [&](int c, int n) { return wv(c * NB + j, n) / ws[n]; },
+      pack_b(prec, K, N,
+             [&](int c, int n) {
+               const int kk = c * NB + j;
+               return fp8 ? wv(kk, n) / ws[n] : W1[(size_t)n * (K * NB) + kk];
+             },
              out.data() + L->hid_w + per * j);
     L->hid_b = put_floats(std::vector<float>(b[li], b[li] + N));
     L->hid_ws = put_floats(ws);
@@ -487,6 +502,38 @@ bool layers_match(const sim_layer* layers, int32_t n) {
 
 }  // namespace
 
+// The split step's and forward's buffers, laid out from byte `at` of a block
+// (`base` NULL: the size only); returns the end.  Group sums for
+// SPLIT_MAX_TILES tiles, and for a simulation whose slots fit them the
+// per-slot state.
+static size_t split_layout(const sim_ctx* c, char* base, size_t at, SplitBufs* out) {
+  const int net = c->cfg.n_out == 3 ? 4 : 1;
+  const size_t groups = (size_t)split_groups(net, c->cfg.prec);
+  const size_t slots =
+      c->has_trace && c->n_wg_max <= SPLIT_MAX_TILES ? (size_t)c->n_wg_max * MT : 0;
+  const size_t ring = slots * SPLIT_RING, mring = net == 4 ? ring : 0;
+  auto take = [&](auto*& p, size_t n) {
+    using T = std::remove_reference_t<decltype(*p)>;
+    p = base && n ? reinterpret_cast<T*>(base + at) : nullptr;
+    at += (n * sizeof(T) + 255) / 256 * 256;
+  };
+  SplitBufs b{};
+  take(b.part, (size_t)SPLIT_MAX_TILES * groups * MT * NetC3::HID);
+  take(b.cst, slots);
+  take(b.scal[0], slots);
+  take(b.scal[1], slots);
+  take(b.q_e, ring);
+  take(b.q_t, ring);
+  take(b.q_r, ring);
+  take(b.m_idx, mring);
+  take(b.m_es, mring);
+  take(b.m_t, mring);
+  take(b.m_r, mring);
+  take(b.m_x, mring);
+  if (out) *out = b;
+  return at;
+}
+
 static void drop_graph(sim_ctx* c) {
   if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
   c->graph_exec = nullptr;
@@ -546,47 +593,6 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
   return SIM_OK;
 }
 
-// The split step's and forward's buffers, made once when a C3 network's
-// weights are loaded (nothing is allocated in a step or a forward).  Without
-// them (an allocation failed) every tile runs on one workgroup.
-static void ensure_split(sim_ctx* c) {
-  if (c->split_block || c->net == 0) return;
-  const size_t groups = (size_t)split_groups(c->net, c->cfg.prec);
-  const size_t slots = c->has_trace && c->n_wg_max <= SPLIT_MAX_TILES ? (size_t)c->n_wg_max * MT : 0;
-  const size_t ring = slots * SPLIT_RING, mring = c->cfg.n_out == 3 ? ring : 0;
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = off;
-    off += (bytes + 255) / 256 * 256;
-    return at;
-  };
-  const size_t part = take((size_t)SPLIT_MAX_TILES * groups * MT * NetC3::HID * sizeof(float)),
-               cst = take(slots * sizeof(SlotConst)), sc0 = take(slots * sizeof(SlotScalars)),
-               sc1 = take(slots * sizeof(SlotScalars)), qe = take(ring * 4), qt = take(ring * 8),
-               qr = take(ring * 8), mi = take(mring * 4), me = take(mring * 4),
-               mt = take(mring * 8), mr = take(mring * 8), mx = take(mring * 8);
-  if (hipMalloc(&c->split_block, off) != hipSuccess) {
-    (void)hipGetLastError();
-    c->split_block = nullptr;
-    return;
-  }
-  char* base = static_cast<char*>(c->split_block);
-  SplitBufs& b = c->split;
-  b.part = reinterpret_cast<float*>(base + part);
-  if (slots == 0) return;
-  b.cst = reinterpret_cast<SlotConst*>(base + cst);
-  b.scal[0] = reinterpret_cast<SlotScalars*>(base + sc0);
-  b.scal[1] = reinterpret_cast<SlotScalars*>(base + sc1);
-  b.q_e = reinterpret_cast<int32_t*>(base + qe);
-  b.q_t = reinterpret_cast<int64_t*>(base + qt);
-  b.q_r = reinterpret_cast<int64_t*>(base + qr);
-  b.m_idx = reinterpret_cast<int32_t*>(base + mi);
-  b.m_es = reinterpret_cast<int32_t*>(base + me);
-  b.m_t = reinterpret_cast<int64_t*>(base + mt);
-  b.m_r = reinterpret_cast<int64_t*>(base + mr);
-  b.m_x = reinterpret_cast<int64_t*>(base + mx);
-}
-
 // Shape of a split launch over `tiles` tiles: one unit per group and as many
 // column slices as one workgroup per CU allows (a workgroup's LDS fills a
 // CU); with more tiles, fewer units of several groups.  units < 2: not worth
@@ -596,7 +602,7 @@ static void ensure_split(sim_ctx* c) {
 // 43; 128 tiles 2 units 46, 4 units 58; 163 tiles 2 units 81 against 54 on
 // one workgroup per tile).
 static SplitShape split_shape(const sim_ctx* c, int64_t tiles) {
-  if (!c->split_block || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1};
+  if (!c->split.part || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1};
   const int64_t groups = split_groups(c->net, c->cfg.prec);
   for (int32_t s : {4, 2, 1})
     if (tiles * groups * s <= c->n_cu) return SplitShape{(int32_t)groups, s};
@@ -738,7 +744,13 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
       T.perm_off[l] = qf;
       qf += (T.n_perm[l] + 63) / 64 * 64;
     }
-    if (e == hipSuccess) e = hipMalloc(&T.perm, qf * 4);
+    // (a context without a simulation: the split forward's sums too)
+    const size_t pf = (qf * 4 + 255) / 256 * 256;
+    const bool split = !c->split.part;
+    if (e == hipSuccess)
+      e = hipMalloc(&T.perm, split ? split_layout(c, nullptr, pf, nullptr) : qf * 4);
+    if (e == hipSuccess && split)
+      split_layout(c, reinterpret_cast<char*>(T.perm), pf, &c->split);
     if (e != hipSuccess) return hip_fail(c, e, "training buffers");
     // per master parameter its byte offsets in the packed and permuted
     // copies (-1: none), for sim_adam_load's re-layout in the update pass
@@ -778,7 +790,6 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
   c->relu = relu;
   int rc = relayout_train(c);
   if (rc != SIM_OK) return rc;
-  ensure_split(c);
   c->weights = true;
   return SIM_OK;
 }
@@ -1026,7 +1037,16 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
   const size_t o_mi = take(4 * KC), o_mes = take(4 * KC), o_mt = take(8 * KC), o_mr = take(8 * KC),
                o_mx = take(8 * KC), o_mh = take(4 * KM), o_mc = take(4 * KM), o_mq = take(4 * KM),
                o_xp = take(8 * KM);
-  hipError_t e = hipMalloc(&c->dev_block, off);
+  // the split step's buffers behind it (without them, if they do not fit,
+  // every tile runs on one workgroup)
+  const bool split = c->net != 0;
+  hipError_t e = hipMalloc(&c->dev_block, split ? split_layout(c, nullptr, off, nullptr) : off);
+  if (e == hipSuccess && split) {
+    split_layout(c, static_cast<char*>(c->dev_block), off, &c->split);
+  } else if (e != hipSuccess && split) {
+    (void)hipGetLastError();
+    e = hipMalloc(&c->dev_block, off);
+  }
   if (e != hipSuccess) {
     fprintf(stderr, "sim_init: hipMalloc(%zu): %s\n", off, hipGetErrorString(e));
     if (c->feat16) (void)hipFree(c->feat16);
@@ -1148,8 +1168,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     c->calibrated = false;
     int rc = upload_weights(c, SIM_FP32, host.data(), nullptr, &c->dev_w32, &c->w32);
     if (rc != SIM_OK) return rc;
-    ensure_split(c);
-    c->weights = true;
+      c->weights = true;
     return sim_reset(c);
   }
   int rc = upload_weights(c, c->cfg.prec, host.data(), nullptr, &c->dev_weights, &c->w);
@@ -1162,7 +1181,14 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     if (e == hipSuccess) e = hipMalloc(&c->rb_logits, sizeof(float) * slots * NetRB7::NOUT);
     if (e != hipSuccess) return hip_fail(c, e, "hipMalloc RB7 step buffers");
   }
-  ensure_split(c);
+  if (!c->has_trace && c->net != 0 && !c->split.part) {  // the split forward's sums
+    if (hipMalloc(&c->dev_block, split_layout(c, nullptr, 0, nullptr)) == hipSuccess) {
+      split_layout(c, static_cast<char*>(c->dev_block), 0, &c->split);
+    } else {
+      (void)hipGetLastError();
+      c->dev_block = nullptr;
+    }
+  }
   c->weights = true;
   return sim_reset(c);
 }
@@ -1882,7 +1908,6 @@ void sim_destroy(sim_ctx* c) {
   if (c->tr.side) (void)hipStreamDestroy(c->tr.side);
   if (c->tr.work) (void)hipFree(c->tr.work);
   if (c->dev_block) (void)hipFree(c->dev_block);
-  if (c->split_block) (void)hipFree(c->split_block);
   if (c->rb_trunk) (void)hipFree(c->rb_trunk);
   if (c->rb_active) (void)hipFree(c->rb_active);
   if (c->rb_logits) (void)hipFree(c->rb_logits);
