@@ -62,6 +62,7 @@ struct sim_ctx {
   // split step and forward (C3 networks, few windows): buffers, steps taken
   // since the reset (a lower bound), each tile's longest sub-trace in claim
   // order
+  std::vector<char> results;  // host side of sim_run's one copy
   SplitBufs split{};
   int64_t steps_done = 0;
   std::vector<int64_t> tile_len;
@@ -1091,12 +1092,13 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
     s.x_prev = reinterpret_cast<int64_t*>(base + o_xp);
   }
 
+  c->results.resize(o_tot + 8 - o_fe);
   hipError_t e1 = hipMemcpyAsync(base + o_first, first.data(), 8 * K, hipMemcpyHostToDevice, c->stream);
   hipError_t e2 = hipMemcpyAsync(base + o_npos, npos.data(), 8 * K, hipMemcpyHostToDevice, c->stream);
   hipError_t e3 = hipMemcpyAsync(base + o_warm, warm.data(), 4 * K, hipMemcpyHostToDevice, c->stream);
   hipError_t e4 = hipMemcpyAsync(base + o_poff, poff.data(), 8 * K, hipMemcpyHostToDevice, c->stream);
   hipError_t e7 = hipMemcpyAsync(base + o_order, order.data(), 4 * K, hipMemcpyHostToDevice, c->stream);
-  hipError_t e5 = launch_reset(s, K, C, n_slots, c->stream);
+  hipError_t e5 = launch_reset(s, K, n_slots, c->stream);
   hipError_t e6 = hipStreamSynchronize(c->stream);  // host vectors die at return
   for (hipError_t x : {e1, e2, e3, e4, e7, e5, e6})
     if (x != hipSuccess) {
@@ -1196,7 +1198,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
 int sim_reset(sim_ctx* c) {
   if (!c) return SIM_EINVAL;
   if (!c->has_trace) return SIM_OK;
-  hipError_t e = launch_reset(c->st, c->n_sub, c->C, c->n_wg_max * MT, c->stream);
+  hipError_t e = launch_reset(c->st, c->n_sub, c->n_wg_max * MT, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reset");
   c->completed = false;
   c->ran_to_end = false;
@@ -1480,23 +1482,23 @@ int sim_run(sim_ctx* c, int32_t mode, const int32_t* table, sim_result* res) {
     e = launch_total(c->st, c->n_sub, c->dev_total, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "total launch");
   }
-  int64_t total = 0;
-  unsigned long long ctr[NCOUNTERS] = {0};
-  e = hipMemcpyAsync(&total, c->dev_total, 8, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(ctr, c->st.counters, sizeof ctr, hipMemcpyDeviceToHost, c->stream);
-  const size_t kb = 8 * (size_t)c->n_sub;
-  if (e == hipSuccess && res->fetch_cycles)
-    e = hipMemcpyAsync(res->fetch_cycles, c->st.fetch, kb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess && res->drain_cycles)
-    e = hipMemcpyAsync(res->drain_cycles, c->st.drain, kb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess && res->final_tick)
-    e = hipMemcpyAsync(res->final_tick, c->st.final_tick, kb, hipMemcpyDeviceToHost, c->stream);
-  if (e == hipSuccess && res->warm_tick)
-    e = hipMemcpyAsync(res->warm_tick, c->st.warm_tick, kb, hipMemcpyDeviceToHost, c->stream);
+  // the results lie one after another (fetch, drain, final and warm ticks,
+  // counters, total): one copy to the host instead of six
+  const char* from = reinterpret_cast<const char*>(c->st.fetch);
+  e = hipMemcpyAsync(c->results.data(), from, c->results.size(), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "sim_run results");
-  res->total_cycles = total;
+  auto host = [&](const void* dev) {
+    return c->results.data() + (static_cast<const char*>(dev) - from);
+  };
+  const size_t kb = 8 * (size_t)c->n_sub;
+  if (res->fetch_cycles) memcpy(res->fetch_cycles, host(c->st.fetch), kb);
+  if (res->drain_cycles) memcpy(res->drain_cycles, host(c->st.drain), kb);
+  if (res->final_tick) memcpy(res->final_tick, host(c->st.final_tick), kb);
+  if (res->warm_tick) memcpy(res->warm_tick, host(c->st.warm_tick), kb);
+  unsigned long long ctr[NCOUNTERS];
+  memcpy(ctr, host(c->st.counters), sizeof ctr);
+  memcpy(&res->total_cycles, host(c->dev_total), 8);
   res->measured_instr = c->n_meas;
   res->predicted_instr = c->n_pred;
   res->n_clamped = (int64_t)ctr[0];
