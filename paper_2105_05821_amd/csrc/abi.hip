@@ -847,6 +847,11 @@ static SaveBlock save_block(const sim_ctx* c, void* save, int64_t B) {
   return sb;
 }
 
+// Outputs per window of a network's inference head.
+static int n_outputs(int net) {
+  return net == 3 || net == 5 ? NetC3Hyb::NOUT : net == 4 ? NetC3S::NOUT : NetC3::NOUT;
+}
+
 static GemmOperand opnd(const void* p, int bf16, int64_t rs, int64_t cs,
                         int64_t grp = NO_GROUP, int64_t gs = 0) {
   GemmOperand o;
@@ -1508,6 +1513,21 @@ int sim_run(sim_ctx* c, int32_t mode, const int32_t* table, sim_result* res) {
   return SIM_OK;
 }
 
+// At least n windows' last-conv outputs in c->rb_ws, kept for later calls.
+static hipError_t trunk_workspace(sim_ctx* c, int64_t n) {
+  if (n <= c->rb_ws_B) return hipSuccess;
+  if (c->rb_ws) {
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipFree(c->rb_ws);
+    c->rb_ws = nullptr;
+    c->rb_ws_B = 0;
+  }
+  const size_t per = NetC3::NB * NetC3::CH3 * elem_size(c->cfg.prec);
+  hipError_t e = hipMalloc(&c->rb_ws, (size_t)n * per);
+  if (e == hipSuccess) c->rb_ws_B = n;
+  return e;
+}
+
 int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* save_or_null) {
   if (!c) return SIM_EINVAL;
   if (!c->weights) return fail(c, SIM_ESTATE, "weights not loaded");
@@ -1538,18 +1558,8 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   if (save_or_null) return fail(c, SIM_EUNSUPPORTED, "save buffer not supported");
   if (c->net == 5) {  // convolutions, residual blocks, FC 512 and head over a workspace
     if (B > INT64_MAX / (NetRB7::NB * NetRB7::CH3 * 4)) return fail(c, SIM_EINVAL, "batch too large");
-    if (B > c->rb_ws_B) {
-      if (c->rb_ws) {
-        (void)hipStreamSynchronize(c->stream);
-        (void)hipFree(c->rb_ws);
-        c->rb_ws = nullptr;
-        c->rb_ws_B = 0;
-      }
-      hipError_t e = hipMalloc(&c->rb_ws, (size_t)B * NetRB7::NB * NetRB7::CH3 *
-                                              elem_size(c->cfg.prec));
-      if (e != hipSuccess) return hip_fail(c, e, "hipMalloc RB7 workspace");
-      c->rb_ws_B = B;
-    }
+    if (hipError_t e = trunk_workspace(c, B); e != hipSuccess)
+      return hip_fail(c, e, "hipMalloc RB7 workspace");
     const SplitShape sh = split_shape(c, (B + MT - 1) / MT);
     const bool split = sh.units >= 2;
     hipError_t e = split ? launch_split_trunk(c->cfg.prec, c->w, c->relu,
@@ -1570,13 +1580,41 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     if (e != hipSuccess) return hip_fail(c, e, "RB7 forward");
     return SIM_OK;
   }
-  const SplitShape sh = c->net != 0 ? split_shape(c, (B + MT - 1) / MT) : SplitShape{1, 1};
-  hipError_t e = sh.units >= 2
-                     ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu,
-                                            static_cast<const float*>(x), B, logits, SaveBlock{},
-                                            c->split.part, sh, c->stream)
-                     : launch_forward(c->net, c->cfg.prec, c->w, c->relu,
-                                      static_cast<const float*>(x), B, logits, c->stream);
+  // n windows: few split over several workgroups per tile (split_shape), at
+  // most one round of workgroups in one kernel, more through rows (BF16,
+  // FWD_ROUNDS rounds at a time; without their memory, or under capture while
+  // there is none yet, in one kernel too)
+  const int64_t round = (int64_t)MT * c->n_cu;
+  bool rows = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && B > round;
+  const int64_t most = std::min(B, FWD_ROUNDS * round);
+  if (rows && most > c->rb_ws_B) {
+    rows = !capturing(c->stream) && trunk_workspace(c, most) == hipSuccess;
+    if (!rows) (void)hipGetLastError();
+  }
+  const float* xs = static_cast<const float*>(x);
+  hipError_t e = hipSuccess;
+  auto part = [&](int64_t n) {
+    const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1};
+    if (n <= 0 || e != hipSuccess) return;
+    e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits,
+                                             SaveBlock{}, c->split.part, sh, c->stream)
+        : rows && n > round
+            ? launch_forward_rows(c->net, c->w, c->relu, xs, n, static_cast<uint16_t*>(c->rb_ws),
+                                  logits, c->n_cu,
+                                  c->stream)
+            : launch_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits, c->stream);
+    xs += n * c->cfg.n_slot * c->cfg.n_feat;
+    logits += n * n_outputs(c->net);
+    B -= n;
+  };
+  if (rows) {
+    // a few windows beyond whole rounds cost less split than as one more
+    // round (us, 4,100 windows: 102 in one piece, 82 as 4,096 and 4; 8,200:
+    // 141, 134)
+    const int64_t over = B % round, rest = over <= round / 8 ? over : 0;
+    while (B - rest > 0) part(std::min(B - rest, most));
+  }
+  part(B);
   if (e != hipSuccess) return hip_fail(c, e, "forward launch");
   return SIM_OK;
 }

@@ -384,6 +384,9 @@ struct SplitBufs {
   int64_t *m_t, *m_r, *m_x;
   float* part;
 };
+// Rounds (MT windows per CU) launch_forward_rows takes at once: its head runs
+// up to 4 row tiles per workgroup.
+constexpr int64_t FWD_ROUNDS = 4;
 // Groups of blocks per window of a C3 network (net 4: with the memory write
 // queue) in a form.
 int split_groups(int net, int prec);
@@ -404,6 +407,12 @@ hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t re
 hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t relu,
                                 const float* x, int64_t B, float* logits, const SaveBlock& sb,
                                 float* sums, SplitShape sh, hipStream_t stream);
+// Forward over many windows (BF16 form, nets 1 and 3): the convolutions'
+// outputs to rows, then the hidden layer and the head on 2 to 4 row tiles
+// per workgroup.
+hipError_t launch_forward_rows(int net, const DevWeights& w, uint32_t relu, const float* x,
+                               int64_t B, uint16_t* rows, float* logits, int n_cu,
+                               hipStream_t stream);
 // RB7 over few windows: the convolutions (launch_split_step with net 5 in a
 // simulation), then launch_resblocks, then FC 512's group sums, then the head
 // (in a simulation the next launch_split_step).

@@ -785,4 +785,157 @@ hipError_t launch_split_forward(int net, int prec, const DevWeights& w, uint32_t
   return hipErrorInvalidValue;
 }
 
+// ----------------------------------------------------------- many windows ---
+
+// A batch of more windows than one workgroup per CU takes in a round: the
+// fused forward streams 3.4 MB of hidden-FC weights through each CU's L2 port
+// for every 16 windows, ~30 of a round's 67 us.  Here the convolutions write
+// their outputs (6.7 KB a window) to memory, ~38 us a round, and one launch
+// runs the hidden layer on M tiles per workgroup, so that a weight fragment
+// serves M tiles (256 CUs, us: M = 2 43, M = 3 55, M = 4 65; the weight stream
+// alone 37).  Forward of C3, BF16, fused -> this (us): 8,192 windows 135 ->
+// 120, 16,384 269 -> 219, 20,480 328 -> 289, 65,536 1,017 -> 843.  FP8 halves
+// the weights and gains nothing (16,384: 224 -> 216, 4,100: 95.7 -> 96.1), so
+// it stays fused.  FP32 is bound by its matrix instructions.
+
+// The hidden layer and the head on M tiles of MT windows from the last conv's
+// outputs x [B][NB][CH3].  A block's rows are staged into one of two LDS
+// buffers while the block before is multiplied; a group's sums accumulate
+// across its blocks and are then added, as hidden_fc does.
+template <class Net, class P, int M>
+__global__ void __launch_bounds__(Net::WAVES * 64)
+    rows_head_kernel(DevWeights wt, uint32_t relu_mask, const typename P::T* __restrict__ x,
+                     int64_t B, float* __restrict__ logits) {
+  using G = Geo<Net, P>;
+  using GR = Groups<Net, P>;
+  using T = typename P::T;
+  using S = FcShape<Net, P, 1>;
+  constexpr int HT = S::HT, K = Net::CHL, SA = K + G::PAD, NT = G::NT;
+  constexpr int EV = 16 / (int)sizeof(T), V = K / EV, R = M * MT;
+  constexpr int PER = (R * V + NT - 1) / NT;  // 16-byte pieces per thread and block
+  __shared__ NetSmem<Net, P> sm;
+  static_assert(2 * R * SA <= G::NXA2, "staged rows fit X's region");
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t b0 = (int64_t)blockIdx.x * R;
+  T* const buf = sm.x();
+  uint4 r[PER];
+  auto request = [&](int j) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = q * NT + tid, row = i / V, v = i % V;
+      r[q] = make_uint4(0u, 0u, 0u, 0u);
+      if (row < R && b0 + row < B)
+        r[q] = reinterpret_cast<const uint4*>(x + ((b0 + row) * Net::NB + j) * K)[v];
+    }
+  };
+  auto commit = [&](int j) {
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int i = q * NT + tid, row = i / V, v = i % V;
+      if (row < R) *reinterpret_cast<uint4*>(buf + (j & 1) * R * SA + row * SA + v * EV) = r[q];
+    }
+  };
+  v4f hacc[M][HT], acc[M][HT];
+#pragma unroll
+  for (int m = 0; m < M; ++m)
+#pragma unroll
+    for (int t = 0; t < HT; ++t) hacc[m][t] = acc[m][t] = v4f{0.f, 0.f, 0.f, 0.f};
+  request(0);
+  commit(0);
+  for (int j = 0; j < Net::NB; ++j) {
+    if (j + 1 < Net::NB) request(j + 1);
+    const auto head = fc_head<Net, P, 1>(wt, j, wave, lane);
+    lds_barrier();
+    const T* ap[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+      ap[m] = buf + (j & 1) * R * SA + (m * MT + (lane & 15)) * SA + (P::KG / 4) * (lane >> 4);
+    mma_stream<P, S::KGS, Net::HID / 16, HT, M, Net::FC1_FRAGS, true>(acc, ap, S::weights(wt, j),
+                                                                      wave * HT, lane, &head);
+    if (j + 1 < Net::NB) commit(j + 1);
+    if ((j + 1) % GR::NG == 0 || j + 1 == Net::NB)  // the group's last block
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int t = 0; t < HT; ++t) {
+          hacc[m][t] += acc[m][t];
+          acc[m][t] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+  }
+  sm.stage_head(wt, tid, NT);
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    __syncthreads();
+    head_tile<Net, P, false, false>(wt, relu_mask, sm, hacc[m], nullptr, nullptr, {});
+    __syncthreads();
+    if (tid < MT * Net::NOUT) {
+      const int s = tid / Net::NOUT, o = tid % Net::NOUT;
+      const int64_t b = b0 + m * MT + s;
+      if (b < B) logits[b * Net::NOUT + o] = sm.logit[s][o];
+    }
+  }
+}
+
+// Convolutions of explicit windows, one workgroup per tile, to rows.
+template <class Net, class P>
+__global__ void __launch_bounds__(Net::WAVES * 64)
+    rows_trunk_kernel(DevWeights wt, uint32_t relu_mask, const float* __restrict__ x, int64_t B,
+                      typename P::T* __restrict__ rows) {
+  using G = Geo<Net, P>;
+  using GA = Gather<Net, P>;
+  using T = typename P::T;
+  constexpr int BS = Net::BS, GSL = GA::GSL, TPR = GA::TPR, CPT = GA::CPT;
+  __shared__ NetSmem<Net, P> sm;
+  const int tid = threadIdx.x;
+  const int64_t b0 = (int64_t)blockIdx.x * MT;
+  const int row = tid / TPR, part = tid % TPR;
+  const int s = row / GSL, t = row % GSL;
+  if constexpr (P::SCALED) {
+    for (int i = tid; i < Net::D; i += G::NT) sm.x_inv[i] = wt.x_inv[i];
+    __syncthreads();
+  }
+  auto load = [&](int j0, int nb) {
+    return request_window_row<Net, CPT, TPR>(x, B, b0 + s, j0 * BS + t, t < nb * BS, part);
+  };
+  auto commit = [&](int j0, int nb, const RowRegs<CPT>& r, T* X) {
+    (void)j0;
+    if (t < nb * BS) commit_window_row<Net, P>(sm.x_inv, s, t, part, r, X);
+  };
+  SavePtrs<T> sv{};
+  sv.a3 = rows + b0 * Net::NB * Net::CH3;
+  sv.rows = (int)(B - b0 < MT ? B - b0 : MT);
+  predict_tile<Net, P, false, true, true>(wt, relu_mask, sm, load, commit, nullptr, nullptr, sv);
+}
+
+template <class Net>
+static hipError_t launch_forward_rows_t(const DevWeights& w, uint32_t relu, const float* x,
+                                        int64_t B, uint16_t* rows, float* logits, int n_cu,
+                                        hipStream_t stream) {
+  using P = PBF16;
+  const int64_t tiles = (B + MT - 1) / MT;
+  const dim3 block(Geo<Net, P>::NT);
+  hipLaunchKernelGGL((rows_trunk_kernel<Net, P>), dim3((unsigned)tiles), block, 0, stream, w, relu,
+                     x, B, rows);
+  auto head = [&](auto kernel, int m) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + m - 1) / m)), block, 0, stream, w, relu,
+                       rows, B, logits);
+  };
+  // as few row tiles per workgroup as one round of workgroups allows
+  if (tiles <= 2 * (int64_t)n_cu)
+    head(rows_head_kernel<Net, P, 2>, 2);
+  else if (tiles <= 3 * (int64_t)n_cu)
+    head(rows_head_kernel<Net, P, 3>, 3);
+  else
+    head(rows_head_kernel<Net, P, 4>, 4);
+  return hipGetLastError();
+}
+
+hipError_t launch_forward_rows(int net, const DevWeights& w, uint32_t relu, const float* x,
+                               int64_t B, uint16_t* rows, float* logits, int n_cu,
+                               hipStream_t stream) {
+  if (net == 1) return launch_forward_rows_t<NetC3>(w, relu, x, B, rows, logits, n_cu, stream);
+  if (net == 3) return launch_forward_rows_t<NetC3Hyb>(w, relu, x, B, rows, logits, n_cu, stream);
+  return hipErrorInvalidValue;
+}
+
 }  // namespace simnet

@@ -150,3 +150,20 @@ def test_split_training_forward_equals_one_workgroup(torch, sn, prec):
         for g, w in zip(parts(sb, B), want):
             assert torch.equal(g, w[:B]), B
     pred.close()
+
+
+@pytest.mark.parametrize("net", ["c3", "hyb"])
+def test_forward_over_rounds_equals_single_tiles(torch, sn, net):
+    """More windows than 16 per CU: whole rounds through the convolutions'
+    outputs in memory, a short rest split; on 256 CUs two, three and four row
+    tiles per workgroup, two passes, a rest of one window and of 513."""
+    s = simulator(sn, torch, net, 1, np.array([0]), np.array([8]), np.array([0], np.int32))
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    rnd = 16 * n_cu
+    x = torch.randn((4 * rnd + rnd // 8 + 1, L, D), device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(3))
+    want = torch.cat([s.forward(x[i:i + rnd].contiguous()) for i in range(0, len(x), rnd)])
+    for B in (rnd + 1, 2 * rnd - 15, 2 * rnd + rnd // 8, 2 * rnd + rnd // 2, 3 * rnd + rnd // 2,
+              4 * rnd, len(x)):
+        assert torch.equal(s.forward(x[:B].contiguous()), want[:B]), B
+    s.close()
