@@ -711,23 +711,129 @@ __global__ void __launch_bounds__(64) wave_step_kernel(DevWeights wt, uint32_t r
   }
 }
 
-// ------------------------------------------ four wavefronts per sub-trace ---
-// The small network's FP32 step split over the four blocks of its kernel-2
-// stride-2 tree: conv2's position j depends on window slots 4j .. 4j+3 only,
-// so wave j builds those four slots, runs conv1 at positions 2j and 2j+1 and
-// conv2 at position j (each wave reading only what it wrote), and multiplies
-// its share of the final FC; the four partial sums meet in LDS, and every
-// wave runs the same clock and queue update on the same values (wave 0
-// alone writes the ring, the results and the state).  Per lane that is
-// 64 + 64 multiply-adds per prediction instead of the single wave's 768.
-// The ring has QR = 16 entries for the C = 15 visible ones, so a push never
-// lands on an entry read in the same step and two barriers per step
-// suffice: one after the partial sums, one after the push.  Each wave keeps
-// the retire times of the last W instructions in a register spread over its
-// lanes (lane l: the instruction with pos % W == l).  Same state, work queue
-// and results as step_kernel (the ring is written back with head 0).
-constexpr int QW = 4, QR = 16;
-static_assert(WV_NB == QW && WV_L == 16 && WV_C < QR, "four blocks of four slots");
+// ------------------------------------------ queue in a row of 16 lanes ---
+// The small network's processor queue (15 visible entries) held by 16
+// consecutive lanes: lane j has the j-th newest instruction, a push moves
+// every entry one lane up (DPP, no LDS), and the entries that have left stay
+// behind the visible ones, so lane W - 1 always holds the retire time of the
+// instruction W before.  The sub-trace's scalars are the same in all 16
+// lanes.
+constexpr int QL = 16;
+static_assert(WV_C < QL && WMAX <= QL, "queue and retire history fit a row");
+
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp(int32_t fill, int32_t x) {
+  return __builtin_amdgcn_update_dpp(fill, x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(dpp<CTRL>(0, __float_as_int(x)));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E;  // quad permutations
+constexpr int DPP_HALF_MIRROR = 0x141;           // lane i of 8 reads 7 - i
+constexpr int DPP_ROR4 = 0x124, DPP_ROR8 = 0x128, DPP_SHR1 = 0x111;  // within 16
+
+struct RowQueue {
+  int32_t e;
+  int64_t t, r;
+  int64_t cur, t_w, r_prev, pos, n_pos, row, g;  // row: trace row of pos; g: prediction index
+  int32_t count, warm;
+  // sub-trace k's state (uniform over the 16 lanes); j: the lane's entry
+  __device__ __forceinline__ void load(const DevState& st, int k, int j, int W) {
+    cur = st.cur[k];
+    t_w = st.t_w[k];
+    r_prev = st.r_prev[k];
+    pos = st.pos[k];
+    n_pos = st.n_pos[k];
+    row = st.first[k] + pos;
+    g = st.pred_off[k] + pos;
+    count = st.count[k];
+    warm = st.warm[k];
+    e = 0;
+    t = r = 0;
+    if (j < count) {
+      int q = st.head[k] + count - 1 - j;
+      q = q >= WV_C ? q - WV_C : q;
+      const size_t at = (size_t)k * WV_C + q;
+      e = st.q_e[at];
+      t = st.q_t[at];
+      r = st.q_r[at];
+    } else if (j < W && j < pos) {
+      r = st.rw[(size_t)k * WMAX + (pos - 1 - j) % W];
+    }
+  }
+  // back to memory, the ring from entry 0 (head 0)
+  __device__ __forceinline__ void store(const DevState& st, int k, int j, int W) const {
+    if (j == 0) {
+      st.cur[k] = cur;
+      st.t_w[k] = t_w;
+      st.r_prev[k] = r_prev;
+      st.pos[k] = pos;
+      st.head[k] = 0;
+      st.count[k] = count;
+    }
+    if (j < count) {
+      const size_t at = (size_t)k * WV_C + (count - 1 - j);
+      st.q_idx[at] = (int32_t)(row - 1 - j);
+      st.q_e[at] = e;
+      st.q_t[at] = t;
+      st.q_r[at] = r;
+    }
+    if (j < W && j < pos) st.rw[(size_t)k * WMAX + (pos - 1 - j) % W] = r;
+  }
+  // r_{i-W} + 1, or the least value before there are W instructions
+  __device__ __forceinline__ int64_t retire_bound(int lane, int W) const {
+    const int64_t rb = __shfl(r, (lane & ~(QL - 1)) + W - 1);
+    return pos >= W ? rb + 1 : INT64_MIN;
+  }
+  // clock and queue (Sec. 3.2): T = cur + F; the retired prefix (r <= T)
+  // leaves; r = max(T + E + 1, r_prev, r_{i-W} + 1); push.  Returns the
+  // number of entries that were visible and stay so.
+  __device__ __forceinline__ int advance(int32_t F, int32_t E, int64_t rb, int lane, int j) {
+    const int64_t Tn = cur + F;
+    const uint64_t gone = __ballot(j < count && r <= Tn);
+    const int kept = count - __popc((uint32_t)(gone >> (lane & ~(QL - 1))) & 0xffffu);
+    int64_t rn = Tn + E + 1;
+    rn = rn > r_prev ? rn : r_prev;
+    rn = rn > rb ? rn : rb;
+    auto shift = [](int64_t fill, int64_t x) {
+      const uint32_t lo = (uint32_t)dpp<DPP_SHR1>((int32_t)fill, (int32_t)x);
+      const uint32_t hi = (uint32_t)dpp<DPP_SHR1>((int32_t)(fill >> 32), (int32_t)(x >> 32));
+      return (int64_t)(((uint64_t)hi << 32) | lo);
+    };
+    e = dpp<DPP_SHR1>(E, e);
+    t = shift(Tn, t);
+    r = shift(rn, r);
+    count = kept < WV_C ? kept + 1 : WV_C;  // only the newest C stay visible
+    r_prev = rn;
+    cur = Tn;
+    ++pos;
+    ++row;
+    ++g;
+    if (pos == warm) t_w = Tn;
+    return kept;
+  }
+  // the drain ends (Eq. 1)
+  __device__ __forceinline__ void finish(const DevState& st, int k) const {
+    st.fetch[k] = cur - t_w;
+    st.drain[k] = r_prev - cur;
+    st.final_tick[k] = r_prev;
+    st.warm_tick[k] = t_w;
+    st.pos[k] = pos;
+    st.cur[k] = cur;
+  }
+};
+
+// Run counters of the lanes that own a sub-trace, added to the state's.
+struct StepCounts {
+  uint32_t clamped = 0, nonfinite = 0, mismatch = 0, pred = 0;
+  __device__ __forceinline__ void add_to(const DevState& st) const {
+    if (clamped) atomicAdd(&st.counters[0], (unsigned long long)clamped);
+    if (nonfinite) atomicAdd(&st.counters[1], (unsigned long long)nonfinite);
+    if (mismatch) atomicAdd(&st.counters[2], (unsigned long long)mismatch);
+    if (pred) atomicAdd(&st.counters[3], (unsigned long long)pred);
+  }
+};
 
 // LDS written by this wave and read by other lanes of it: the wave's LDS
 // requests complete in order, so a compiler fence and a wait suffice
@@ -737,18 +843,49 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+// ------------------------------------------ four wavefronts per sub-trace ---
+// The small network's FP32 step split over the four blocks of its kernel-2
+// stride-2 tree: conv2's position j depends on window slots 4j .. 4j+3 only,
+// so wave j builds those four slots, runs conv1 at positions 2j and 2j+1 and
+// conv2 at position j (each wave reading only what it wrote), and multiplies
+// its share of the final FC; the four partial sums meet in LDS, and every
+// wave runs the same clock and queue update on the same values (wave 0
+// alone writes the results and the state), each row of 16 lanes holding the
+// whole queue.  Per lane that is 64 + 64 multiply-adds per prediction instead
+// of the single wave's 768.  What bounds it is the chain of one step; the
+// queue in registers leaves it one barrier, after the partial sums (written
+// to alternating buffers), and the sums over a wave are DPP and lane swaps: 1.39
+// us per step of one sub-trace (1.87 with the ring in LDS, a second barrier,
+// LDS shuffles and a 64-bit remainder per step).  Three workgroups per CU
+// instead of two spill 39 registers.  Same state, work queue and results as
+// step_kernel.
+constexpr int QW = 4;
+static_assert(WV_NB == QW && WV_L == 16, "four blocks of four slots");
+
+// s summed over the wave's 64 lanes, pairs 32, 16, 8, 4, 2, 1 apart in turn
+__device__ __forceinline__ float wave_sum(float s) {
+  auto halves = [](auto v) { return __uint_as_float(v[0]) + __uint_as_float(v[1]); };
+  const uint32_t u = __float_as_uint(s);
+  s = halves(__builtin_amdgcn_permlane32_swap(u, u, false, false));
+  const uint32_t w = __float_as_uint(s);
+  s = halves(__builtin_amdgcn_permlane16_swap(w, w, false, false));
+  s += dpp<DPP_ROR8>(s);
+  s += dpp<DPP_ROR4>(s);  // (lanes 8 apart hold the same by now)
+  s += dpp<DPP_XOR2>(s);
+  s += dpp<DPP_XOR1>(s);
+  return s;
+}
+
 template <bool RUN_NET>
 __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint32_t relu_mask,
                                                            DevState st, StepParams p) {
-  constexpr int D = WV_D, C = WV_C;
+  constexpr int D = WV_D;
   __shared__ __attribute__((aligned(16))) float x[QW][4][D];   // each wave's four slots
   __shared__ __attribute__((aligned(16))) float a1[QW][2][WV_C1];  // its conv1 output
-  __shared__ float red[QW][2];                                   // partial sums of the final FC
-  __shared__ int32_t q_e[QR];
-  __shared__ int64_t q_t[QR], q_r[QR];
+  __shared__ __attribute__((aligned(16))) float red[2][2][QW];   // partial sums of the final FC
   __shared__ int claimed;
   const int tid = threadIdx.x, v = tid >> 6, lane = tid & 63, slot = blockIdx.x;
-  const int W = p.W;
+  const int j = lane & (QL - 1), W = p.W;
 
   // this lane's weights: conv1 channel lane % 32 (position 2v + lane / 32),
   // conv2 channel lane (position v), the final FC's weights of that channel
@@ -781,38 +918,11 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
     __syncthreads();
     k = claimed;
   }
-  int64_t cur = 0, t_w = 0, r_prev = 0, pos = 0, first = 0, n_pos = 0, pred_off = 0;
-  int32_t head = 0, count = 0, warm = 0;
-  int64_t rwv = 0;  // lane l < W: retire time of the last instruction with pos % W == l
-  // the sub-trace's state; the ring into LDS from entry 0 (head 0)
-  auto load_state = [&]() {
-    if (k >= 0) {
-      cur = st.cur[k];
-      t_w = st.t_w[k];
-      r_prev = st.r_prev[k];
-      pos = st.pos[k];
-      first = st.first[k];
-      n_pos = st.n_pos[k];
-      pred_off = st.pred_off[k];
-      const int h = st.head[k];
-      count = st.count[k];
-      warm = st.warm[k];
-      head = 0;
-      if (v == 0 && lane < count) {
-        int e = h + lane;
-        e = e >= C ? e - C : e;
-        const size_t g = (size_t)k * C + e;
-        q_e[lane] = st.q_e[g];
-        q_t[lane] = st.q_t[g];
-        q_r[lane] = st.q_r[g];
-      }
-      rwv = lane < W ? st.rw[(size_t)k * WMAX + lane] : 0;
-    }
-    __syncthreads();
-  };
+  RowQueue q{};
+  if (k >= 0) q.load(st, k, j, W);
   // this lane's window element pair: slot w = 4v + lane / 16, features
-  // f0, f0 + 1; its trace row is instruction (first + pos) - w
-  const int ls = lane >> 4, w = 4 * v + ls, f0 = (lane & 15) * 2;
+  // f0, f0 + 1; its trace row is that of the current instruction less w
+  const int ls = lane >> 4, w = 4 * v + ls, f0 = j * 2;
   auto row_of = [&](int64_t row, float (&r)[2]) {
     if (p.codes) {
       const uint32_t code = p.codes[row];
@@ -827,38 +937,40 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
   float rowv[2] = {0.f, 0.f};
   auto load_row = [&]() {
     rowv[0] = rowv[1] = 0.f;
-    if (RUN_NET && k >= 0 && pos < n_pos && w <= pos) row_of(first + pos - w, rowv);
+    if (RUN_NET && k >= 0 && q.pos < q.n_pos && w <= q.pos) row_of(q.row - w, rowv);
   };
-  load_state();
   load_row();
-  uint32_t n_clamped = 0, n_nonfinite = 0, n_mismatch = 0, n_pred = 0;
+  StepCounts n;
 
-  for (int it = 0; it < p.n_steps && k >= 0 && pos < n_pos; ++it) {
-    const int64_t g = pred_off + pos;
+  for (int it = 0; it < p.n_steps && k >= 0 && q.pos < q.n_pos; ++it) {
     float nxt[2] = {0.f, 0.f};  // the next step's row for this lane
-    if (RUN_NET && pos + 1 < n_pos && w <= pos + 1) row_of(first + pos + 1 - w, nxt);
+    if (RUN_NET && q.pos + 1 < q.n_pos && w <= q.pos + 1) row_of(q.row + 1 - w, nxt);
+    const int64_t rb = q.retire_bound(lane, W);
+    int32_t inj[2] = {0, 0};
+    if (p.lat_mode != 0)
+      for (int o = 0; o < 2; ++o) inj[o] = p.lat_table[q.g * 2 + o];
     float z[2] = {0.f, 0.f};
     if (RUN_NET) {
       // window: slot 0 the current instruction with zero dynamic columns,
-      // slot w >= 1 the w-th newest queued one (queue entry count - w)
+      // slot w >= 1 the w-th newest queued one (lane w - 1's)
       {
-        float res = 0.f, ex = 0.f;
-        bool valid = w == 0;
-        if (w >= 1 && w <= count) {
-          const int e = (head + count - w) & (QR - 1);
-          res = (float)(cur - q_t[e]);
-          ex = (float)q_e[e];
-          valid = true;
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int c = f0 + e;
-          float val = valid ? rowv[e] : 0.f;
-          if (c == p.col_res) val = res;
-          if (c == p.col_exe) val = ex;
-          if (c == p.col_sto) val = 0.f;
-          x[v][ls][c] = val;
-        }
+        const int src = (lane & ~(QL - 1)) + (w >= 1 ? w - 1 : 0);
+        float res = __shfl((float)(q.cur - q.t), src);
+        float ex = __shfl((float)q.e, src);
+        const bool queued = w >= 1 && w <= q.count, valid = w == 0 || queued;
+        res = queued ? res : 0.f;
+        ex = queued ? ex : 0.f;
+        float2 val;
+        val.x = valid ? rowv[0] : 0.f;
+        val.y = valid ? rowv[1] : 0.f;
+        auto put = [&](int c, float u) {
+          val.x = f0 == c ? u : val.x;
+          val.y = f0 + 1 == c ? u : val.y;
+        };
+        put(p.col_res, res);
+        put(p.col_exe, ex);
+        put(p.col_sto, 0.f);
+        *reinterpret_cast<float2*>(&x[v][ls][f0]) = val;
       }
       wave_lds_sync();
       // conv1: channel c1 at position 2v + pl (slots 2 pl, 2 pl + 1 of the wave)
@@ -898,17 +1010,19 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
         part[0] = wf[0] * val;
         part[1] = wf[1] * val;
       }
+      // (a wave writes this buffer again two barriers on, every wave having
+      // read it before the first of them)
+      float(&rd)[2][QW] = red[it & 1];
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        float s = part[o];
-#pragma unroll
-        for (int m = 32; m >= 1; m >>= 1) s += __shfl_xor(s, m);
-        if (lane == 0) red[v][o] = s;
+        const float s = wave_sum(part[o]);
+        if (lane == 0) rd[o][v] = s;
       }
       lds_barrier();
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        float s = ((red[0][o] + red[1][o]) + red[2][o]) + red[3][o];
+        const float4 f = *reinterpret_cast<const float4*>(rd[o]);
+        float s = ((f.x + f.y) + f.z) + f.w;
         s += bl[o];
         if (relu_mask & 4u) s = fmaxf(s, 0.f);
         z[o] = s;
@@ -918,100 +1032,365 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
     int32_t lat[2];
     if (RUN_NET) {
       if (p.logits_out && tid == 0)
-        for (int o = 0; o < 2; ++o) p.logits_out[g * 2 + o] = z[o];
+        for (int o = 0; o < 2; ++o) p.logits_out[q.g * 2 + o] = z[o];
 #pragma unroll
-      for (int o = 0; o < 2; ++o) lat[o] = round_latency(z[o], p.lat_max, n_clamped, n_nonfinite);
+      for (int o = 0; o < 2; ++o) lat[o] = round_latency(z[o], p.lat_max, n.clamped, n.nonfinite);
     }
-    ++n_pred;
+    ++n.pred;
     if (p.lat_mode != 0) {
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        const int32_t inj = p.lat_table[g * 2 + o];
-        if (RUN_NET && inj != lat[o]) ++n_mismatch;
-        lat[o] = inj;
+        if (RUN_NET && inj[o] != lat[o]) ++n.mismatch;
+        lat[o] = inj[o];
       }
     }
-    // clock and queue (Sec. 3.2): T = cur + F; the retired prefix (r <= T)
-    // leaves; r = max(T + E + 1, r_prev, r_{i-W} + 1); push
-    const int64_t Tn = cur + lat[0];
-    {
-      bool gone = false;
-      if (lane < count) gone = q_r[(head + lane) & (QR - 1)] <= Tn;
-      const int n_gone = __popcll(__ballot(gone));
-      head = (head + n_gone) & (QR - 1);
-      count -= n_gone;
-    }
-    int64_t r = Tn + lat[1] + 1;
-    r = r > r_prev ? r : r_prev;
-    const int wi = (int)(pos % W);
-    if (pos >= W) {
-      const int64_t rb = __shfl(rwv, wi) + 1;
-      r = r > rb ? r : rb;
-    }
-    if (lane == wi) rwv = r;
-    const int sl = (head + count) & (QR - 1);
-    if (count == C) {
-      head = (head + 1) & (QR - 1);  // only the newest C stay visible
-    } else {
-      ++count;
-    }
-    if (tid == 0) {
-      q_e[sl] = lat[1];
-      q_t[sl] = Tn;
-      q_r[sl] = r;
-    }
-    r_prev = r;
-    cur = Tn;
-    ++pos;
-    if (pos == warm) t_w = Tn;
-    if (pos == n_pos) {  // the drain ends (Eq. 1); the slot takes the next sub-trace
+    q.advance(lat[0], lat[1], rb, lane, j);
+    if (q.pos == q.n_pos) {  // the slot takes the next sub-trace
+      __syncthreads();  // every wave has read `claimed` of the sub-trace before
       if (tid == 0) {
-        st.fetch[k] = Tn - t_w;
-        st.drain[k] = r - Tn;
-        st.final_tick[k] = r;
-        st.warm_tick[k] = t_w;
-        st.pos[k] = pos;
-        st.cur[k] = Tn;
+        q.finish(st, k);
         claimed = claim_subtrace(st, p.n_sub);
       }
       __syncthreads();
       k = claimed;
-      load_state();
+      if (k >= 0) q.load(st, k, j, W);
       load_row();
     } else {
       rowv[0] = nxt[0];
       rowv[1] = nxt[1];
-      lds_barrier();  // the push is visible to the next step's window
     }
   }
 
-  // the slot's state back to memory, the ring from entry 0 (head 0)
+  // the slot's state back to memory
   if (tid == 0) {
     st.slot_kid[slot] = k;
+    n.add_to(st);
+  }
+  if (k >= 0 && tid < QL) q.store(st, k, j, W);
+}
+
+// --------------------------------------- the small network's 16-slot tile ---
+// Step of 16 sub-trace slots per workgroup (runs of more sub-traces than
+// quad_step_kernel is for, and every BF16 and FP8 run): what bounds a step is
+// the chain through it, not its 1.1 MFLOP per tile (MFMA FP32: 1.7 us, BF16
+// 0.1).  So all weights stay in registers for the launch; the windows stay in
+// LDS, a ring of 16 rows per slot turning one row per step (row of window
+// slot w at step it: (it - w) % 16), of which a step writes the current
+// instruction's row (requested a step before) and the dynamic columns; the
+// queues are rows of 16 lanes (RowQueue; wave v holds slots 4v .. 4v + 3);
+// wave v runs conv1 at positions 2v and 2v + 1 and conv2 at position v, so
+// only the windows and conv2's outputs cross waves: two barriers.
+// Against step_kernel<NetSmall, P>, which gathered the windows, streamed the
+// weights and updated the queues one thread per slot anew each step (us per
+// step over 120 steps, launch and results included; FP32, BF16, FP8): 3,000
+// sub-traces 7.9 -> 4.2, 4.3 -> 2.5, 6.5 -> 2.5; 16,384: 18.4 -> 11.5, 8.5 ->
+// 5.4, 13.5 -> 6.2.  Same products and sums in the same order as
+// predict_tile<NetSmall, P>, same state, work queue and results.
+template <class P>
+struct SmallTile {
+  using T = typename P::T;
+  static constexpr int D = WV_D, PAD = 16 / (int)sizeof(T);
+  static constexpr int KGS = 2 * D / P::KG;     // k-groups of either conv
+  static constexpr int SX = WV_L * D + PAD;     // window ring, per slot
+  static constexpr int SA = 2 * WV_C1 + PAD;    // a wave's conv1 output, per slot
+  static constexpr int SO = QW * WV_C2 + PAD;   // conv2 output, per slot
+  static_assert(WV_C1 == D && padded_feat(D, P::ID) == D && MT == 4 * QW, "small network shape");
+  alignas(16) T x[MT * SX];
+  alignas(16) T a1[QW][MT * SA];
+  alignas(16) T out[MT * SO];
+  alignas(16) uint32_t live[2][QW];
+};
+
+template <class P, bool RUN_NET>
+__global__ void __launch_bounds__(QW * 64, 2)
+    small_step_kernel(DevWeights wt, uint32_t relu_mask, DevState st, StepParams p) {
+  using S = SmallTile<P>;
+  using T = typename P::T;
+  constexpr int D = WV_D, KGS = S::KGS, KQ = P::KG / 4;
+  constexpr int N1 = WV_C1 / 16, N2 = WV_C2 / 16, NS1 = P::SCALED ? N1 : 1,
+                NS2 = P::SCALED ? N2 : 1;
+  constexpr int CPL = WV_C2 / 8;  // final-FC channels per lane and block
+  __shared__ S sm;
+  const int tid = threadIdx.x, v = tid >> 6, lane = tid & 63;
+  const int s = tid >> 4, j = tid & (QL - 1), W = p.W;  // slot, queue entry
+  const int mr = lane & 15, g4 = lane >> 4;             // MFMA row (slot), k quarter
+  const int fo = j >> 3, fsub = j & 7, f0 = 2 * j;
+  const int slot = blockIdx.x * MT + s;
+
+  uint4 w1[KGS][N1], w2[KGS][N2];
+  v4f b1[N1], b2[N2], s1[NS1] = {}, i1[NS1] = {}, s2[NS2] = {}, i2[NS2] = {};
+  float wl[QW][CPL], lb = 0.f;
+  float xi[2] = {1.f, 1.f}, xr = 1.f, xe = 1.f;  // FP8: input scales of this lane's columns
+  if constexpr (RUN_NET) {
+    const uint4* W1 = static_cast<const uint4*>(wt.conv_w[0]);
+    const uint4* W2 = static_cast<const uint4*>(wt.conv_w[1]);
+#pragma unroll
+    for (int kg = 0; kg < KGS; ++kg) {
+#pragma unroll
+      for (int n = 0; n < N1; ++n) w1[kg][n] = W1[(kg * N1 + n) * 64 + lane];
+#pragma unroll
+      for (int n = 0; n < N2; ++n) w2[kg][n] = W2[(kg * N2 + n) * 64 + lane];
+    }
+#pragma unroll
+    for (int n = 0; n < N1; ++n) {
+      const int c = n * 16 + 4 * g4;
+      b1[n] = *reinterpret_cast<const v4f*>(wt.conv_b[0] + c);
+      if constexpr (P::SCALED) {
+        s1[n] = *reinterpret_cast<const v4f*>(wt.conv_ws[0] + c);
+        i1[n] = *reinterpret_cast<const v4f*>(wt.conv_ai[0] + c);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < N2; ++n) {
+      const int c = n * 16 + 4 * g4;
+      b2[n] = *reinterpret_cast<const v4f*>(wt.conv_b[1] + c);
+      if constexpr (P::SCALED) {
+        s2[n] = *reinterpret_cast<const v4f*>(wt.conv_ws[1] + c);
+        i2[n] = *reinterpret_cast<const v4f*>(wt.conv_ai[1] + c);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < QW; ++b)
+#pragma unroll
+      for (int c = 0; c < CPL; ++c)
+        wl[b][c] = wt.last_w[((size_t)b * 2 + fo) * WV_C2 + fsub * CPL + c];
+    lb = wt.last_b[fo];
+    if constexpr (P::SCALED) {
+      auto scale = [&](int c) { return c >= 0 && c < D ? wt.x_inv[c] : 1.f; };
+      xi[0] = scale(f0);
+      xi[1] = scale(f0 + 1);
+      xr = scale(p.col_res);
+      xe = scale(p.col_exe);
+    }
+  }
+
+  T* const xs = sm.x + s * S::SX;
+  // feature c of trace row `row`, dynamic columns zero, in storage precision
+  auto feature = [&](int64_t row, int c) -> T {
+    if (c == p.col_res || c == p.col_exe || c == p.col_sto) return P::cvt(0.f);
+    float f;
+    if (p.codes) {
+      f = code_feature(p.codes[row], c);
+    } else if constexpr (P::ID == 1) {
+      return p.feat16[row * staged_feat(D) + c];
+    } else {
+      f = p.feat[row * D + c];
+    }
+    if constexpr (P::SCALED) f *= wt.x_inv[c];
+    return P::cvt(f);
+  };
+  // the current instruction's row: this lane's two features as they are in
+  // the trace (or its code), requested a step ahead
+  uint32_t raw[2] = {0u, 0u};
+  auto request = [&](int64_t row) {
+    if (p.codes) {
+      raw[0] = p.codes[row];
+    } else if constexpr (P::ID == 1) {
+      raw[0] = *reinterpret_cast<const uint32_t*>(p.feat16 + row * staged_feat(D) + f0);
+    } else {
+      const uint2 r = *reinterpret_cast<const uint2*>(p.feat + row * D + f0);
+      raw[0] = r.x;
+      raw[1] = r.y;
+    }
+  };
+  auto commit = [&](T* dst) {
+    T e[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int c = f0 + i;
+      float f = 0.f;
+      if (p.codes) {
+        f = code_feature(raw[0], c);
+      } else if constexpr (P::ID == 1) {
+        f = __uint_as_float(i ? raw[0] & 0xffff0000u : raw[0] << 16);
+      } else {
+        f = __uint_as_float(raw[i]);
+      }
+      const bool dyn = c == p.col_res || c == p.col_exe || c == p.col_sto;
+      if constexpr (P::SCALED) f *= xi[i];
+      e[i] = P::cvt(dyn ? 0.f : f);
+      if constexpr (P::ID == 1)  // the BF16 rows' own bits
+        if (!p.codes) e[i] = dyn ? (T)0 : (T)(i ? raw[0] >> 16 : raw[0]);
+    }
+    store_run<2 * sizeof(T)>(dst + f0, e);
+  };
+  auto zero_row = [&](T* row) {
+#pragma unroll
+    for (int q = 0; q < D * (int)sizeof(T) / 16; ++q)
+      reinterpret_cast<uint4*>(row)[q] = make_uint4(0u, 0u, 0u, 0u);
+  };
+
+  RowQueue q{};
+  bool active = false;
+  int k = st.slot_kid[slot];
+  if (k < 0) {
+    if (j == 0) k = claim_subtrace(st, p.n_sub);
+    k = __shfl(k, lane & ~(QL - 1));
+  }
+  // the slot's state, and its windows' rows but the current one's as step
+  // `it` finds them (lane j: window slot j + 1)
+  auto load = [&](int it) {
+    active = false;
     if (k >= 0) {
-      st.cur[k] = cur;
-      st.t_w[k] = t_w;
-      st.r_prev[k] = r_prev;
-      st.pos[k] = pos;
-      st.head[k] = 0;
-      st.count[k] = count;
+      q.load(st, k, j, W);
+      active = q.pos < q.n_pos;
     }
-    if (n_clamped) atomicAdd(&st.counters[0], (unsigned long long)n_clamped);
-    if (n_nonfinite) atomicAdd(&st.counters[1], (unsigned long long)n_nonfinite);
-    if (n_mismatch) atomicAdd(&st.counters[2], (unsigned long long)n_mismatch);
-    if (n_pred) atomicAdd(&st.counters[3], (unsigned long long)n_pred);
-  }
-  if (k >= 0 && v == 0) {
-    if (lane < count) {
-      const int e = (head + lane) & (QR - 1);
-      const size_t gq = (size_t)k * C + lane;
-      st.q_idx[gq] = (int32_t)(first + pos - count + lane);
-      st.q_e[gq] = q_e[e];
-      st.q_t[gq] = q_t[e];
-      st.q_r[gq] = q_r[e];
+    if constexpr (RUN_NET) {
+      T* row = xs + ((it - 1 - j) & (WV_L - 1)) * D;
+      zero_row(row);
+      if (active) {
+        if (j < q.count)
+          for (int c = 0; c < D; ++c) row[c] = feature(q.row - 1 - j, c);
+        request(q.row);
+      }
     }
-    if (lane < W) st.rw[(size_t)k * WMAX + lane] = rwv;
+  };
+  load(0);
+  StepCounts n;
+
+  for (int it = 0; it < p.n_steps; ++it) {
+    const int64_t rb = q.retire_bound(lane, W);
+    int32_t inj[2] = {0, 0};
+    if (p.lat_mode != 0 && active)
+      for (int o = 0; o < 2; ++o) inj[o] = p.lat_table[q.g * 2 + o];
+    float z[2] = {0.f, 0.f};
+    if constexpr (RUN_NET) {
+      if (active) {
+        commit(xs + (it & (WV_L - 1)) * D);
+        if (j < q.count) {
+          T* row = xs + ((it - 1 - j) & (WV_L - 1)) * D;
+          auto put = [&](int c, float u, float inv) {
+            if constexpr (P::SCALED) u *= inv;
+            if ((unsigned)c < (unsigned)D) row[c] = P::cvt(u);
+          };
+          put(p.col_res, (float)(q.cur - q.t), xr);
+          put(p.col_exe, (float)q.e, xe);
+          put(p.col_sto, 0.f, 1.f);
+        }
+        if (q.pos + 1 < q.n_pos) request(q.row + 1);
+      }
+      if (lane == 0) sm.live[it & 1][v] = 0u;
+      if (active) sm.live[it & 1][v] = 1u;
+      lds_barrier();
+      const uint4 any = *reinterpret_cast<const uint4*>(sm.live[it & 1]);
+      if (!(any.x | any.y | any.z | any.w)) break;
+      // conv1 at positions 2v, 2v + 1
+      v4f acc[2][N1];
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int n = 0; n < N1; ++n) acc[i][n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kg = 0; kg < KGS; ++kg) {
+        const int k0 = kg * P::KG + KQ * g4, tap = k0 / D, off = k0 % D;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int row = (it - 2 * (2 * v + i) - tap) & (WV_L - 1);
+          const uint4 a = *reinterpret_cast<const uint4*>(sm.x + mr * S::SX + row * D + off);
+#pragma unroll
+          for (int n = 0; n < N1; ++n) acc[i][n] = P::mma(acc[i][n], w1[kg][n], a);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int n = 0; n < N1; ++n) {
+          T e[4];
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            e[c] = to_storage_v<P>(activation_v<P>(acc[i][n][c], b1[n][c], s1[P::SCALED ? n : 0][c],
+                                                   relu_mask & 1u),
+                                   i1[P::SCALED ? n : 0][c]);
+          store_run<4 * sizeof(T)>(&sm.a1[v][mr * S::SA + i * WV_C1 + n * 16 + 4 * g4], e);
+        }
+      wave_lds_sync();
+      // conv2 at position v
+      v4f acc2[N2];
+#pragma unroll
+      for (int n = 0; n < N2; ++n) acc2[n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kg = 0; kg < KGS; ++kg) {
+        const uint4 a = *reinterpret_cast<const uint4*>(
+            &sm.a1[v][mr * S::SA + kg * P::KG + KQ * g4]);
+#pragma unroll
+        for (int n = 0; n < N2; ++n) acc2[n] = P::mma(acc2[n], w2[kg][n], a);
+      }
+#pragma unroll
+      for (int n = 0; n < N2; ++n) {
+        T e[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          e[c] = to_storage_v<P>(activation_v<P>(acc2[n][c], b2[n][c], s2[P::SCALED ? n : 0][c],
+                                                 relu_mask & 2u),
+                                 i2[P::SCALED ? n : 0][c]);
+        store_run<4 * sizeof(T)>(&sm.out[mr * S::SO + v * WV_C2 + n * 16 + 4 * g4], e);
+      }
+      lds_barrier();
+      // final FC: 8 lanes per (slot, output)
+      float f = 0.f;
+#pragma unroll
+      for (int b = 0; b < QW; ++b) {
+        alignas(16) T a[CPL];
+        __builtin_memcpy(a, __builtin_assume_aligned(
+                                &sm.out[s * S::SO + b * WV_C2 + fsub * CPL], CPL * sizeof(T) < 16
+                                                                                 ? CPL * sizeof(T)
+                                                                                 : 16),
+                         sizeof a);
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) f = fmaf(P::val(a[c]), wl[b][c], f);
+      }
+      f += dpp<DPP_XOR1>(f);
+      f += dpp<DPP_XOR2>(f);
+      f += dpp<DPP_HALF_MIRROR>(f);  // (lanes of a quad hold the same by now)
+      f += lb;
+      if (relu_mask & 4u) f = fmaxf(f, 0.f);
+      const float other = dpp<DPP_ROR8>(f);
+      z[0] = fo ? other : f;
+      z[1] = fo ? f : other;
+      if (p.logits_out && active && fsub == 0) p.logits_out[q.g * 2 + fo] = f;
+    } else if (!__any(active)) {
+      break;
+    }
+    int32_t lat[2] = {0, 0};
+    const int32_t count = q.count;
+    StepCounts m;
+    if (RUN_NET) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) lat[o] = round_latency(z[o], p.lat_max, m.clamped, m.nonfinite);
+    }
+    if (p.lat_mode != 0) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        if (RUN_NET && inj[o] != lat[o]) ++m.mismatch;
+        lat[o] = inj[o];
+      }
+    }
+    if (active) {
+      ++n.pred;
+      n.clamped += m.clamped;
+      n.nonfinite += m.nonfinite;
+      n.mismatch += m.mismatch;
+      const int kept = q.advance(lat[0], lat[1], rb, lane, j);
+      if constexpr (RUN_NET)
+        // rows that left the window: that of the entry one lane down now (a
+        // full queue's oldest is the next current row)
+        if (j >= kept && j < count) zero_row(xs + ((it - 1 - j) & (WV_L - 1)) * D);
+      if (q.pos == q.n_pos) {  // the slot takes the next sub-trace
+        if (j == 0) {
+          q.finish(st, k);
+          k = claim_subtrace(st, p.n_sub);
+        }
+        k = __shfl(k, lane & ~(QL - 1));
+        load(it + 1);
+      }
+    }
   }
+
+  if (j == 0) {
+    st.slot_kid[slot] = k;
+    n.add_to(st);
+  }
+  if (k >= 0) q.store(st, k, j, W);
 }
 
 // Predictor over explicit windows x [B][L][D] -> logits [B][NOUT]; TRUNK:
@@ -1446,6 +1825,15 @@ static const void* c3_step_fn(int prec) {
   return reinterpret_cast<const void*>(&step_kernel<Net, PFP8, true>);
 }
 
+static const void* small_step_fn(int prec, bool run_net) {
+  auto fn = [&](auto form) {
+    using P = decltype(form);
+    return run_net ? reinterpret_cast<const void*>(&small_step_kernel<P, true>)
+                   : reinterpret_cast<const void*>(&small_step_kernel<P, false>);
+  };
+  return prec == 0 ? fn(PF32{}) : prec == 1 ? fn(PBF16{}) : fn(PFP8{});
+}
+
 hipError_t c3_step_scratch(int prec, int variant, size_t* bytes) {
   const void* f = variant == 1   ? c3_step_fn<NetC3V1>(prec)
                   : variant == 2 ? c3_step_fn<NetC3V2>(prec)
@@ -1493,8 +1881,15 @@ hipError_t launch_step(int net, int prec, int variant, const DevWeights& w, uint
       hipLaunchKernelGGL(quad_step_kernel<true>, grid, block, 0, stream, w, relu, s, p);
     return hipGetLastError();
   }
-  return net == 0 ? launch_step_n<NetSmall>(prec, w, relu, s, p, stream)
-                  : launch_step_n<NetC3>(prec, w, relu, s, p, stream);
+  if (net == 0) {
+    const void* f = small_step_fn(prec, p.lat_mode != 1);
+    DevWeights wa = w;
+    DevState sa = s;
+    StepParams pa = p;
+    void* args[] = {&wa, &relu, &sa, &pa};
+    return hipLaunchKernel(f, dim3(p.n_wg), dim3(QW * 64), args, 0, stream);
+  }
+  return launch_step_n<NetC3>(prec, w, relu, s, p, stream);
 }
 
 template <class Net, class P>
@@ -1607,9 +2002,8 @@ hipError_t build_run_graph(int net, int prec, int variant, const DevWeights& w, 
     nt = QW * 64;
     grid_x = p.n_wg * MT;
   } else if (net == 0) {
-    fn = prec == 0 ? step_fn<NetSmall, PF32>(run_net)
-         : prec == 1 ? step_fn<NetSmall, PBF16>(run_net) : step_fn<NetSmall, PFP8>(run_net);
-    nt = Geo<NetSmall, PF32>::NT;
+    fn = const_cast<void*>(small_step_fn(prec, run_net));
+    nt = QW * 64;
   } else if (net == 3) {
     if (prec > 1) return hipErrorInvalidValue;
     fn = prec == 0 ? step_fn<NetC3Hyb, PF32>(run_net) : step_fn<NetC3Hyb, PBF16>(run_net);

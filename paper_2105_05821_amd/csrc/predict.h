@@ -870,20 +870,14 @@ __device__ __forceinline__ float dep_flag(uint2 m, uint2 c, int f) {
 // clamped to [0, lat_max].
 __device__ __forceinline__ int32_t round_latency(float v, int32_t lat_max, uint32_t& clamped,
                                                  uint32_t& nonfinite) {
-  if (!isfinite(v)) {
-    ++nonfinite;
-    return 0;
-  }
-  const float r = rintf(v);
-  if (r < 0.f) {
-    ++clamped;
-    return 0;
-  }
-  if (r > (float)lat_max) {
-    ++clamped;
-    return lat_max;
-  }
-  return (int32_t)r;
+  // (selects, not branches: this lies on the chain through every step)
+  const bool finite = isfinite(v);
+  const float r = rintf(v), top = (float)lat_max;
+  const bool low = finite && r < 0.f, high = finite && r > top;
+  nonfinite += !finite;
+  clamped += low || high;
+  const int32_t i = (int32_t)(finite && !low && !high ? r : 0.f);
+  return high ? lat_max : i;
 }
 
 // Execution and store latency (each at most 65535) in one 32-bit word.
