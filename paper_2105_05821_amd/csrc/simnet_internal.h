@@ -307,8 +307,28 @@ struct SumSegs {
   int32_t beta;
 };
 hipError_t launch_sum_partials(SumSegs segs, hipStream_t stream);
+// Weight gradients launched together: one launch for the products, one for
+// their split-K partials and the lists of segs.  groups(): whether a product
+// may join.  A product with rowsum set writes its k-splits' row sums there
+// (at most GROUP_SPLITS lists of M), segs.seg[bias[p]] being their sum.
+constexpr int64_t GROUP_SPLITS = 256;
+struct GemmGroup {
+  static constexpr int MAX = 5;
+  GemmArgs g[MAX];
+  struct At {  // set by launch_gemm_group
+    int32_t kind, nx, ny, first, perm, red_lanes, red_blocks;
+  } at[MAX];
+  int32_t bias[MAX];
+  int32_t count;
+};
+bool groups(GemmArgs g, int bf16_mma);
+hipError_t launch_gemm_group(GemmGroup& grp, int bf16_mma, float* part, int64_t part_cap,
+                             SumSegs& segs, hipStream_t stream);
 hipError_t launch_pad_rows(const float* src, int64_t rows, int64_t cols, int64_t ld, void* dst,
                            int32_t dst_bf16, hipStream_t stream);
+// ... and the column-sum partials of src in work, as launch_colsum_partial.
+hipError_t launch_pad_rows_sum(const float* src, int64_t rows, int64_t cols, int64_t ld, void* dst,
+                               int32_t dst_bf16, float* work, int64_t* chunks, hipStream_t stream);
 // dst[i] = src[map[i]] (0 where map[i] < 0) for i < n, in FP32 or rounded
 // to BF16, for up to MAX (map, n, dst) segments in one launch.
 struct GatherSeg {
@@ -323,7 +343,9 @@ struct GatherSegs {
   int32_t count;
 };
 hipError_t launch_map_gather_multi(const float* src, const GatherSegs& segs, hipStream_t stream);
-hipError_t launch_zero(float* p, int64_t n, hipStream_t stream);
+// Columns from .. ld - 1 of every row of p [rows][ld] cleared.
+hipError_t launch_zero_columns(float* p, int64_t rows, int64_t ld, int64_t from,
+                               hipStream_t stream);
 hipError_t launch_adam(float* w, const float* g, float* m, float* v, int64_t n, float lr, float b1,
                        float b2, float eps, int32_t t, hipStream_t stream);
 // Adam, then master[i] = w[i] and, for inv[i] = (packed byte offset, perm

@@ -16,6 +16,9 @@
 //                    strides and alignment take gemm_bf16_kernel (128x128
 //                    tiles, rounded to BF16 in LDS) and gemm_kernel (FP32
 //                    MFMA, 64x64 tiles).
+//   gemm_group_kernel, group_reduce
+//                    all weight gradients of a pass in one launch, their
+//                    partials and the bias sums in another.
 //   reductions       split-K partials summed in order with the epilogue.
 //   loss_kernel      hybrid loss per window (400-bin cross-entropy + L1 on
 //                    log1p(latency) per latency type) and its gradient
@@ -26,6 +29,7 @@
 //   pad_rows         a row-major matrix copied with its rows padded.
 //   adam kernels     Adam on FP32 master weights (and, fused, the re-layout
 //                    of the updated weights).
+#include <algorithm>
 #include <type_traits>
 
 #include "simnet_internal.h"
@@ -107,10 +111,11 @@ __device__ __forceinline__ void gemm_store_row(const GemmArgs& g, int64_t m, int
 // Split-K: workgroup z covers k in [z*kc, min(K, (z+1)*kc)) and writes its
 // raw partial product to part[z][M][N]; gemm_reduce sums the partials in
 // order and applies the epilogue.
-__device__ __forceinline__ void k_range(const GemmArgs& g, int step, int64_t* kb, int64_t* ke) {
+__device__ __forceinline__ void k_range(const GemmArgs& g, int step, int64_t z, int64_t* kb,
+                                        int64_t* ke) {
   const int64_t per = (g.K + g.ksplit - 1) / g.ksplit;
   const int64_t kc = (per + step - 1) / step * step;
-  *kb = (int64_t)blockIdx.z * kc;
+  *kb = z * kc;
   *ke = *kb + kc < g.K ? *kb + kc : g.K;
 }
 
@@ -157,7 +162,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(GemmArgs g) {
   const int64_t m0 = (int64_t)blockIdx.y * GB, n0 = (int64_t)blockIdx.x * GB;
   const int wm = wave >> 1, wn = wave & 1;
   int64_t kb, ke;
-  k_range(g, GK, &kb, &ke);
+  k_range(g, GK, blockIdx.z, &kb, &ke);
   v4f acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
@@ -359,8 +364,8 @@ constexpr int epilogue_floats() {
 template <int TM, int TN>
 __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs& g,
                                                    v4f (&acc)[TM / 32][TN / 32], float* E,
-                                                   int64_t m0, int64_t n0, int wm, int wn, int tid,
-                                                   int lane) {
+                                                   int64_t m0, int64_t n0, int64_t z, int wm,
+                                                   int wn, int tid, int lane) {
   constexpr int MI = TM / 32, NI = TN / 32;
   if (g.evec) {
     // whole 16-byte rows: the tile goes through LDS 32 rows x TN columns at a
@@ -394,7 +399,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs& g,
         }
         if (g.ksplit > 1) {
           float4* cp = reinterpret_cast<float4*>(
-              g.part + ((int64_t)blockIdx.z * g.M + mi) * g.N + n);
+              g.part + (z * g.M + mi) * g.N + n);
 #pragma unroll
           for (int q = 0; q < CW / 4; ++q)
             cp[q] = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
@@ -478,7 +483,7 @@ __device__ __forceinline__ void gemm_tile_epilogue(const GemmArgs& g,
 #pragma unroll
       for (int j = 0; j < NI; ++j) v[j] = acc[i][j][r] + bj[j];
       if (g.ksplit > 1) {
-        float* prow = g.part + ((int64_t)blockIdx.z * g.M + m) * g.N;
+        float* prow = g.part + (z * g.M + m) * g.N;
 #pragma unroll
         for (int j = 0; j < NI; ++j)
           if (nb + 16 * j < g.N) prow[nb + 16 * j] = v[j];
@@ -495,7 +500,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
   const int64_t m0 = (int64_t)blockIdx.y * HB, n0 = (int64_t)blockIdx.x * HB;
   const int wm = wave >> 1, wn = wave & 1;
   int64_t kb, ke;
-  k_range(g, HK, &kb, &ke);
+  k_range(g, HK, blockIdx.z, &kb, &ke);
   v4f acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
@@ -539,8 +544,8 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(GemmArgs g) {
     __syncthreads();
     cur ^= 1;
   }
-  gemm_tile_epilogue<HB, HB>(g, acc, reinterpret_cast<float*>(&As[0][0][0]), m0, n0, wm, wn, tid,
-                             lane);
+  gemm_tile_epilogue<HB, HB>(g, acc, reinterpret_cast<float*>(&As[0][0][0]), m0, n0, blockIdx.z, wm,
+                             wn, tid, lane);
 }
 
 // out[n] = sum_{c < cnt} src[c * stride + n] for n < N, in a fixed order:
@@ -721,17 +726,17 @@ static void launch_reduce(const float* src, int64_t cnt, int64_t stride, int64_t
   }
 }
 
-// The tile of this workgroup.  Workgroups go to the 8 XCDs in turn (id %
+// The tile of workgroup id of nx x ny.  Workgroups go to the 8 XCDs in turn (id %
 // 8), each XCD with its own L2: when the tiles of a k-split divide evenly,
 // XCD x takes the x-th eighth of them in row-major order along the longer
 // tile dimension, a band that shares the shorter operand whole and holds an
 // eighth of the other, instead of tiles from everywhere.
-__device__ __forceinline__ void xcd_tile(int64_t* tm, int64_t* tn) {
-  const int64_t nx = gridDim.x, ny = gridDim.y, tiles = nx * ny;
-  *tm = blockIdx.y;
-  *tn = blockIdx.x;
+__device__ __forceinline__ void xcd_tile(int64_t id, int64_t nx, int64_t ny, int64_t* tm,
+                                         int64_t* tn) {
+  const int64_t tiles = nx * ny;
+  *tm = id / nx;
+  *tn = id % nx;
   if (tiles % 8 != 0 || tiles < 64) return;
-  const int64_t id = (int64_t)blockIdx.y * nx + blockIdx.x;
   const int64_t t = (id % 8) * (tiles / 8) + id / 8;
   if (ny >= nx) {
     *tm = t / nx;
@@ -930,22 +935,26 @@ __device__ __forceinline__ void dma_barrier() {
     asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// three stages (A's tile, then B's); afterwards the epilogue's scratch
+constexpr int dma_elems(int TM, int TN) { return 3 * (TM + TN) * HK; }
+
+// st: LDS array of dma_elems(TM, TN), at byte address lds; id: the workgroup
+// among the nx x ny tiles of k-split z.
 template <int AM, int BM, int TM, int TN>
-__global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* st, uint32_t lds,
+                                                   int64_t id, int64_t nx, int64_t ny, int64_t z) {
   using OA = DmaOp<AM, TM>;
   using OB = DmaOp<BM, TN>;
   constexpr int MI = TM / 32, NI = TN / 32;  // 16-wide tiles per wave
-  // three stages (A's tile, then B's); afterwards the epilogue's scratch
   constexpr int SN = (TM + TN) * HK;
   static_assert(3 * SN >= 2 * epilogue_floats<TN>(), "epilogue scratch");
-  __shared__ __attribute__((aligned(1024))) uint16_t st[3 * SN];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int64_t tm, tn;
-  xcd_tile(&tm, &tn);
+  xcd_tile(id, nx, ny, &tm, &tn);
   const int64_t m0 = tm * TM, n0 = tn * TN;
   const int wm = wave >> 1, wn = wave & 1;
   int64_t kb, ke;
-  k_range(g, HK, &kb, &ke);
+  k_range(g, HK, z, &kb, &ke);
   v4f acc[MI][NI], rs[MI];
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
@@ -966,7 +975,6 @@ __global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(G
       r3.init(g.B, n0, g.N, kb, tid);
     else
       pb.init(g.B, true, n0, g.N, kb, w, lane);
-    const uint32_t lds = lds_addr(st);
     auto issue = [&](int i, int stage) __attribute__((always_inline)) {
       pa.issue(lds + stage * 2 * SN, i, ke, w);
       if constexpr (BM != 3) pb.issue(lds + stage * 2 * SN + 2 * TM * HK, i, ke, w);
@@ -1039,10 +1047,18 @@ __global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(G
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t m = m0 + wm * (TM / 2) + i * 16 + 4 * (lane >> 4) + r;
-        if (m < g.M) g.rowsum[(int64_t)blockIdx.z * g.M + m] = rs[i][r];
+        if (m < g.M) g.rowsum[z * g.M + m] = rs[i][r];
       }
   }
-  gemm_tile_epilogue<TM, TN>(g, acc, reinterpret_cast<float*>(st), m0, n0, wm, wn, tid, lane);
+  gemm_tile_epilogue<TM, TN>(g, acc, reinterpret_cast<float*>(st), m0, n0, z, wm, wn, tid, lane);
+}
+
+template <int AM, int BM, int TM, int TN>
+__global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) uint16_t st[dma_elems(TM, TN)];
+  gemm_bf16_dma_tile<AM, BM, TM, TN>(g, st, lds_addr(st),
+                                     (int64_t)blockIdx.y * gridDim.x + blockIdx.x, gridDim.x,
+                                     gridDim.y, blockIdx.z);
 }
 
 // The FP32 kernel for operands in 16-byte aligned rows, staged straight into
@@ -1121,18 +1137,18 @@ struct DmaF32 {
 };
 
 template <int AM, int BM>
-__global__ void __launch_bounds__(256, 3) gemm_f32_dma_kernel(GemmArgs g) {
+__device__ __forceinline__ void gemm_f32_dma_tile(const GemmArgs& g, float* st, uint32_t lds,
+                                                  int64_t id, int64_t nx, int64_t ny, int64_t z) {
   using OA = DmaF32<AM>;
   using OB = DmaF32<BM>;
   constexpr int TI = FT / 32, SN = 2 * FT * HK;
-  __shared__ __attribute__((aligned(1024))) float st[3 * SN];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   int64_t tm, tn;
-  xcd_tile(&tm, &tn);
+  xcd_tile(id, nx, ny, &tm, &tn);
   const int64_t m0 = tm * FT, n0 = tn * FT;
   const int wm = wave >> 1, wn = wave & 1;
   int64_t kb, ke;
-  k_range(g, HK, &kb, &ke);
+  k_range(g, HK, z, &kb, &ke);
   v4f acc[TI][TI];
   float rs[TI] = {};
 #pragma unroll
@@ -1151,7 +1167,6 @@ __global__ void __launch_bounds__(256, 3) gemm_f32_dma_kernel(GemmArgs g) {
       r3.init(g.B, n0, g.N, kb, tid);
     else
       pb.init(g.B, true, n0, g.N, kb, w, lane);
-    const uint32_t lds = lds_addr(st);
     auto issue = [&](int i, int stage) __attribute__((always_inline)) {
       pa.issue(lds + stage * 4 * SN, i, ke, w);
       if constexpr (BM != 3) pb.issue(lds + stage * 4 * SN + 4 * FT * HK, i, ke, w);
@@ -1221,10 +1236,55 @@ __global__ void __launch_bounds__(256, 3) gemm_f32_dma_kernel(GemmArgs g) {
       v += __shfl_xor(v, 16);
       v += __shfl_xor(v, 32);
       const int64_t m = m0 + wm * (FT / 2) + i * 16 + lane;
-      if (lane < 16 && m < g.M) g.rowsum[(int64_t)blockIdx.z * g.M + m] = v;
+      if (lane < 16 && m < g.M) g.rowsum[z * g.M + m] = v;
     }
   }
-  gemm_tile_epilogue<FT, FT>(g, acc, st, m0, n0, wm, wn, tid, lane);
+  gemm_tile_epilogue<FT, FT>(g, acc, st, m0, n0, z, wm, wn, tid, lane);
+}
+
+template <int AM, int BM>
+__global__ void __launch_bounds__(256, 3) gemm_f32_dma_kernel(GemmArgs g) {
+  __shared__ __attribute__((aligned(1024))) float st[dma_elems(FT, FT)];
+  gemm_f32_dma_tile<AM, BM>(g, st, lds_addr(st), (int64_t)blockIdx.y * gridDim.x + blockIdx.x,
+                            gridDim.x, gridDim.y, blockIdx.z);
+}
+
+// Several weight gradients (mode 2 both operands, or the windows as mode 3)
+// in one launch: workgroups first[p] .. of problem p, k-split by k-split.
+// Each alone leaves the chip part idle (80 to 416 workgroups, some with a few
+// k-steps, some with hundreds) and ends in a launch that adds its partials;
+// together they are one round of workgroups of equal length and one such
+// launch (group_reduce), and nothing is left for a second stream to overlap.
+// Training step, a launch or two per product on one stream up to 1,024 windows
+// (BF16) or 256 (FP32) and on two above -> grouped (us): BF16 16 152 -> 119,
+// 512 191 -> 143, 1,024 217 -> 171, 2,048 277 -> 223, 4,096 400 -> 354; FP32 16 197
+// -> 154, 256 231 -> 188, 1,024 391 -> 360, 4,096 1,004 -> 983.
+template <bool BF>
+__global__ void __launch_bounds__(256, 3) gemm_group_kernel(GemmGroup grp) {
+  using T = typename std::conditional<BF, uint16_t, float>::type;
+  constexpr int SZ = BF ? dma_elems(HB, HB) : dma_elems(FT, FT);
+  __shared__ __attribute__((aligned(1024))) T st[SZ];
+  int p = 0;
+  while (p + 1 < grp.count && (int)blockIdx.x >= grp.at[p + 1].first) ++p;
+  const GemmGroup::At at = grp.at[p];
+  const int b = (int)blockIdx.x - at.first, tiles = at.nx * at.ny;
+  const int z = b / tiles, id = b - z * tiles;
+  const GemmArgs& g = grp.g[p];
+  if (z >= g.ksplit) return;  // (first is a whole number of XCD rounds)
+  const uint32_t lds = lds_addr(st);
+  if constexpr (BF) {
+    if (at.kind == 0)
+      gemm_bf16_dma_tile<2, 2, HB, HB>(g, st, lds, id, at.nx, at.ny, z);
+    else if (at.kind == 1)
+      gemm_bf16_dma_tile<2, 2, 64, 64>(g, st, lds, id, at.nx, at.ny, z);
+    else
+      gemm_bf16_dma_tile<2, 3, 64, HB>(g, st, lds, id, at.nx, at.ny, z);
+  } else {
+    if (at.kind == 1)
+      gemm_f32_dma_tile<2, 2>(g, st, lds, id, at.nx, at.ny, z);
+    else
+      gemm_f32_dma_tile<2, 3>(g, st, lds, id, at.nx, at.ny, z);
+  }
 }
 
 // Operand access mode for the BF16 kernel (see gemm_bf16_kernel) and the
@@ -1250,34 +1310,66 @@ static void operand_mode(const GemmOperand& o, bool is_b, int32_t* mode, int32_t
   *vec = fits(16) ? 2 : fits(8) ? 1 : 0;
 }
 
-hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
-                       hipStream_t stream, int64_t* rowsum_parts) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  // grouped rows are divided in 32 bits
-  const int64_t big = (int64_t)1 << 32;
-  if ((g.A.grp < NO_GROUP && g.M >= big) || (g.B.grp < NO_GROUP && g.K >= big) ||
-      (g.mask.p && g.mask.grp < NO_GROUP && g.M >= big) || (g.cgrp < NO_GROUP && g.M >= big) ||
-      (g.ccg != 0 && (g.ccg < 0 || g.N >= big)))
-    return hipErrorInvalidValue;
+// Which kernel takes a product: 0 the general ones, 2 the LDS-direct one, 3
+// the same with the right operand FP32 in 8-byte pieces along n, rows
+// possibly grouped (the windows).  Sets the operands' modes.
+static int dma_mode(GemmArgs& g, int bf16_mma) {
   operand_mode(g.A, false, &g.amode, &g.avec);
   operand_mode(g.B, true, &g.bmode, &g.bvec);
-  // BF16 operands in aligned rows: staged straight into LDS (runs of 8 along
-  // the outer dimension within a readable extent; k in whole steps where an
-  // operand is contiguous along it)
+  // operands of the form in aligned rows: staged straight into LDS (runs of
+  // 16 bytes along the outer dimension within a readable extent; k in whole
+  // steps where an operand is contiguous along it)
   auto direct = [&](const GemmOperand& o, int32_t mode, int32_t vec, int64_t dim) {
     const int64_t cap = o.ext ? o.ext : dim;
     return (o.bf16 != 0) == (bf16_mma != 0) && vec == 2 && o.grp >= NO_GROUP &&
            ((mode == 1 && g.K % HK == 0) ||
             (mode == 2 && cap % (o.bf16 ? 8 : 4) == 0 && cap >= dim));
   };
-  // (the right operand also FP32 in 8-byte pieces along n, rows possibly
-  // grouped: the windows)
   const int64_t bcap = g.B.ext ? g.B.ext : g.N;
-  const bool dir_a = direct(g.A, g.amode, g.avec, g.M);
-  const bool dir_b = direct(g.B, g.bmode, g.bvec, g.N);
-  const bool b3 = dir_a && !dir_b && !g.B.bf16 && g.bmode == 2 && g.bvec >= 1 &&
-                  bcap % (bf16_mma ? 16 : 8) == 0 && bcap >= g.N;
-  const bool dma = dir_a && (dir_b || b3);
+  if (!direct(g.A, g.amode, g.avec, g.M)) return 0;
+  if (direct(g.B, g.bmode, g.bvec, g.N)) return 2;
+  return !g.B.bf16 && g.bmode == 2 && g.bvec >= 1 && bcap % (bf16_mma ? 16 : 8) == 0 &&
+                 bcap >= g.N
+             ? 3
+             : 0;
+}
+
+// Grouped rows are divided in 32 bits.
+static bool rows_fit(const GemmArgs& g) {
+  const int64_t big = (int64_t)1 << 32;
+  return !((g.A.grp < NO_GROUP && g.M >= big) || (g.B.grp < NO_GROUP && g.K >= big) ||
+           (g.mask.p && g.mask.grp < NO_GROUP && g.M >= big) || (g.cgrp < NO_GROUP && g.M >= big) ||
+           (g.ccg != 0 && (g.ccg < 0 || g.N >= big)));
+}
+
+// C permuted whole rows at a time, in 16-byte aligned rows (reduce_gemm_perm4).
+static bool perm_rows(const GemmArgs& g) {
+  return g.ccg > 0 && g.N == g.ccg * g.ccm && !g.bias && !g.mask.p && !g.c_bf16 &&
+         g.cgrp >= NO_GROUP && g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(g.C) % 16 == 0;
+}
+
+// The tiles' vector epilogue: split-K partials in whole 16-byte runs; else no
+// bias, N whole 16-column runs, C and the mask in 16-byte aligned rows
+// contiguous along n.
+static bool vector_epilogue(const GemmArgs& g) {
+  const int64_t mq = g.mask.bf16 ? 8 : 4;
+  const int64_t cq = g.c_bf16 ? 8 : 4;  // elements per 16 bytes of C
+  const bool c_ok = reinterpret_cast<uintptr_t>(g.C) % 16 == 0 && g.ldc % cq == 0 &&
+                    (g.cgrp >= NO_GROUP || g.cgs % cq == 0);
+  const bool m_ok = !g.mask.p || (g.mask.cs == 1 &&
+                                  reinterpret_cast<uintptr_t>(g.mask.p) % 16 == 0 &&
+                                  g.mask.rs % mq == 0 &&
+                                  (g.mask.grp >= NO_GROUP || g.mask.gs % mq == 0));
+  return g.N % 16 == 0 && (g.ksplit > 1 ? reinterpret_cast<uintptr_t>(g.part) % 16 == 0
+                                        : !g.bias && g.ccg == 0 && c_ok && m_ok);
+}
+
+hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
+                       hipStream_t stream, int64_t* rowsum_parts) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (!rows_fit(g)) return hipErrorInvalidValue;
+  const int mode = dma_mode(g, bf16_mma);
+  const bool dma = mode != 0, b3 = mode == 3;
   auto tiles_of = [&](int64_t tm, int64_t tn) {
     return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn);
   };
@@ -1305,22 +1397,7 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
   }
   g.ksplit = (int32_t)ks;
   g.part = part;
-  // the BF16 kernels' vector epilogue: split-K partials in whole 16-byte
-  // runs; else no bias, N whole 16-column runs, C and the mask in 16-byte
-  // aligned rows contiguous along n
-  {
-    const int64_t mq = g.mask.bf16 ? 8 : 4;
-    const int64_t cq = g.c_bf16 ? 8 : 4;  // elements per 16 bytes of C
-    const bool c_ok = reinterpret_cast<uintptr_t>(g.C) % 16 == 0 && g.ldc % cq == 0 &&
-                      (g.cgrp >= NO_GROUP || g.cgs % cq == 0);
-    const bool m_ok = !g.mask.p || (g.mask.cs == 1 &&
-                                    reinterpret_cast<uintptr_t>(g.mask.p) % 16 == 0 &&
-                                    g.mask.rs % mq == 0 &&
-                                    (g.mask.grp >= NO_GROUP || g.mask.gs % mq == 0));
-    g.evec = (bf16_mma || dma) && g.N % 16 == 0 &&
-             (ks > 1 ? reinterpret_cast<uintptr_t>(part) % 16 == 0
-                     : !g.bias && g.ccg == 0 && c_ok && m_ok);
-  }
+  g.evec = (bf16_mma || dma) && vector_epilogue(g);
   const dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)ks);
   if (rowsum_parts) *rowsum_parts = dma && g.rowsum ? ks : 0;
   if (!dma) g.rowsum = nullptr;
@@ -1360,10 +1437,7 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
   }
   if (ks > 1) {
     const int64_t MN = g.M * g.N;
-    const bool perm4 = g.ccg > 0 && g.N == g.ccg * g.ccm && !g.bias && !g.mask.p && !g.c_bf16 &&
-                       g.cgrp >= NO_GROUP && g.ldc % 4 == 0 &&
-                       reinterpret_cast<uintptr_t>(g.C) % 16 == 0;
-    if (ks < 64 && g.N % 4 == 0 && perm4)
+    if (ks < 64 && g.N % 4 == 0 && perm_rows(g))
       hipLaunchKernelGGL(reduce_gemm_perm4, dim3((unsigned)((MN / 4 + 255) / 256)), dim3(256), 0,
                          stream, part, ks, MN, g);
     else if (ks < 64 && g.N % 4 == 0)
@@ -1372,6 +1446,186 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
     else
       launch_reduce<true>(part, ks, MN, MN, g, nullptr, 0, stream);
   }
+  return hipGetLastError();
+}
+
+// Several lists of partials summed in one launch: workgroup b serves the
+// segment whose block range holds b; per segment L lanes per output (16 or
+// 64, or 4 for short lists), lane l summing partials c = l, l + L, ... in
+// order, then the L lane sums combined by a fixed butterfly.
+__device__ __forceinline__ void sum_seg(const SumSegs& segs, int64_t b) {
+  int s = 0;
+  while (s + 1 < segs.count && b >= segs.seg[s].blocks) {
+    b -= segs.seg[s].blocks;
+    ++s;
+  }
+  const SumSeg& q = segs.seg[s];
+  const int L = q.lanes, sub = threadIdx.x % L;
+  const int64_t n = b * (256 / L) + threadIdx.x / L;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  if (n < q.N) {
+    int64_t c = sub;
+    for (; c + 3 * L < q.cnt; c += 4 * L) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] += q.src[(c + u * L) * q.N + n];
+    }
+    for (; c < q.cnt; c += L) acc[0] += q.src[c * q.N + n];
+  }
+  float v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  for (int off = L / 2; off >= 1; off /= 2) v += __shfl_xor(v, off);
+  if (sub == 0 && n < q.N) q.out[n] = segs.beta ? q.out[n] + v : v;
+}
+
+__global__ void __launch_bounds__(256) sum_partials(SumSegs segs) { sum_seg(segs, blockIdx.x); }
+
+// Lanes and blocks of each list; the blocks in all.
+static int64_t plan_sums(SumSegs& segs) {
+  int64_t blocks = 0;
+  for (int s = 0; s < segs.count; ++s) {
+    SumSeg& q = segs.seg[s];
+    q.lanes = q.cnt >= 256 ? 64 : q.cnt >= 32 ? 16 : 4;
+    q.blocks = (q.N + 256 / q.lanes - 1) / (256 / q.lanes);
+    blocks += q.blocks;
+  }
+  return blocks;
+}
+
+// One launch that ends a group of weight gradients: the split-K partials of
+// its products added in part order (within one of L lanes, the lanes by a
+// fixed butterfly), four adjacent outputs per L lanes, in C's own order where
+// its columns are permuted, then the bias sums (sum_seg).
+__global__ void __launch_bounds__(256) group_reduce(GemmGroup grp, SumSegs segs) {
+  int p = 0;
+  int64_t b = blockIdx.x;
+  while (p < grp.count && b >= grp.at[p].red_blocks) b -= grp.at[p++].red_blocks;
+  if (p == grp.count) {
+    sum_seg(segs, b);
+    return;
+  }
+  const GemmArgs& g = grp.g[p];
+  const int L = grp.at[p].red_lanes, sub = threadIdx.x % L;
+  const int64_t MN = g.M * g.N, q = (b * (256 / L) + threadIdx.x / L) * 4;
+  const bool on = q < MN;
+  const int64_t m = on ? q / g.N : 0, n = on ? q - m * g.N : 0;
+  float a[4] = {0.f, 0.f, 0.f, 0.f};
+  if (on && grp.at[p].perm) {
+    const float* src[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t d = (uint32_t)n + e, t = d / (uint32_t)g.ccm;
+      src[e] = g.part + m * g.N + (int64_t)(d - t * (uint32_t)g.ccm) * g.ccg + t;
+    }
+#pragma unroll 4
+    for (int c = sub; c < g.ksplit; c += L)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] += src[e][c * MN];
+  } else if (on) {
+#pragma unroll 4
+    for (int c = sub; c < g.ksplit; c += L) {
+      const float4 t = *reinterpret_cast<const float4*>(g.part + c * MN + q);
+      a[0] += t.x;
+      a[1] += t.y;
+      a[2] += t.z;
+      a[3] += t.w;
+    }
+  }
+  for (int off = L / 2; off >= 1; off /= 2)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], off);
+  if (!on || sub != 0) return;
+  if (grp.at[p].perm) {
+    float4* c = reinterpret_cast<float4*>(g.C + m * g.ldc + n);
+    float4 o = make_float4(a[0], a[1], a[2], a[3]);
+    if (g.beta) {
+      const float4 was = *c;
+      o = make_float4(was.x + o.x, was.y + o.y, was.z + o.z, was.w + o.w);
+    }
+    *c = o;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) gemm_store(g, m, n + e, a[e]);
+  }
+}
+
+// Workgroups a group's work is split for, in equal numbers of k-steps: BF16 two
+// per CU (us per training step of 4,096 windows: 512 359, 640 379, 1,536 390;
+// of 1,024: 171, 175, 183), FP32, whose tiles are a quarter the size, six
+// (512 1,071, 1,024 1,009, 1,536 983, 2,048 972; of 1,024 windows 376, 365, 360,
+// 368).  A k-step with the windows operand, through registers and half as
+// much again to read, counts GROUP_X_COST times (BF16, 4,096 windows: 1 397,
+// 2 359, 3 354, 4 354).  BF16 groups of less than GROUP_SMALL tiles' k-steps (about
+// 560 windows) take 64 x 64 tiles (512 windows: 143 against 151 with 128 x 128).
+constexpr int64_t GROUP_WGS_BF16 = 512, GROUP_WGS_F32 = 1536, GROUP_X_COST = 3,
+                  GROUP_SMALL = 4096;
+
+bool groups(GemmArgs g, int bf16_mma) {
+  return g.M > 0 && g.N > 0 && g.K > 0 && g.N % 4 == 0 && rows_fit(g) &&
+         dma_mode(g, bf16_mma) != 0 && g.amode == 2 && g.bmode == 2;
+}
+
+hipError_t launch_gemm_group(GemmGroup& grp, int bf16_mma, float* part, int64_t part_cap,
+                             SumSegs& segs, hipStream_t stream) {
+  // k-steps times tiles of the whole group, in 128 x 128 tiles (BF16) or 64 x 64
+  // (FP32), to be spread over the workgroups the chip holds
+  auto tiles_of = [](const GemmArgs& g, int64_t tm, int64_t tn) {
+    return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn);
+  };
+  const int64_t T = bf16_mma ? HB : FT;
+  int mode[GemmGroup::MAX];
+  int64_t work = 0;
+  for (int p = 0; p < grp.count; ++p) {
+    GemmArgs& g = grp.g[p];
+    mode[p] = dma_mode(g, bf16_mma);
+    const int64_t tm = mode[p] == 3 ? 64 : T, tn = T;
+    work += tiles_of(g, tm, tn) * ((g.K + HK - 1) / HK);
+  }
+  const bool small = bf16_mma && work < GROUP_SMALL;
+  // k-steps a workgroup: at least 8, of the windows at least 16
+  int64_t per = work / (bf16_mma ? GROUP_WGS_BF16 : GROUP_WGS_F32);
+  if (per < 8) per = 8;
+  // (scratch kept for the products after this one, 64 splits of a small output)
+  int64_t later[GemmGroup::MAX] = {};
+  for (int p = grp.count - 2; p >= 0; --p) {
+    const int64_t MN = grp.g[p + 1].M * grp.g[p + 1].N;
+    later[p] = later[p + 1] + (MN <= 16 * 1024 ? 256 : MN <= 64 * 1024 ? 64 : 1) * ((MN + 63) / 64 * 64);
+  }
+  int64_t first = 0, red = 0;
+  for (int p = 0; p < grp.count; ++p) {
+    GemmArgs& g = grp.g[p];
+    GemmGroup::At& at = grp.at[p];
+    at.kind = mode[p] == 3 ? 2 : !bf16_mma || small ? 1 : 0;
+    const int64_t tm = at.kind == 0 ? HB : 64, tn = at.kind == 1 ? 64 : T;
+    const int64_t steps = (g.K + HK - 1) / HK, MN = g.M * g.N;
+    const int64_t mine =
+        mode[p] == 3 ? std::max(per / GROUP_X_COST, std::min<int64_t>(per, 16)) : per;
+    int64_t ks = (steps + mine - 1) / mine;
+    if (ks > GROUP_SPLITS) ks = GROUP_SPLITS;
+    const int64_t each = (MN + 63) / 64 * 64, room = part_cap - later[p];
+    if (ks > room / each) ks = room / each;
+    if (ks < 2) ks = 1;
+    g.ksplit = (int32_t)ks;
+    g.part = part;
+    if (ks > 1) {
+      part += ks * each;
+      part_cap -= ks * each;
+    }
+    g.evec = vector_epilogue(g);
+    at.nx = (int32_t)((g.N + tn - 1) / tn);
+    at.ny = (int32_t)((g.M + tm - 1) / tm);
+    at.first = (int32_t)first;
+    first += ((int64_t)at.nx * at.ny * ks + 7) / 8 * 8;
+    at.perm = perm_rows(g);
+    at.red_lanes = ks < 8 ? 1 : ks < 32 ? 4 : ks < 128 ? 16 : 64;
+    at.red_blocks = ks > 1 ? (int32_t)((MN / 4 + 256 / at.red_lanes - 1) / (256 / at.red_lanes)) : 0;
+    red += at.red_blocks;
+    if (g.rowsum) segs.seg[grp.bias[p]].cnt = ks;
+  }
+  if (first > INT32_MAX || red > INT32_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(bf16_mma ? gemm_group_kernel<true> : gemm_group_kernel<false>,
+                     dim3((unsigned)first), dim3(256), 0, stream, grp);
+  red += plan_sums(segs);
+  if (red > 0)
+    hipLaunchKernelGGL(group_reduce, dim3((unsigned)red), dim3(256), 0, stream, grp, segs);
   return hipGetLastError();
 }
 
@@ -1637,43 +1891,9 @@ hipError_t launch_colsum_partial(const void* y, int y_bf16, int64_t M, int64_t N
   return hipGetLastError();
 }
 
-// Several lists of partials summed in one launch: workgroup b serves the
-// segment whose block range holds b; per segment L lanes per output (16 or
-// 64, or 4 for short lists), lane l summing partials c = l, l + L, ... in
-// order, then the L lane sums combined by a fixed butterfly.
-__global__ void __launch_bounds__(256) sum_partials(SumSegs segs) {
-  int s = 0;
-  int64_t b = blockIdx.x;
-  while (s + 1 < segs.count && b >= segs.seg[s].blocks) {
-    b -= segs.seg[s].blocks;
-    ++s;
-  }
-  const SumSeg& q = segs.seg[s];
-  const int L = q.lanes, sub = threadIdx.x % L;
-  const int64_t n = b * (256 / L) + threadIdx.x / L;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  if (n < q.N) {
-    int64_t c = sub;
-    for (; c + 3 * L < q.cnt; c += 4 * L) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] += q.src[(c + u * L) * q.N + n];
-    }
-    for (; c < q.cnt; c += L) acc[0] += q.src[c * q.N + n];
-  }
-  float v = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-  for (int off = L / 2; off >= 1; off /= 2) v += __shfl_xor(v, off);
-  if (sub == 0 && n < q.N) q.out[n] = segs.beta ? q.out[n] + v : v;
-}
-
 hipError_t launch_sum_partials(SumSegs segs, hipStream_t stream) {
   if (segs.count < 1 || segs.count > SumSegs::MAX) return hipErrorInvalidValue;
-  int64_t blocks = 0;
-  for (int s = 0; s < segs.count; ++s) {
-    SumSeg& q = segs.seg[s];
-    q.lanes = q.cnt >= 256 ? 64 : q.cnt >= 32 ? 16 : 4;
-    q.blocks = (q.N + 256 / q.lanes - 1) / (256 / q.lanes);
-    blocks += q.blocks;
-  }
+  const int64_t blocks = plan_sums(segs);
   if (blocks == 0) return hipSuccess;
   hipLaunchKernelGGL(sum_partials, dim3((unsigned)blocks), dim3(256), 0, stream, segs);
   return hipGetLastError();
@@ -1692,6 +1912,53 @@ __global__ void pad_rows(const float* __restrict__ src, int64_t cols, int64_t ld
     static_cast<uint16_t*>(dst)[r * ld + c] = to_bf16(v);
   else
     static_cast<float*>(dst)[r * ld + c] = v;
+}
+
+// The same for an even number of columns in 8-byte aligned rows, with the
+// column sums of each chunk of `per` rows (grid y) in part[chunk][cols] on
+// the way: 128 columns per workgroup, 4 row lanes, combined as in colsum_vec.
+__global__ void __launch_bounds__(256) pad_rows_sum(const float* __restrict__ src, int64_t rows,
+                                                    int64_t cols, int64_t ld, int64_t per,
+                                                    void* __restrict__ dst, int32_t dst_bf16,
+                                                    float* __restrict__ part) {
+  __shared__ float red[512];
+  const int j = threadIdx.x % 64, r = threadIdx.x / 64;
+  const int64_t n = (int64_t)blockIdx.x * 128 + 2 * j;
+  const int64_t c = blockIdx.y, lo = c * per, hi = lo + per < rows ? lo + per : rows;
+  float a[2] = {0.f, 0.f};
+  if (n < ld) {
+#pragma unroll 4
+    for (int64_t m = lo + r; m < hi; m += 4) {
+      float2 v = make_float2(0.f, 0.f);
+      if (n < cols) v = *reinterpret_cast<const float2*>(src + m * cols + n);
+      if (dst_bf16)
+        *reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(dst) + m * ld + n) =
+            (uint32_t)to_bf16(v.x) | ((uint32_t)to_bf16(v.y) << 16);
+      else
+        *reinterpret_cast<float2*>(static_cast<float*>(dst) + m * ld + n) = v;
+      a[0] += v.x;
+      a[1] += v.y;
+    }
+  }
+  lane_tree<2>(a, red, r, j, 64, 4);
+  if (r == 0 && n < cols) *reinterpret_cast<float2*>(part + c * cols + n) = make_float2(a[0], a[1]);
+}
+
+hipError_t launch_pad_rows_sum(const float* src, int64_t rows, int64_t cols, int64_t ld, void* dst,
+                               int32_t dst_bf16, float* work, int64_t* chunks,
+                               hipStream_t stream) {
+  if (rows <= 0 || cols % 2 || ld % 2 || reinterpret_cast<uintptr_t>(src) % 8 ||
+      (ld + 127) / 128 > INT32_MAX) {
+    const hipError_t e = launch_pad_rows(src, rows, cols, ld, dst, dst_bf16, stream);
+    return e != hipSuccess ? e : launch_colsum_partial(src, 0, rows, cols, cols, work, chunks, stream);
+  }
+  int64_t n = (rows + 31) / 32;  // about 8 rows per lane
+  if (n > COLSUM_MAX_CHUNKS) n = COLSUM_MAX_CHUNKS;
+  const int64_t per = (rows + n - 1) / n;
+  *chunks = (rows + per - 1) / per;
+  hipLaunchKernelGGL(pad_rows_sum, dim3((unsigned)((ld + 127) / 128), (unsigned)*chunks), dim3(256),
+                     0, stream, src, rows, cols, ld, per, dst, dst_bf16, work);
+  return hipGetLastError();
 }
 
 hipError_t launch_pad_rows(const float* src, int64_t rows, int64_t cols, int64_t ld, void* dst,
@@ -1736,14 +2003,22 @@ hipError_t launch_map_gather_multi(const float* src, const GatherSegs& segs, hip
   return hipGetLastError();
 }
 
-__global__ void zero_kernel(float* __restrict__ p, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = 0.f;
+// Columns from .. ld - 1 of every row of p [rows][ld] cleared.
+__global__ void __launch_bounds__(256) zero_columns(float* __restrict__ p, int64_t rows, int64_t ld,
+                                                    int64_t from) {
+  const int64_t n = ld - from, total = rows * n;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * 256) {
+    const int64_t r = i / n;
+    p[r * ld + from + (i - r * n)] = 0.f;
+  }
 }
 
-hipError_t launch_zero(float* p, int64_t n, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, p, n);
+hipError_t launch_zero_columns(float* p, int64_t rows, int64_t ld, int64_t from,
+                               hipStream_t stream) {
+  if (rows <= 0 || from >= ld) return hipSuccess;
+  const int64_t blocks = std::min<int64_t>((rows * (ld - from) + 255) / 256, 4096);
+  hipLaunchKernelGGL(zero_columns, dim3((unsigned)blocks), dim3(256), 0, stream, p, rows, ld, from);
   return hipGetLastError();
 }
 

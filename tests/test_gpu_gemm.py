@@ -1,7 +1,7 @@
 """The training products at the sizes where their kernels change or have
 edges: batches whose contractions end in a short k-step, 64- and 128-wide
-tiles, split and unsplit K, one stream and two, and a save buffer that is not
-16-byte aligned (the general kernels).
+tiles, split and unsplit K, and a save buffer that is not 16-byte aligned (the
+general kernels).
 
 The reference is the backward pass in float64 on the GPU's own saved
 activations and loss gradient (so no ReLU sits on another side), with the
@@ -66,6 +66,27 @@ def reference(torch, ws, x, acts, dz, prec):
 @pytest.mark.parametrize("B,shift", [(1, 0), (5, 0), (33, 0), (64, 0), (257, 0), (1030, 0),
                                      (37, 8)])
 def test_training_products(torch, sn, prec, B, shift):
+    products(torch, sn, prec, B, shift)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("B,x_off,dz_off,dp_off", [
+    (45, 1, 0, 0), (45, 0, 1, 0), (45, 0, 0, 1), (45, 1, 1, 3), (2, 0, 0, 0), (556, 0, 0, 0),
+    (600, 0, 0, 0), (2050, 0, 0, 2)])
+def test_weight_gradients_together(torch, sn, prec, B, x_off, dz_off, dp_off):
+    """Weight gradients in one launch: either side of the batch where their
+    tiles change, many k-splits, and windows, loss gradients or parameter
+    gradients that start off a 16- or 8-byte boundary (offsets in floats: a
+    product on its own, a copy and sums on their own, single stores)."""
+    products(torch, sn, prec, B, 0, x_off, dz_off, dp_off)
+
+
+def moved_by(torch, t, off):
+    out = torch.empty(t.numel() + off, dtype=t.dtype, device=t.device)[off:].view(t.shape)
+    return out.copy_(t)
+
+
+def products(torch, sn, prec, B, shift, x_off=0, dz_off=0, dp_off=0):
     layers = synth.net_c3_hybrid()
     ws, bs = synth.init_weights(3, layers, out_bias=None, out_gain=1.0)
     pred = sn.Predictor(layers, prec)
@@ -75,10 +96,11 @@ def test_training_products(torch, sn, prec, B, shift):
     y = torch.randint(0, 420, (B, 2), generator=gen, device="cuda").int()
     z, save = pred.forward(x)
     _, dz = pred.loss(z, y)
+    x, dz = moved_by(torch, x, x_off), moved_by(torch, dz, dz_off)
     n = pred.save_bytes(B)
     moved = torch.empty(n + shift, dtype=torch.uint8, device="cuda")[shift:]
     moved.copy_(save[:n])
-    dp = torch.empty(2_204_642, device="cuda")
+    dp = torch.empty(2_204_642 + dp_off, device="cuda")[dp_off:]
     dx = pred.backward(x, moved, dz, dp, want_dx=True)
     v = save[:n].view(torch.float32 if prec == 0 else torch.bfloat16).double()
     sizes = (52 * 64, 26 * 128, 13 * 256, 512)
