@@ -2064,15 +2064,13 @@ __device__ __forceinline__ float adam_one(const float* __restrict__ w,
 // master copy and, where inv gives byte offsets (-1: none), to its packed and
 // permuted copies in the form's precision (BF16 rounded to nearest even, as
 // map_gather_multi writes them): the update and the re-layout in one pass.
-// Thread t takes parameter t, or t + skip_n from skip_lo on (a range that
-// adam_hidden_tiles updates).
-__global__ void adam_relayout_kernel(float* __restrict__ w, const float* __restrict__ g,
-                                     float* __restrict__ m, float* __restrict__ v, int64_t n,
-                                     float lr, float b1, float b2, float eps, float c1, float c2,
-                                     float* __restrict__ master, const int2* __restrict__ inv,
-                                     char* __restrict__ packed, char* __restrict__ perm,
-                                     int32_t bf16, int64_t skip_lo, int64_t skip_n) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Index t is parameter t, or t + skip_n from skip_lo on (a range that
+// adam_hidden_tile updates).
+__device__ __forceinline__ void adam_relayout_one(
+    int64_t i, float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
+    float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float c1, float c2,
+    float* __restrict__ master, const int2* __restrict__ inv, char* __restrict__ packed,
+    char* __restrict__ perm, int32_t bf16, int64_t skip_lo, int64_t skip_n) {
   if (i >= skip_lo) i += skip_n;
   if (i >= n) return;
   const float wi = adam_one(w, g, m, v, i, lr, b1, b2, eps, c1, c2);
@@ -2091,28 +2089,29 @@ __global__ void adam_relayout_kernel(float* __restrict__ w, const float* __restr
 
 // The hidden layer's weights (HO outputs x HC channels x HP positions,
 // parameter o*HC*HP + c*HP + p) in tiles of HTO outputs x HTC channels: Adam
-// on the tile's rows (contiguous runs of HTC*HP parameters, four requested
-// per thread before any is used), the new weights to the master copy and to
+// on the tile's rows (contiguous runs of HTC*HP parameters, all of a thread's
+// requested before any is used), the new weights to the master copy and to
 // LDS, then from LDS to the permuted copy ([p*HC + c][o]: runs of HTO
 // outputs) and the packed copy (per position p the K = HC x N = HO fragment
 // order of the forward kernels: k-groups of KG channels, 16-output tiles,
 // lane (k % KG) / E * 16 + o % 16, element k % E, E = KG / 4: whole 64 x E
 // blocks), in the form's precision.
 constexpr int HO = 512, HC = 256, HP = 13, HTO = 16, HTC = 32, HROW = HTC * HP + 1;
-__global__ void __launch_bounds__(256)
-    adam_hidden_tiles(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                      float* __restrict__ v, float lr, float b1, float b2, float eps, float c1,
-                      float c2, float* __restrict__ master, char* __restrict__ packed,
-                      char* __restrict__ perm, int32_t bf16, int32_t KG) {
-  __shared__ float T[HTO * HROW];  // [o - o0][(c - c0) * HP + p], rows padded by one
-  constexpr int NT = HTO * HTC * HP, U = 4;
-  const int o0 = blockIdx.x * HTO, c0 = blockIdx.y * HTC;
-  for (int base = threadIdx.x; base < NT; base += 256 * U) {
+constexpr int AT = 1024;  // threads
+__device__ __forceinline__ void adam_hidden_tile(
+    int tile, float* T, float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
+    float* __restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2,
+    float* __restrict__ master, char* __restrict__ packed, char* __restrict__ perm, int32_t bf16,
+    int32_t KG) {
+  // T: [o - o0][(c - c0) * HP + p], rows padded by one
+  constexpr int NT = HTO * HTC * HP, U = (NT + AT - 1) / AT;
+  const int o0 = tile % (HO / HTO) * HTO, c0 = tile / (HO / HTO) * HTC;
+  {
     int64_t ii[U];
     float gv[U], mv[U], vv[U], wv[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int idx = base + u * 256;
+      const int idx = threadIdx.x + u * AT;
       const int r = idx / (HTC * HP), col = idx - r * (HTC * HP);
       ii[u] = (int64_t)(o0 + r) * (HC * HP) + c0 * HP + col;
       if (idx < NT) {
@@ -2124,7 +2123,7 @@ __global__ void __launch_bounds__(256)
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int idx = base + u * 256;
+      const int idx = threadIdx.x + u * AT;
       if (idx >= NT) continue;
       float mi = mv[u], vi = vv[u];
       const float wi = adam_math(gv[u], mi, vi, wv[u], lr, b1, b2, eps, c1, c2);
@@ -2138,7 +2137,7 @@ __global__ void __launch_bounds__(256)
   }
   __syncthreads();
   // permuted copy: element (p, c, o) at (p*HC + c)*HO + o
-  for (int idx = threadIdx.x; idx < NT; idx += 256) {
+  for (int idx = threadIdx.x; idx < NT; idx += AT) {
     const int ol = idx % HTO, rest = idx / HTO, cl = rest % HTC, p = rest / HTC;
     const float x = T[ol * HROW + cl * HP + p];
     const int64_t q = ((int64_t)p * HC + c0 + cl) * HO + o0 + ol;
@@ -2149,7 +2148,7 @@ __global__ void __launch_bounds__(256)
   }
   // packed copy: per position p, blocks (kg, nt) of 64 lanes x E elements
   const int E = KG / 4, BLK = 64 * E, NKG = HTC / KG, NNT = HTO / 16;
-  for (int idx = threadIdx.x; idx < NT; idx += 256) {
+  for (int idx = threadIdx.x; idx < NT; idx += AT) {
     const int blk = idx / BLK, wi = idx - blk * BLK, lane = wi / E, e = wi - lane * E;
     const int ntl = blk % NNT, rest = blk / NNT, kgl = rest % NKG, p = rest / NKG;
     const int kg = c0 / KG + kgl, nt = o0 / 16 + ntl;
@@ -2163,6 +2162,29 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// Both in one launch: workgroups 0 .. hid_tiles - 1 a tile of the hidden layer
+// each, the others AT of the remaining parameters.  What bounds it is the
+// latency of 16 bytes read and written per parameter: 16 waves per CU with all
+// their reads in flight, and one launch (4,096 windows' step: 7 + 25 us as two
+// launches of 256 threads with four reads in flight -> 18; 64 windows: 16).
+__global__ void __launch_bounds__(AT)
+    adam_relayout_kernel(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
+                         float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps,
+                         float c1, float c2, float* __restrict__ master,
+                         const int2* __restrict__ inv, char* __restrict__ packed,
+                         char* __restrict__ perm, int32_t bf16, int32_t hid_tiles, int64_t hid_off,
+                         int64_t hid_n, char* __restrict__ hid_packed,
+                         char* __restrict__ hid_perm) {
+  __shared__ float T[HTO * HROW];
+  const int b = (int)blockIdx.x;
+  if (b < hid_tiles)
+    adam_hidden_tile(b, T, w + hid_off, g + hid_off, m + hid_off, v + hid_off, lr, b1, b2, eps, c1,
+                     c2, master + hid_off, hid_packed, hid_perm, bf16, bf16 ? 32 : 16);
+  else
+    adam_relayout_one((int64_t)(b - hid_tiles) * AT + threadIdx.x, w, g, m, v, n, lr, b1, b2, eps,
+                      c1, c2, master, inv, packed, perm, bf16, hid_off, hid_n);
+}
+
 hipError_t launch_adam_relayout(float* w, const float* g, float* m, float* v, int64_t n, float lr,
                                 float b1, float b2, float eps, int32_t t, float* master,
                                 const int2* inv, void* packed, void* perm, int32_t bf16,
@@ -2172,16 +2194,13 @@ hipError_t launch_adam_relayout(float* w, const float* g, float* m, float* v, in
   const int64_t hn = hid_packed ? (int64_t)HO * HC * HP : 0;
   if (hid_packed && (hid_off < 0 || hid_off + hn > n)) return hipErrorInvalidValue;
   const int64_t rest = n - hn;
-  if (rest > 0)
-    hipLaunchKernelGGL(adam_relayout_kernel, dim3((unsigned)((rest + 255) / 256)), dim3(256), 0,
-                       stream, w, g, m, v, n, lr, b1, b2, eps, c1, c2, master, inv,
-                       static_cast<char*>(packed), static_cast<char*>(perm), bf16,
-                       hid_packed ? hid_off : n, hn);
-  if (hid_packed)
-    hipLaunchKernelGGL(adam_hidden_tiles, dim3(HO / HTO, HC / HTC), dim3(256), 0, stream,
-                       w + hid_off, g + hid_off, m + hid_off, v + hid_off, lr, b1, b2, eps, c1,
-                       c2, master + hid_off, static_cast<char*>(hid_packed),
-                       static_cast<char*>(hid_perm), bf16, bf16 ? 32 : 16);
+  const int32_t tiles = hid_packed ? HO / HTO * (HC / HTC) : 0;
+  const int64_t blocks = tiles + (rest + AT - 1) / AT;
+  if (blocks > 0)
+    hipLaunchKernelGGL(adam_relayout_kernel, dim3((unsigned)blocks), dim3(AT), 0, stream, w, g, m, v,
+                       n, lr, b1, b2, eps, c1, c2, master, inv, static_cast<char*>(packed),
+                       static_cast<char*>(perm), bf16, tiles, hid_packed ? hid_off : n, hn,
+                       static_cast<char*>(hid_packed), static_cast<char*>(hid_perm));
   return hipGetLastError();
 }
 
