@@ -272,7 +272,7 @@ struct GemmArgs {
   // (FP32, k in order), written by the pipelined BF16 kernel only
   float* rowsum;
   // set by launch_gemm
-  int32_t ksplit, amode, avec, bmode, bvec, evec;
+  int32_t ksplit, amode, avec, bmode, bvec, evec, fold;
   float* part;
 };
 // bf16_mma: BF16 MFMA with operands rounded to BF16 (else FP32 MFMA).  part

@@ -940,7 +940,10 @@ constexpr int dma_elems(int TM, int TN) { return 3 * (TM + TN) * HK; }
 
 // st: LDS array of dma_elems(TM, TN), at byte address lds; id: the workgroup
 // among the nx x ny tiles of k-split z.
-template <int AM, int BM, int TM, int TN>
+// FOLD: the k-steps in runs of g.fold, each run's sums accumulated from zero
+// and then added in order, as k-splits of that length and their reduction
+// make them.
+template <int AM, int BM, int TM, int TN, bool FOLD = false>
 __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* st, uint32_t lds,
                                                    int64_t id, int64_t nx, int64_t ny, int64_t z) {
   using OA = DmaOp<AM, TM>;
@@ -955,7 +958,8 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* 
   const int wm = wave >> 1, wn = wave & 1;
   int64_t kb, ke;
   k_range(g, HK, z, &kb, &ke);
-  v4f acc[MI][NI], rs[MI];
+  v4f acc[MI][NI], rs[MI], tot[FOLD ? MI : 1][FOLD ? NI : 1] = {};
+  int left = FOLD ? g.fold : 0;  // k-steps to the end of the run
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     rs[i] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -1000,6 +1004,17 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* 
                                                          __builtin_bit_cast(v8bf_t, one), rs[i],
                                                          0, 0, 0);
       }
+      if constexpr (FOLD)
+        if (--left == 0) {
+          left = g.fold;
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+              tot[i][j] += acc[i][j];
+              acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+            }
+        }
     };
     // k-step i reads stage i % 3 (cur) once its loads have landed everywhere;
     // then the stage of step i - 1 (nxt), which every wave has read, takes
@@ -1041,6 +1056,11 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* 
     }
     __syncthreads();
   }
+  if constexpr (FOLD)
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[i][j] = tot[i][j] + acc[i][j];
   if (do_rs && (lane & 15) == 0) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -1053,10 +1073,10 @@ __device__ __forceinline__ void gemm_bf16_dma_tile(const GemmArgs& g, uint16_t* 
   gemm_tile_epilogue<TM, TN>(g, acc, reinterpret_cast<float*>(st), m0, n0, z, wm, wn, tid, lane);
 }
 
-template <int AM, int BM, int TM, int TN>
+template <int AM, int BM, int TM, int TN, bool FOLD = false>
 __global__ void __launch_bounds__(256, TM == 128 ? 3 : 4) gemm_bf16_dma_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint16_t st[dma_elems(TM, TN)];
-  gemm_bf16_dma_tile<AM, BM, TM, TN>(g, st, lds_addr(st),
+  gemm_bf16_dma_tile<AM, BM, TM, TN, FOLD>(g, st, lds_addr(st),
                                      (int64_t)blockIdx.y * gridDim.x + blockIdx.x, gridDim.x,
                                      gridDim.y, blockIdx.z);
 }
@@ -1385,15 +1405,30 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
   // weight gradient of 4,096 windows 28.6 us with 256 workgroups, 35.8 with
   // 512; the hidden layer's 104 tiles 38.9 with 416, 42.3 with 208; FP32 74
   // with 512, 89 with 256)
+  auto splits = [&](int64_t t, int64_t target, int64_t step) {
+    int64_t n = target / t;
+    const int64_t steps = g.K / (step * 8);
+    if (n > steps) n = steps;
+    if (n > part_cap / (g.M * g.N)) n = part_cap / (g.M * g.N);
+    if (n > 65535) n = 65535;
+    return n < 2 ? 1 : n;
+  };
   int64_t ks = 1;
-  const int64_t target = dma && bf16_mma && !b3 && tiles < 64 ? 256 : 512;
-  if (part && tiles < 128) {
-    ks = target / tiles;
-    const int64_t steps = g.K / ((bf16_mma || dma ? HK : GK) * 8);
-    if (ks > steps) ks = steps;
-    if (ks > part_cap / (g.M * g.N)) ks = part_cap / (g.M * g.N);
-    if (ks > 65535) ks = 65535;
-    if (ks < 2) ks = 1;
+  g.fold = 0;
+  if (g.c_bf16) {
+    // The result is rounded to BF16, so its number of partial sums is part of
+    // it: by 128 x 128 tiles whatever the kernel.  64 x 64 tiles add them up
+    // themselves (two or three, k is short: a split's launch that adds its
+    // partials costs more than it saves, 64 windows' step 114 us against 113,
+    // 4,096 345 against 340).
+    if (part && tiles_of(HB, HB) < 128) ks = splits(tiles_of(HB, HB), 512, HK);
+    if (small && ks > 1) {
+      g.fold = (int32_t)(((g.K + ks - 1) / ks + HK - 1) / HK);
+      ks = 1;
+    }
+  } else if (part && tiles < 128) {
+    ks = splits(tiles, dma && bf16_mma && !b3 && tiles < 64 ? 256 : 512,
+                bf16_mma || dma ? HK : GK);
   }
   g.ksplit = (int32_t)ks;
   g.part = part;
@@ -1416,6 +1451,13 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
   } else if (b3) {
     g.amode == 1 ? launch(gemm_bf16_dma_kernel<1, 3, 64, 128>)
                  : launch(gemm_bf16_dma_kernel<2, 3, 64, 128>);
+  } else if (small && g.fold) {
+    if (g.amode == 1)
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64, true>)
+                   : launch(gemm_bf16_dma_kernel<1, 2, 64, 64, true>);
+    else
+      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, 64, 64, true>)
+                   : launch(gemm_bf16_dma_kernel<2, 2, 64, 64, true>);
   } else if (small) {
     if (g.amode == 1)
       g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64>)
@@ -1580,7 +1622,7 @@ hipError_t launch_gemm_group(GemmGroup& grp, int bf16_mma, float* part, int64_t 
     work += tiles_of(g, tm, tn) * ((g.K + HK - 1) / HK);
   }
   const bool small = bf16_mma && work < GROUP_SMALL;
-  // k-steps a workgroup: at least 8, of the windows at least 16
+  // k-steps a workgroup: at least 8
   int64_t per = work / (bf16_mma ? GROUP_WGS_BF16 : GROUP_WGS_F32);
   if (per < 8) per = 8;
   // (scratch kept for the products after this one, 64 splits of a small output)
@@ -1596,13 +1638,15 @@ hipError_t launch_gemm_group(GemmGroup& grp, int bf16_mma, float* part, int64_t 
     at.kind = mode[p] == 3 ? 2 : !bf16_mma || small ? 1 : 0;
     const int64_t tm = at.kind == 0 ? HB : 64, tn = at.kind == 1 ? 64 : T;
     const int64_t steps = (g.K + HK - 1) / HK, MN = g.M * g.N;
-    const int64_t mine =
-        mode[p] == 3 ? std::max(per / GROUP_X_COST, std::min<int64_t>(per, 16)) : per;
+    const int64_t mine = mode[p] == 3 ? std::max<int64_t>(per / GROUP_X_COST, 8) : per;
     int64_t ks = (steps + mine - 1) / mine;
     if (ks > GROUP_SPLITS) ks = GROUP_SPLITS;
     const int64_t each = (MN + 63) / 64 * 64, room = part_cap - later[p];
     if (ks > room / each) ks = room / each;
     if (ks < 2) ks = 1;
+    // (a large permuted output in two splits, stored whole rows at a time by
+    // group_reduce, rather than element by element: FP32, 256 windows, 177 -> 172)
+    if (ks < 2 && steps > 1 && MN > 64 * 1024 && perm_rows(g) && room / each >= 2) ks = 2;
     g.ksplit = (int32_t)ks;
     g.part = part;
     if (ks > 1) {
