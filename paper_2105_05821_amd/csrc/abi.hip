@@ -599,11 +599,12 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
 // 43; 128 tiles 2 units 46, 4 units 58; 163 tiles 2 units 81 against 54 on
 // one workgroup per tile).
 static SplitShape split_shape(const sim_ctx* c, int64_t tiles) {
-  if (!c->split.part || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1};
+  const int32_t max = c->n_cu / 8 * 8;
+  if (!c->split.part || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1, max};
   const int64_t groups = split_groups(c->net, c->cfg.prec);
   for (int32_t s : {4, 2, 1})
-    if (tiles * groups * s <= c->n_cu) return SplitShape{(int32_t)groups, s};
-  return SplitShape{(int32_t)std::min<int64_t>(groups, c->n_cu / tiles), 1};
+    if (tiles * groups * s <= c->n_cu) return SplitShape{(int32_t)groups, s, max};
+  return SplitShape{(int32_t)std::min<int64_t>(groups, c->n_cu / tiles), 1, max};
 }
 
 // ------------------------------------------------------------ training ---
@@ -1584,7 +1585,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   const float* xs = static_cast<const float*>(x);
   hipError_t e = hipSuccess;
   auto part = [&](int64_t n) {
-    const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1};
+    const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1, 0};
     if (n <= 0 || e != hipSuccess) return;
     e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits,
                                              SaveBlock{}, c->split.part, sh, c->stream)

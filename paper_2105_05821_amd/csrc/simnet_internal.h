@@ -381,6 +381,7 @@ hipError_t launch_rb_trunk(int prec, const DevWeights& w, uint32_t relu, const f
 // columns over `slices` (1, 2 or 4).
 struct SplitShape {
   int32_t units, slices;
+  int32_t max_wgs;  // workgroups resident at once (one per CU, 8 XCDs alike)
 };
 constexpr int SPLIT_RING = 128;       // queue entries per slot, position mod 128
 constexpr int SPLIT_MAX_TILES = 128;  // tiles of MT windows the buffers hold
