@@ -594,10 +594,10 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
 // column slices as one workgroup per CU allows (a workgroup's LDS fills a
 // CU); with more tiles, fewer units of several groups.  units < 2: not worth
 // splitting (one workgroup per tile).  More workgroups than CUs lose, each
-// round paying the head and the update again (us per step, BF16: 32 tiles 4
-// units x 2 or 1 slices 28, x 4 38; 85 tiles 3 units 37, 4 units 53, 2 units
-// 43; 128 tiles 2 units 46, 4 units 58; 163 tiles 2 units 81 against 54 on
-// one workgroup per tile).
+// round paying the head and the update again (us per step, BF16: 16 tiles 4
+// units x 4 slices 18.2, x 2 19.6; 32 tiles 4 units x 2 slices 21, x 1 25, x 4
+// 37; 85 tiles 3 units 36, 4 units 52, 2 units 40; 128 tiles 2 units 43, 4
+// units 57, unsplit 51; 163 tiles 2 units 81 against 54 unsplit).
 static SplitShape split_shape(const sim_ctx* c, int64_t tiles) {
   const int32_t max = c->n_cu / 8 * 8;
   if (!c->split.part || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1, max};

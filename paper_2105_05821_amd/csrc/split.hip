@@ -16,11 +16,13 @@
 // one-workgroup step in the same order, so the results are identical.
 //
 // Time per step, one workgroup per tile -> split (uniform sub-traces):
-// BF16 16 sub-traces 47 -> 17 us, 512 49 -> 28, 1,024 51 -> 33, 2,048 54 ->
-// 47; FP32 16 221 -> 36, 512 224 -> 58, 2,048 224 -> 144; a forward of one
-// window BF16 47 -> 15, FP32 207 -> 28.  What bounds a small step now: ~4.5
-// us to launch, ~4 us for the sums, head and update, then one group's
-// convolutions (~6 us) and its weights' latency.
+// BF16 16 sub-traces 47 -> 16 us, 512 49 -> 21, 1,024 51 -> 27, 2,048 54 ->
+// 43; FP32 16 221 -> 36, 512 224 -> 51, 2,048 224 -> 138; a forward of one
+// window BF16 47 -> 15, FP32 207 -> 28.  What bounds a small step now: ~6 us
+// to launch, add the sums and run the head and the update, then ~9 us of one
+// group's convolutions and its slice of the hidden layer, each layer waiting
+// for the latency of its weights.  (The first group's trace rows requested
+// before the head changed nothing.)
 //
 // RB7's step is three launches: this kernel with the convolutions only, the
 // residual blocks, FC 512's group sums (1,000 windows BF16: 28 + 357 + 38 +
