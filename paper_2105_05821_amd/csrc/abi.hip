@@ -1574,10 +1574,12 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   // n windows: few split over several workgroups per tile (split_shape), at
   // most one round of workgroups in one kernel, more through rows (BF16,
   // FWD_ROUNDS rounds at a time; without their memory, or under capture while
-  // there is none yet, in one kernel too)
+  // there is none yet, in one kernel too).  The memory is for FWD_ROUNDS rounds
+  // at once, so it stays where it is: a captured call may be replayed after any
+  // other.
   const int64_t round = (int64_t)MT * c->n_cu;
   bool rows = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && B > round;
-  const int64_t most = std::min(B, FWD_ROUNDS * round);
+  const int64_t most = FWD_ROUNDS * round;
   if (rows && most > c->rb_ws_B) {
     rows = !capturing(c->stream) && trunk_workspace(c, most) == hipSuccess;
     if (!rows) (void)hipGetLastError();

@@ -167,3 +167,30 @@ def test_forward_over_rounds_equals_single_tiles(torch, sn, net):
               4 * rnd, len(x)):
         assert torch.equal(s.forward(x[:B].contiguous()), want[:B]), B
     s.close()
+
+
+def test_captured_forwards_replay(torch, sn):
+    """A captured forward of few windows (split) and of more than a round
+    (through memory), replayed between eager calls of other sizes, gives the
+    eager result every time."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        s = simulator(sn, torch, "c3", 1, np.array([0]), np.array([8]), np.array([0], np.int32))
+        rnd = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+        x = torch.randn((2 * rnd, L, D), device="cuda",
+                        generator=torch.Generator("cuda").manual_seed(5))
+        want = s.forward(x)
+        side.synchronize()
+        for B in (5, rnd + rnd // 2):
+            xb = x[:B].contiguous()
+            out = torch.empty_like(want[:B])
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                out.copy_(s.forward(xb))
+            for i in range(3):
+                out.zero_()
+                graph.replay()
+                side.synchronize()
+                assert torch.equal(out, want[:B]), (B, i)
+                assert torch.equal(s.forward(x[:B - 1 - i].contiguous()), want[:B - 1 - i])
+        s.close()
