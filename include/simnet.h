@@ -298,7 +298,11 @@ SIMNET_API int sim_act_scales(const sim_ctx* ctx, float* out, int32_t n);
  * [B][n_slot][n_feat] float32, logits DEVICE [B][network outputs] float32
  * (n_out = 2 for the regression head, 22 for the hybrid head and RB7).
  * RB7 uses a workspace of B * 13 * 256 elements of the form, kept by the
- * context and grown as needed.  save_or_null must be NULL except for the
+ * context and grown as needed.  C3 in BF16 (regression or hybrid head) takes
+ * more than 16 windows per CU through a workspace of 64 windows per CU, 6.7 KB
+ * each, allocated at the first such call and kept (without it, or when that
+ * first call is being captured, in one kernel; the same results).
+ * save_or_null must be NULL except for the
  * training head, where it is required.
  *
  * Training head (Sec. 2.3's hybrid output, Sec. 4's training set-up): a
