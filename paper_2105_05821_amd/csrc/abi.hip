@@ -502,7 +502,7 @@ bool layers_match(const sim_layer* layers, int32_t n) {
 // The split step's and forward's buffers, laid out from byte `at` of a block
 // (`base` NULL: the size only); returns the end.  Group sums for
 // SPLIT_MAX_TILES tiles, and for a simulation whose slots fit them the
-// per-slot state.
+// per-slot state and its tiles' group sums once more.
 static size_t split_layout(const sim_ctx* c, char* base, size_t at, SplitBufs* out) {
   const int net = c->cfg.n_out == 3 ? 4 : 1;
   const size_t groups = (size_t)split_groups(net, c->cfg.prec);
@@ -515,7 +515,8 @@ static size_t split_layout(const sim_ctx* c, char* base, size_t at, SplitBufs* o
     at += (n * sizeof(T) + 255) / 256 * 256;
   };
   SplitBufs b{};
-  take(b.part, (size_t)SPLIT_MAX_TILES * groups * MT * NetC3::HID);
+  take(b.part[0], (size_t)SPLIT_MAX_TILES * groups * MT * NetC3::HID);
+  take(b.part[1], slots * groups * NetC3::HID);
   take(b.cst, slots);
   take(b.scal[0], slots);
   take(b.scal[1], slots);
@@ -600,7 +601,7 @@ static int upload_weights(sim_ctx* c, int prec, const float* params,
 // units 57, unsplit 51; 163 tiles 2 units 81 against 54 unsplit).
 static SplitShape split_shape(const sim_ctx* c, int64_t tiles) {
   const int32_t max = c->n_cu / 8 * 8;
-  if (!c->split.part || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1, max};
+  if (!c->split.part[0] || tiles < 1 || tiles > SPLIT_MAX_TILES) return SplitShape{1, 1, max};
   const int64_t groups = split_groups(c->net, c->cfg.prec);
   for (int32_t s : {4, 2, 1})
     if (tiles * groups * s <= c->n_cu) return SplitShape{(int32_t)groups, s, max};
@@ -744,7 +745,7 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
     }
     // (a context without a simulation: the split forward's sums too)
     const size_t pf = (qf * 4 + 255) / 256 * 256;
-    const bool split = !c->split.part;
+    const bool split = !c->split.part[0];
     if (e == hipSuccess)
       e = hipMalloc(&T.perm, split ? split_layout(c, nullptr, pf, nullptr) : qf * 4);
     if (e == hipSuccess && split)
@@ -1179,7 +1180,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     if (e == hipSuccess) e = hipMalloc(&c->rb_logits, sizeof(float) * slots * NetRB7::NOUT);
     if (e != hipSuccess) return hip_fail(c, e, "hipMalloc RB7 step buffers");
   }
-  if (!c->has_trace && c->net != 0 && !c->split.part) {  // the split forward's sums
+  if (!c->has_trace && c->net != 0 && !c->split.part[0]) {  // the split forward's sums
     if (hipMalloc(&c->dev_block, split_layout(c, nullptr, 0, nullptr)) == hipSuccess) {
       split_layout(c, static_cast<char*>(c->dev_block), 0, &c->split);
     } else {
@@ -1399,7 +1400,7 @@ static hipError_t split_steps(sim_ctx* c, int64_t n_steps, int32_t mode, const i
       e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_trunk, win * NetRB7::NB,
                            c->rb_active, c->n_cu, c->stream);
       if (e == hipSuccess)
-        e = launch_split_fc(c->cfg.prec, c->w, c->rb_trunk, win, c->rb_active, c->split.part,
+        e = launch_split_fc(c->cfg.prec, c->w, c->rb_trunk, win, c->rb_active, c->split.part[0],
                             split_shape(c, tiles), c->stream);
     }
   }
@@ -1534,7 +1535,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     hipError_t e =
         sh.units >= 2 ? launch_split_forward(2, c->cfg.prec, c->w, c->relu,
                                              static_cast<const float*>(x), B, nullptr, sb,
-                                             c->split.part, sh, c->stream)
+                                             c->split.part[0], sh, c->stream)
                       : launch_forward_save(c->cfg.prec, c->w, c->relu,
                                             static_cast<const float*>(x), B, sb, c->stream);
     TrainState& T = c->tr;
@@ -1562,9 +1563,9 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
       e = launch_resblocks(c->cfg.prec, c->w, c->relu, c->rb_ws, B * NetRB7::NB, nullptr, c->n_cu,
                            c->stream);
     if (e == hipSuccess && split) {
-      e = launch_split_fc(c->cfg.prec, c->w, c->rb_ws, B, nullptr, c->split.part, sh, c->stream);
+      e = launch_split_fc(c->cfg.prec, c->w, c->rb_ws, B, nullptr, c->split.part[0], sh, c->stream);
       if (e == hipSuccess)
-        e = launch_split_rb_head(c->cfg.prec, c->w, c->relu, c->split.part, B, logits, c->stream);
+        e = launch_split_rb_head(c->cfg.prec, c->w, c->relu, c->split.part[0], B, logits, c->stream);
     } else if (e == hipSuccess) {
       e = launch_rb_head(c->cfg.prec, c->w, c->relu, c->rb_ws, B, nullptr, logits, c->stream);
     }
@@ -1590,7 +1591,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1, 0};
     if (n <= 0 || e != hipSuccess) return;
     e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits,
-                                             SaveBlock{}, c->split.part, sh, c->stream)
+                                             SaveBlock{}, c->split.part[0], sh, c->stream)
         : rows && n > round
             ? launch_forward_rows(c->net, c->w, c->relu, xs, n, static_cast<uint16_t*>(c->rb_ws),
                                   logits, c->n_cu,

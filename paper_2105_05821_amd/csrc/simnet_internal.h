@@ -397,7 +397,9 @@ struct alignas(16) SlotScalars {
 };
 // Per slot: constants, scalars (two buffers, read and written by alternate
 // launches), the queue ring and (store latencies) the stores' ring by
-// sequence number mod SPLIT_RING; per tile and group the hidden layer's sums.
+// sequence number mod SPLIT_RING; per tile and group the hidden layer's sums
+// (two buffers likewise; forwards use the first, the second is for the
+// simulation's tiles only).
 struct SplitBufs {
   SlotConst* cst;
   SlotScalars* scal[2];
@@ -405,7 +407,7 @@ struct SplitBufs {
   int64_t *q_t, *q_r;
   int32_t *m_idx, *m_es;
   int64_t *m_t, *m_r, *m_x;
-  float* part;
+  float* part[2];
 };
 // Rounds (MT windows per CU) launch_forward_rows takes at once: its head runs
 // up to 4 row tiles per workgroup.
@@ -419,8 +421,9 @@ hipError_t launch_split_import(const DevState& s, const SplitBufs& sp, int tiles
 hipError_t launch_split_export(const DevState& s, const SplitBufs& sp, int tiles, int in,
                                int32_t C, int32_t W, hipStream_t stream);
 // One launch of the first `tiles` tiles: finish = head and update of the
-// previous launch's sums (scalars from buffer in to the other), predict = the
-// next step's sums.
+// previous launch's sums (in buffer in; scalars from buffer in to the other),
+// predict = the next step's sums (to buffer in ^ 1, without finish to buffer
+// in).
 hipError_t launch_split_step(int net, int prec, const DevWeights& w, uint32_t relu,
                              const DevState& s, const StepParams& p, const SplitBufs& sp,
                              SplitShape sh, int tiles, int in, int finish, int predict,

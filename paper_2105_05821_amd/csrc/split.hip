@@ -10,10 +10,13 @@
 // column slices of the weights, leaving each group's FP32 sums in memory.
 // The next launch's workgroups all begin by adding the groups' sums in order,
 // then run the head and the clock and queue update on the tile (redundantly,
-// so that no second launch and no wait between workgroups is needed; unit 0
-// slice 0 writes the new state, into the other of two buffers, so no
-// workgroup of the launch reads what it writes).  The sums are those of the
-// one-workgroup step in the same order, so the results are identical.
+// so that no second launch and no wait between workgroups is needed).  A
+// launch reads one of two buffers and writes the other, both the sums (every
+// workgroup its groups') and the new scalars (unit 0 slice 0), so no workgroup
+// reads what another of its launch writes, whenever each of them starts: beside
+// another stream's kernel some start after others have ended.  The sums are
+// those of the one-workgroup step in the same order, so the results are
+// identical.
 //
 // Time per step, one workgroup per tile -> split (uniform sub-traces):
 // BF16 16 sub-traces 47 -> 16 us, 512 49 -> 21, 1,024 51 -> 27, 2,048 54 ->
@@ -150,9 +153,10 @@ struct SplitSmem {
   int32_t m_new[MT], m_vis[MT];     // stores shown: m_vis of them, up to sequence number m_new
 };
 
-// One step of every tile: (finish) the previous launch's sums through the
-// head and the update, from scalars sp.scal[in] to the other buffer;
-// (predict) this step's sums.  Grid: tiles x units x CS, tile by tile, or
+// One step of every tile: (finish) the previous launch's sums sp.part[in]
+// through the head and the update, from scalars sp.scal[in] to the other
+// buffer; (predict) this step's sums, to the buffer that goes with the scalars
+// as they are now.  Grid: tiles x units x CS, tile by tile, or
 // (xcd_tiles = tiles) tile t's workgroups t mod 8 + 8 i.
 template <class Net, class P, bool DEP, int CS>
 __global__ void __launch_bounds__(Net::WAVES * 64)
@@ -204,7 +208,9 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
         is_store = p.codes ? code_feature(p.codes[ii], p.store_col) != 0.f
                            : p.feat[ii * Net::D + p.store_col] != 0.f;
     v4f hacc[(Net::HID / 16) / Net::WAVES];
-    add_groups<Net, P>(reinterpret_cast<const float4*>(sp.part), tile, hacc, wave, lane);
+    // (RB7's are written between the launches, always to the first buffer)
+    add_groups<Net, P>(reinterpret_cast<const float4*>(sp.part[Net::NRES > 0 ? 0 : in]), tile, hacc,
+                       wave, lane);
     sm.net.stage_head(wt, tid, G::NT);
     __syncthreads();
     head_tile<Net, P, false, false>(wt, relu_mask, sm.net, hacc, nullptr, nullptr, {});
@@ -388,7 +394,8 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
   run_units<Net, P, CS, TRUNK, TRUNK>(wt, relu_mask, sm.net, tile,
                                       unit_begin<Net, P>(unit, units),
                                       unit_begin<Net, P>(unit + 1, units), slice,
-                                      reinterpret_cast<float4*>(sp.part), sv, load, commit);
+                                      reinterpret_cast<float4*>(sp.part[finish ? in ^ 1 : in]), sv,
+                                      load, commit);
 }
 
 // Sub-trace state -> split form: slot i runs sub-trace order[i] (every

@@ -194,3 +194,45 @@ def test_captured_forwards_replay(torch, sn):
                 assert torch.equal(out, want[:B]), (B, i)
                 assert torch.equal(s.forward(x[:B - 1 - i].contiguous()), want[:B - 1 - i])
         s.close()
+
+
+@pytest.mark.parametrize("net,prec,n_sub,other", [
+    ("c3", 1, 512, 2400), ("c3", 0, 512, 2400), ("c3", 2, 300, 2400), ("dep", 1, 512, 2400),
+    ("hyb", 1, 777, 2400), ("st", 1, 512, 2400), ("st", 0, 290, 2400), ("rb7", 1, 200, 2400),
+    ("c3", 1, 512, 2048), ("hyb", 0, 2048, 512)])
+def test_split_run_beside_another_context(torch, sn, net, prec, n_sub, other):
+    """A split run on one stream beside another context's steps on a second.
+    The other context's workgroups hold CUs (2,400 sub-traces: 150 of them for
+    its whole launch; fewer: a split run too), so a launch's workgroups start at
+    different times, some after others of their tile have ended: every output
+    equals that of the same run alone, one workgroup per tile."""
+    start, length, warm = streams(n_sub, 3)
+    n_out = NETS[net][0]()[-1].c_out
+    n = 100
+    o_start = np.arange(other, dtype=np.int64) * n
+    o_len = np.full(other, n, np.int64)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        s = simulator(sn, torch, net, prec, start, length, warm)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        o = simulator(sn, torch, "c3", 1, o_start, o_len, np.zeros(other, np.int32), codes=True)
+    o_want = o.run()
+    s.set_tuning(0, (n_sub + 15) // 16 - 1)
+    want_z = torch.full((s.n_pred, n_out), np.nan, device="cuda")
+    got_z = torch.zeros_like(want_z)
+    torch.cuda.synchronize()
+    s.record_logits(want_z)
+    want = s.run()
+    s.set_tuning(0, (n_sub + 15) // 16)
+    s.record_logits(got_z)
+    for i in range(3):
+        o.reset()
+        s.reset()
+        torch.cuda.synchronize()
+        got_z.zero_()
+        torch.cuda.synchronize()
+        o.step(n)
+        same(s.run(), want)
+        assert torch.equal(got_z, want_z), i
+        same(o.run(), o_want)
+    s.close()
+    o.close()
