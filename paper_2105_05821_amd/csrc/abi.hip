@@ -1585,30 +1585,23 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     rows = !capturing(c->stream) && trunk_workspace(c, most) == hipSuccess;
     if (!rows) (void)hipGetLastError();
   }
-  const float* xs = static_cast<const float*>(x);
+  // a few windows beyond whole rounds cost less split than as one more round
+  // (us, 4,100 windows: 102 in one piece, 82 as 4,096 and 4; 8,200: 141, 134)
+  const int64_t over = rows ? B % round : 0, rest = over <= round / 8 ? over : 0;
+  const int64_t whole = rows ? B - rest : 0;
   hipError_t e = hipSuccess;
-  auto part = [&](int64_t n) {
+  for (int64_t at = 0, n; at < B && e == hipSuccess; at += n) {
+    n = at < whole ? std::min(whole - at, most) : B - at;
+    const float* xs = static_cast<const float*>(x) + at * c->cfg.n_slot * c->cfg.n_feat;
+    float* out = logits + at * n_outputs(c->net);
     const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1, 0};
-    if (n <= 0 || e != hipSuccess) return;
-    e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits,
+    e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, out,
                                              SaveBlock{}, c->split.part[0], sh, c->stream)
         : rows && n > round
             ? launch_forward_rows(c->net, c->w, c->relu, xs, n, static_cast<uint16_t*>(c->rb_ws),
-                                  logits, c->n_cu,
-                                  c->stream)
-            : launch_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, logits, c->stream);
-    xs += n * c->cfg.n_slot * c->cfg.n_feat;
-    logits += n * n_outputs(c->net);
-    B -= n;
-  };
-  if (rows) {
-    // a few windows beyond whole rounds cost less split than as one more
-    // round (us, 4,100 windows: 102 in one piece, 82 as 4,096 and 4; 8,200:
-    // 141, 134)
-    const int64_t over = B % round, rest = over <= round / 8 ? over : 0;
-    while (B - rest > 0) part(std::min(B - rest, most));
+                                  out, c->n_cu, c->stream)
+            : launch_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, out, c->stream);
   }
-  part(B);
   if (e != hipSuccess) return hip_fail(c, e, "forward launch");
   return SIM_OK;
 }

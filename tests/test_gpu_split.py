@@ -236,3 +236,24 @@ def test_split_run_beside_another_context(torch, sn, net, prec, n_sub, other):
         same(o.run(), o_want)
     s.close()
     o.close()
+
+
+def test_large_forward_returns_an_error(torch, sn):
+    """A batch of several passes whose first pass fails (here an error that an
+    earlier call of this thread left behind and the launch picks up) returns
+    the error, and the next call is right."""
+    import ctypes
+    hip = ctypes.CDLL("libamdhip64.so.7")
+    s = simulator(sn, torch, "hyb", 1, np.array([0]), np.array([8]), np.array([0], np.int32))
+    rnd = 16 * torch.cuda.get_device_properties(0).multi_processor_count
+    x = torch.randn((4 * rnd + rnd // 2, L, D), device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(3))
+    want = s.forward(x)
+    out = torch.empty_like(want)
+    torch.cuda.synchronize()
+    assert hip.hipSetDevice(-1) != 0
+    with pytest.raises(sn.SimError):
+        s.forward(x, out)
+    torch.cuda.synchronize()
+    assert torch.equal(s.forward(x, out), want)
+    s.close()
