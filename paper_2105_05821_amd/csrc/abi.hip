@@ -946,8 +946,10 @@ int sim_init(const sim_config* cfg, const sim_trace* tr, sim_ctx** out) {
   if (tr->n_sub == 0) {  // predictor-only: forward/backward on explicit windows
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      (void)hipGetLastError();
       c->n_cu = 0;
+    }
     c->has_trace = false;
     *out = c;
     return SIM_OK;
@@ -1579,7 +1581,9 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   // at once, so it stays where it is: a captured call may be replayed after any
   // other.
   const int64_t round = (int64_t)MT * c->n_cu;
-  bool rows = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && B > round;
+  // (a predictor-only context may not know its device's CUs: one kernel then)
+  bool rows =
+      (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && round > 0 && B > round;
   const int64_t most = FWD_ROUNDS * round;
   if (rows && most > c->rb_ws_B) {
     rows = !capturing(c->stream) && trunk_workspace(c, most) == hipSuccess;
