@@ -55,12 +55,13 @@ struct sim_ctx {
   int32_t n_wg_max = 0;             // slots allocated at init
   int32_t variant = 0;              // tuning variant of the step kernel
   int32_t n_cu = 0;
-  // split step and forward (C3 networks, few windows): buffers, steps taken
-  // since the reset (a lower bound), each tile's longest sub-trace in claim
-  // order
   std::vector<char> results;  // host side of sim_run's one copy
+  // split step and forward (C3 networks, few windows): buffers, steps taken
+  // since the reset (a lower bound; 0 from a captured reset on, which may be
+  // replayed after any step), each tile's longest sub-trace in claim order
   SplitBufs split{};
   int64_t steps_done = 0;
+  bool reset_captured = false;
   std::vector<int64_t> tile_len;
   const uint32_t* codes = nullptr;  // packed trace (SIM_FEAT_CODE32)
   const uint2* mem = nullptr;       // addresses for the dependency flags
@@ -1194,9 +1195,17 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
   return sim_reset(c);
 }
 
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 int sim_reset(sim_ctx* c) {
   if (!c) return SIM_EINVAL;
   if (!c->has_trace) return SIM_OK;
+  c->reset_captured = c->reset_captured || capturing(c->stream);
   hipError_t e = launch_reset(c->st, c->n_sub, c->n_wg_max * MT, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reset");
   c->completed = false;
@@ -1363,11 +1372,9 @@ static int rb_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t* t
   return SIM_OK;
 }
 
-static bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return true;
+// n_steps steps of every sub-trace launched.
+static void count_steps(sim_ctx* c, int64_t n_steps) {
+  if (!c->reset_captured) c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
 }
 
 // Whether a step of this run is split over several workgroups per tile: a C3
@@ -1428,7 +1435,7 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
   if (split_step(c, mode)) {
     const hipError_t e = split_steps(c, n_steps, mode, table);
     if (e != hipSuccess) return hip_fail(c, e, "split step launch");
-    c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
+    count_steps(c, n_steps);
     return SIM_OK;
   }
   if (c->net == 5 && mode != SIM_LAT_INJECT) return rb_launch(c, n_steps, mode, table);
@@ -1438,8 +1445,7 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
                              c->st, p, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "step launch");
   // (launches under capture may never run, and slots that refill lag)
-  if ((int64_t)c->n_wg * MT >= c->n_sub && !capturing(c->stream))
-    c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
+  if ((int64_t)c->n_wg * MT >= c->n_sub && !capturing(c->stream)) count_steps(c, n_steps);
   return SIM_OK;
 }
 

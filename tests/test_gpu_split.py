@@ -257,3 +257,27 @@ def test_large_forward_returns_an_error(torch, sn):
     torch.cuda.synchronize()
     assert torch.equal(s.forward(x, out), want)
     s.close()
+
+
+@pytest.mark.parametrize("net", ["c3", "rb7"])
+def test_captured_reset_replayed_after_steps(torch, sn, net):
+    """A reset that was captured and is replayed after eager steps: the run
+    that follows is a whole run (the host does not see the replay)."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        start, length, warm = streams(50, 3)
+        s = simulator(sn, torch, net, 1, start, length, warm)
+        want = s.run()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            s.reset()
+        for n in (3, 9, 40):
+            graph.replay()
+            s.step(n)
+            side.synchronize()
+        graph.replay()
+        same(s.run(), want)
+        s.reset()
+        s.step(5)
+        same(s.run(), want)
+        s.close()
