@@ -1536,10 +1536,17 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   if (B < 0 || (B > 0 && (!x || !logits))) return fail(c, SIM_EINVAL, "bad batch arguments");
   if (B == 0) return SIM_OK;
   if ((B + MT - 1) / MT > INT32_MAX) return fail(c, SIM_EINVAL, "batch too large");
+  // A captured call may be replayed on any stream, beside other replays and
+  // the context's own work, so under capture nothing of the context's memory
+  // is written where the network needs none (RB7 does): one workgroup per tile.
+  const bool captured = capturing(c->stream);
+  auto shape = [&](int64_t n) {
+    return captured || c->net == 0 ? SplitShape{1, 1, 0} : split_shape(c, (n + MT - 1) / MT);
+  };
   if (c->net == 2) {
     if (!save_or_null) return fail(c, SIM_EINVAL, "the training form needs a save buffer");
     const SaveBlock sb = save_block(c, save_or_null, B);
-    const SplitShape sh = split_shape(c, (B + MT - 1) / MT);
+    const SplitShape sh = shape(B);
     hipError_t e =
         sh.units >= 2 ? launch_split_forward(2, c->cfg.prec, c->w, c->relu,
                                              static_cast<const float*>(x), B, nullptr, sb,
@@ -1560,7 +1567,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     if (B > INT64_MAX / (NetRB7::NB * NetRB7::CH3 * 4)) return fail(c, SIM_EINVAL, "batch too large");
     if (hipError_t e = trunk_workspace(c, B); e != hipSuccess)
       return hip_fail(c, e, "hipMalloc RB7 workspace");
-    const SplitShape sh = split_shape(c, (B + MT - 1) / MT);
+    const SplitShape sh = shape(B);
     const bool split = sh.units >= 2;
     hipError_t e = split ? launch_split_trunk(c->cfg.prec, c->w, c->relu,
                                               static_cast<const float*>(x), B, c->rb_ws, sh,
@@ -1582,17 +1589,15 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   }
   // n windows: few split over several workgroups per tile (split_shape), at
   // most one round of workgroups in one kernel, more through rows (BF16,
-  // FWD_ROUNDS rounds at a time; without their memory, or under capture while
-  // there is none yet, in one kernel too).  The memory is for FWD_ROUNDS rounds
-  // at once, so it stays where it is: a captured call may be replayed after any
-  // other.
+  // FWD_ROUNDS rounds at a time, in memory allocated once; without it, or under
+  // capture, in one kernel too).
   const int64_t round = (int64_t)MT * c->n_cu;
   // (a predictor-only context may not know its device's CUs: one kernel then)
-  bool rows =
-      (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && round > 0 && B > round;
+  bool rows = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && round > 0 && B > round &&
+              !captured;
   const int64_t most = FWD_ROUNDS * round;
   if (rows && most > c->rb_ws_B) {
-    rows = !capturing(c->stream) && trunk_workspace(c, most) == hipSuccess;
+    rows = trunk_workspace(c, most) == hipSuccess;
     if (!rows) (void)hipGetLastError();
   }
   // a few windows beyond whole rounds cost less split than as one more round
@@ -1604,7 +1609,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
     n = at < whole ? std::min(whole - at, most) : B - at;
     const float* xs = static_cast<const float*>(x) + at * c->cfg.n_slot * c->cfg.n_feat;
     float* out = logits + at * n_outputs(c->net);
-    const SplitShape sh = c->net != 0 ? split_shape(c, (n + MT - 1) / MT) : SplitShape{1, 1, 0};
+    const SplitShape sh = shape(n);
     e = sh.units >= 2 ? launch_split_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, out,
                                              SaveBlock{}, c->split.part[0], sh, c->stream)
         : rows && n > round

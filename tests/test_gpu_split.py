@@ -281,3 +281,71 @@ def test_captured_reset_replayed_after_steps(torch, sn, net):
         s.step(5)
         same(s.run(), want)
         s.close()
+
+
+@pytest.mark.parametrize("net,prec,B", [("c3", 1, 5), ("c3", 0, 40), ("hyb", 1, 600), ("st", 1, 33),
+                                        ("c3", 1, 4600)])
+def test_captured_forwards_replay_at_once(torch, sn, net, prec, B):
+    """Two captured forwards of one context replayed on two streams, beside
+    the context's own steps: none shares memory with another."""
+    side, a, b = (torch.cuda.Stream() for _ in range(3))
+    with torch.cuda.stream(side):
+        start, length, warm = streams(300, 3)
+        s = simulator(sn, torch, net, prec, start, length, warm)
+        want_run = s.run()
+        x = torch.randn((2, B, L, D), device="cuda",
+                        generator=torch.Generator("cuda").manual_seed(7))
+        want = [s.forward(x[i]) for i in range(2)]
+        out = [torch.zeros_like(w) for w in want]
+        graphs = [torch.cuda.CUDAGraph() for _ in range(2)]
+        for g, xi, o in zip(graphs, x, out):
+            with torch.cuda.graph(g, stream=side):
+                s.forward(xi, o)
+    torch.cuda.synchronize()
+    for i in range(4):
+        for o in out:
+            o.zero_()
+        s.reset()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            s.step(10)
+        for g, st in zip(graphs, (a, b)):
+            with torch.cuda.stream(st):
+                for _ in range(3):
+                    g.replay()
+        same(s.run(), want_run)
+        torch.cuda.synchronize()
+        for o, w in zip(out, want):
+            assert torch.equal(o, w), i
+    s.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_captured_training_forwards_replay_at_once(torch, sn, prec):
+    side, a, b = (torch.cuda.Stream() for _ in range(3))
+    layers = synth.net_c3_hybrid()
+    params = sn.flat_params(*synth.init_weights(2, layers, out_bias=None, out_gain=1.0))
+    with torch.cuda.stream(side):
+        pred = sn.Predictor(layers, prec)
+        pred.load_weights(layers, params)
+        x = torch.randn((2, 40, L, D), device="cuda",
+                        generator=torch.Generator("cuda").manual_seed(7))
+        want = [pred.forward(xi) for xi in x]
+        graphs, got = [], []
+        for xi in x:
+            graphs.append(torch.cuda.CUDAGraph())
+            with torch.cuda.graph(graphs[-1], stream=side):
+                got.append(pred.forward(xi))
+    torch.cuda.synchronize()
+    for i in range(4):
+        for z, save in got:
+            z.zero_()
+            save.zero_()
+        torch.cuda.synchronize()
+        for g, st in zip(graphs, (a, b)):
+            with torch.cuda.stream(st):
+                g.replay()
+        torch.cuda.synchronize()
+        for (z, save), (wz, ws) in zip(got, want):
+            assert torch.equal(z, wz) and torch.equal(save, ws), i
+    pred.close()
