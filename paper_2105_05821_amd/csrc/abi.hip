@@ -744,13 +744,18 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
       T.perm_off[l] = qf;
       qf += (T.n_perm[l] + 63) / 64 * 64;
     }
-    // (a context without a simulation: the split forward's sums too)
+    // (a context without a simulation: the split forward's sums too, if they fit)
     const size_t pf = (qf * 4 + 255) / 256 * 256;
     const bool split = !c->split.part[0];
-    if (e == hipSuccess)
-      e = hipMalloc(&T.perm, split ? split_layout(c, nullptr, pf, nullptr) : qf * 4);
-    if (e == hipSuccess && split)
-      split_layout(c, reinterpret_cast<char*>(T.perm), pf, &c->split);
+    if (e == hipSuccess && split) {
+      if (hipMalloc(&T.perm, split_layout(c, nullptr, pf, nullptr)) == hipSuccess) {
+        split_layout(c, reinterpret_cast<char*>(T.perm), pf, &c->split);
+      } else {
+        (void)hipGetLastError();
+        T.perm = nullptr;
+      }
+    }
+    if (e == hipSuccess && !T.perm) e = hipMalloc(&T.perm, qf * 4);
     if (e != hipSuccess) return hip_fail(c, e, "training buffers");
     // per master parameter its byte offsets in the packed and permuted
     // copies (-1: none), for sim_adam_load's re-layout in the update pass
