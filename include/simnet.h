@@ -300,13 +300,14 @@ SIMNET_API int sim_act_scales(const sim_ctx* ctx, float* out, int32_t n);
  * RB7 uses a workspace of B * 13 * 256 elements of the form, kept by the
  * context and grown as needed.  C3 in BF16 (regression or hybrid head) takes
  * more than 16 windows per CU through a workspace of 64 windows per CU, 6.7 KB
- * each, allocated at the first such call and kept (without it in one kernel;
- * the same results).  Up to 2,048 windows the C3 networks' forwards (the
- * training head's too) pass through sums in the context's memory.  A captured
- * call takes one kernel that uses no memory of the context (RB7: the workspace
- * above), so it may be replayed on several streams, or beside a run.
- * save_or_null must be NULL except for the
- * training head, where it is required.
+ * each, kept; the first such call takes one kernel and allocates it behind (if
+ * it is refused, later calls take one kernel too; the same results).  Up to
+ * 2,048 windows the C3 networks' forwards (the training head's too) pass
+ * through group sums in the context's memory (17 to 55 MB, part of every C3
+ * context).  A captured call takes one kernel that uses no memory of the
+ * context (RB7: the workspace above), so it may be replayed on several streams,
+ * or beside a run.  save_or_null must be NULL except for the training head,
+ * where it is required.
  *
  * Training head (Sec. 2.3's hybrid output, Sec. 4's training set-up): a
  * 111x50 context loaded with the layer list conv 50->64, conv 64->128,

@@ -1594,17 +1594,14 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
   }
   // n windows: few split over several workgroups per tile (split_shape), at
   // most one round of workgroups in one kernel, more through rows (BF16,
-  // FWD_ROUNDS rounds at a time, in memory allocated once; without it, or under
-  // capture, in one kernel too).
-  const int64_t round = (int64_t)MT * c->n_cu;
+  // FWD_ROUNDS rounds at a time, in memory of one size; without it, or under
+  // capture, in one kernel too).  The first such call has no memory yet: it
+  // takes the one kernel and allocates behind it.
+  const int64_t round = (int64_t)MT * c->n_cu, most = FWD_ROUNDS * round;
   // (a predictor-only context may not know its device's CUs: one kernel then)
-  bool rows = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && round > 0 && B > round &&
-              !captured;
-  const int64_t most = FWD_ROUNDS * round;
-  if (rows && most > c->rb_ws_B) {
-    rows = trunk_workspace(c, most) == hipSuccess;
-    if (!rows) (void)hipGetLastError();
-  }
+  const bool many = (c->net == 1 || c->net == 3) && c->cfg.prec == SIM_BF16 && round > 0 &&
+                    B > round && !captured;
+  const bool rows = many && most <= c->rb_ws_B;
   // a few windows beyond whole rounds cost less split than as one more round
   // (us, 4,100 windows: 102 in one piece, 82 as 4,096 and 4; 8,200: 141, 134)
   const int64_t over = rows ? B % round : 0, rest = over <= round / 8 ? over : 0;
@@ -1623,6 +1620,7 @@ int predictor_fwd(sim_ctx* c, const void* x, int64_t B, float* logits, void* sav
             : launch_forward(c->net, c->cfg.prec, c->w, c->relu, xs, n, out, c->stream);
   }
   if (e != hipSuccess) return hip_fail(c, e, "forward launch");
+  if (many && !rows && trunk_workspace(c, most) != hipSuccess) (void)hipGetLastError();
   return SIM_OK;
 }
 
