@@ -252,8 +252,10 @@ typedef struct {
  * network's FP32 step starts as four wavefronts per slot when the trace has
  * at most 1,024 sub-traces.  C3 variants whose kernel needs scratch memory
  * (register spills, see sim_variant_scratch) are left out when another
- * variant needs none.  Synchronises.  *out receives the choice and the
- * trials. */
+ * variant needs none.  A shape whose steps are split over more compute units
+ * (see sim_step) runs one kernel whatever the variant: it is timed once, last,
+ * under the variant that was best in the other shapes.  Synchronises.  *out
+ * receives the choice and the trials. */
 SIMNET_API int sim_autotune(sim_ctx* ctx, int32_t n_steps, int32_t lat_mode,
                             const int32_t* lat_table, sim_tuning* out);
 

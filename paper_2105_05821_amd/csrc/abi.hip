@@ -1382,13 +1382,13 @@ static void count_steps(sim_ctx* c, int64_t n_steps) {
   if (!c->reset_captured) c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
 }
 
-// Whether a step of this run is split over several workgroups per tile: a C3
-// network running its predictor, every sub-trace in a slot of its own (so
+// Whether a step in this many tiles is split over several workgroups per tile:
+// a C3 network running its predictor, every sub-trace in a slot of its own (so
 // that `steps` launches are known to end the run), and not under capture (a
 // graph takes the persistent kernel's one node).
-static bool split_step(const sim_ctx* c, int32_t mode) {
+static bool split_step(const sim_ctx* c, int32_t mode, int32_t n_wg) {
   return (c->net == 1 || c->net >= 3) && mode != SIM_LAT_INJECT && c->split.cst &&
-         (int64_t)c->n_wg * MT >= c->n_sub && split_shape(c, c->n_wg).units >= 2 &&
+         (int64_t)n_wg * MT >= c->n_sub && split_shape(c, n_wg).units >= 2 &&
          !capturing(c->stream);
 }
 
@@ -1437,7 +1437,7 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
   if (c->ran_to_end) return SIM_OK;  // every sub-trace has already finished
   if (n_steps == 0) return SIM_OK;   // checks only
   if (n_steps >= INT32_MAX) c->ran_to_end = true;
-  if (split_step(c, mode)) {
+  if (split_step(c, mode, c->n_wg)) {
     const hipError_t e = split_steps(c, n_steps, mode, table);
     if (e != hipSuccess) return hip_fail(c, e, "split step launch");
     count_steps(c, n_steps);
@@ -1466,7 +1466,7 @@ int sim_run(sim_ctx* c, int32_t mode, const int32_t* table, sim_result* res) {
   if (!res) return fail(c, SIM_EINVAL, "null result");
   hipError_t e = hipSuccess;
   // (RB7 and split steps run eagerly)
-  if (c->use_graph && !c->ran_to_end && c->net != 5 && !split_step(c, mode)) {
+  if (c->use_graph && !c->ran_to_end && c->net != 5 && !split_step(c, mode, c->n_wg)) {
     // same checks as a step launch, then replay (rebuilt when its inputs change)
     int rc = step_launch(c, 0, mode, table);
     if (rc != SIM_OK) return rc;
@@ -1673,40 +1673,49 @@ int sim_autotune(sim_ctx* c, int32_t n_steps, int32_t lat_mode, const int32_t* l
   *out = sim_tuning{};
   float best = -1.f;
   int rc = SIM_OK;
-  for (int v = 0; v < nv && rc == SIM_OK; ++v)
-    for (int32_t nw : shapes) {
-      if (v < N_VARIANTS && skip[v]) break;
-      if ((rc = sim_set_tuning(c, v, nw)) != SIM_OK) break;
-      // one untimed launch (first use of a kernel), then the timed one
-      if ((rc = step_launch(c, n_steps, lat_mode, lat_table)) != SIM_OK) break;
-      if ((rc = sim_reset(c)) != SIM_OK) break;
-      float ms = 0.f;
-      unsigned long long ctr[NCOUNTERS] = {0, 0, 0, 0};
-      e = hipEventRecord(e0, c->stream);
-      if (e == hipSuccess) rc = step_launch(c, n_steps, lat_mode, lat_table);
-      if (e == hipSuccess && rc == SIM_OK) e = hipEventRecord(e1, c->stream);
-      if (e == hipSuccess && rc == SIM_OK)
-        e = hipMemcpyAsync(ctr, c->st.counters, sizeof ctr, hipMemcpyDeviceToHost, c->stream);
-      if (e == hipSuccess && rc == SIM_OK) e = hipStreamSynchronize(c->stream);
-      if (e == hipSuccess && rc == SIM_OK) e = hipEventElapsedTime(&ms, e0, e1);
-      if (e != hipSuccess) rc = hip_fail(c, e, "timing");
-      if (rc != SIM_OK) break;
-      // the objective is time per position advanced: fewer slots do less
-      // work per step
-      ms = ctr[3] ? ms * 1e6f / (float)ctr[3] : ms * 1e6f;
-      if (out->n_tried < 16) {
-        out->tried_variant[out->n_tried] = v;
-        out->tried_n_wg[out->n_tried] = nw;
-        out->tried_ms[out->n_tried] = ms;
-        ++out->n_tried;
-      }
-      if (best < 0.f || ms < best) {
-        best = ms;
-        out->variant = v;
-        out->n_wg = nw;
-        out->ms = ms;
-      }
+  auto trial = [&](int v, int32_t nw) {
+    if ((rc = sim_set_tuning(c, v, nw)) != SIM_OK) return;
+    // one untimed launch (first use of a kernel), then the timed one
+    if ((rc = step_launch(c, n_steps, lat_mode, lat_table)) != SIM_OK) return;
+    if ((rc = sim_reset(c)) != SIM_OK) return;
+    float ms = 0.f;
+    unsigned long long ctr[NCOUNTERS] = {0, 0, 0, 0};
+    e = hipEventRecord(e0, c->stream);
+    if (e == hipSuccess) rc = step_launch(c, n_steps, lat_mode, lat_table);
+    if (e == hipSuccess && rc == SIM_OK) e = hipEventRecord(e1, c->stream);
+    if (e == hipSuccess && rc == SIM_OK)
+      e = hipMemcpyAsync(ctr, c->st.counters, sizeof ctr, hipMemcpyDeviceToHost, c->stream);
+    if (e == hipSuccess && rc == SIM_OK) e = hipStreamSynchronize(c->stream);
+    if (e == hipSuccess && rc == SIM_OK) e = hipEventElapsedTime(&ms, e0, e1);
+    if (e != hipSuccess) rc = hip_fail(c, e, "timing");
+    if (rc != SIM_OK) return;
+    // the objective is time per position advanced: fewer slots do less
+    // work per step
+    ms = ctr[3] ? ms * 1e6f / (float)ctr[3] : ms * 1e6f;
+    if (out->n_tried < 16) {
+      out->tried_variant[out->n_tried] = v;
+      out->tried_n_wg[out->n_tried] = nw;
+      out->tried_ms[out->n_tried] = ms;
+      ++out->n_tried;
     }
+    if (best < 0.f || ms < best) {
+      best = ms;
+      out->variant = v;
+      out->n_wg = nw;
+      out->ms = ms;
+    }
+  };
+  // The split step is one kernel whatever the variant: it is timed once, last,
+  // with the variant that was best in the other shapes, which steps that are
+  // not split (under capture) then run.
+  int first = 0;
+  while (skip[first]) ++first;
+  out->variant = first;
+  for (int v = first; v < nv && rc == SIM_OK; ++v)
+    for (int32_t nw : shapes)
+      if (!skip[v] && rc == SIM_OK && !split_step(c, lat_mode, nw)) trial(v, nw);
+  for (int32_t nw : shapes)
+    if (rc == SIM_OK && split_step(c, lat_mode, nw)) trial(out->variant, nw);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != SIM_OK) return rc;

@@ -349,3 +349,28 @@ def test_captured_training_forwards_replay_at_once(torch, sn, prec):
         for (z, save), (wz, ws) in zip(got, want):
             assert torch.equal(z, wz) and torch.equal(save, ws), i
     pred.close()
+
+
+@pytest.mark.parametrize("net,prec,n_sub", [("c3", 1, 600), ("c3", 0, 40), ("c3", 1, 9), ("hyb", 1, 40)])
+def test_autotune_times_a_split_shape_once(torch, sn, net, prec, n_sub):
+    """The split step is one kernel whatever the variant: one trial of the
+    full shape, with the choice's results and every variant's own (below the
+    full shape, where its kernel runs) those of the default."""
+    start, length, warm = streams(n_sub, 3)
+    s = simulator(sn, torch, net, prec, start, length, warm, codes=True)
+    want = s.run()
+    full = (n_sub + 15) // 16
+    t = s.autotune(6)
+    shapes = {full} | {max(1, full * q // 4) for q in (2, 3)}
+    assert [n for _, n, _ in t["trials"]].count(full) == 1 and t["trials"][-1][1] == full
+    assert {n for _, n, _ in t["trials"]} == shapes
+    assert (t["variant"], t["n_wg"]) in [(v, n) for v, n, _ in t["trials"]]
+    if net == "c3" and len(shapes) > 1:
+        free = {v for v in range(4) if s.variant_scratch(v) == 0} or set(range(4))
+        assert {v for v, n, _ in t["trials"] if n != full} == free
+    same(s.run(), want)
+    for v in range(4):
+        for n in shapes:
+            s.set_tuning(v, n)
+            same(s.run(), want)
+    s.close()
