@@ -1414,8 +1414,22 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
   sm.stage_head(wt, tid, NT);
   __syncthreads();
   const int64_t b = b0 + s;
+  // (request_window_row's loads, written out: through the function the FP32
+  // form with store latencies spills scalar registers, 3,000 windows 272 us
+  // against 256)
   auto load = [&](int j0, int nb) {
-    return request_window_row<Net, CPT, TPR>(x, B, b, j0 * BS + t, t < nb * BS, part);
+    RowRegs<CPT> r;
+    r.valid = b < B && t < nb * BS;
+    const float* src = x + ((r.valid ? b : 0) * Net::L + (r.valid ? j0 * BS + t : 0)) * D;
+#pragma unroll
+    for (int cc = 0; cc < CPT; cc += 2) {
+      const int c = part * CPT + cc;
+      if (TPR > 1 || cc < D)
+        r.v[cc / 2] = *reinterpret_cast<const float2*>(src + (c < D ? c : D - 2));
+      else
+        r.v[cc / 2] = make_float2(0.f, 0.f);
+    }
+    return r;
   };
   auto commit = [&](int j0, int nb, const RowRegs<CPT>& r, T* X) {
     (void)j0;
