@@ -205,9 +205,11 @@ SIMNET_API int sim_load_weights(sim_ctx* ctx, const sim_layer* layers, int32_t n
  * advances only the sub-traces currently in slots.  Results do not depend on
  * the slot assignment.  With a slot for every sub-trace and at most 2,048 of
  * them, the C3 networks' predicting steps are spread over more compute units,
- * one launch per step (never more launches than steps are left; under stream
- * capture the call stays one launch); results are the same.  lat_table (DEVICE int32, needed for INJECT and SHADOW) is
- * indexed by the sub-trace's simulated position: row
+ * one launch per step (never more launches than steps are left; a call under
+ * stream capture, or of one or two BF16 or FP8 steps of more than about 1,360
+ * sub-traces, stays one launch); results are the same.  lat_table (DEVICE
+ * int32, needed for INJECT and SHADOW) is indexed by the sub-trace's simulated
+ * position: row
  * sum_{k'<k}(warm[k']+len[k']) + p, column o (0 fetch, 1 execution). */
 SIMNET_API int sim_step(sim_ctx* ctx, int32_t n_steps, int32_t lat_mode, const int32_t* lat_table);
 

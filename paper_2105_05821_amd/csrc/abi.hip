@@ -1382,14 +1382,25 @@ static void count_steps(sim_ctx* c, int64_t n_steps) {
   if (!c->reset_captured) c->steps_done = std::min(c->max_pos, c->steps_done + n_steps);
 }
 
-// Whether a step in this many tiles is split over several workgroups per tile:
-// a C3 network running its predictor, every sub-trace in a slot of its own (so
-// that `steps` launches are known to end the run), and not under capture (a
-// graph takes the persistent kernel's one node).
-static bool split_step(const sim_ctx* c, int32_t mode, int32_t n_wg) {
-  return (c->net == 1 || c->net >= 3) && mode != SIM_LAT_INJECT && c->split.cst &&
-         (int64_t)n_wg * MT >= c->n_sub && split_shape(c, n_wg).units >= 2 &&
-         !capturing(c->stream);
+// Whether a call of n_steps steps in this many tiles is split over several
+// workgroups per tile: a C3 network running its predictor, every sub-trace in a
+// slot of its own (so that `steps` launches are known to end the run), and not
+// under capture (a graph takes the persistent kernel's one node).  Nor a short
+// call on many tiles: the state's way in and out and the last head and update
+// cost a call ~33 us, and with two units per tile (86 to 128 tiles) a BF16 or FP8
+// step gains less than that (us a call, one workgroup per tile -> split, 2,048
+// sub-traces: C3 BF16 1 step 64 -> 75, 2 steps 115 -> 116, 4 216 -> 197; hybrid 1
+// 64 -> 65, 2 116 -> 106; store latencies 80 -> 84, 139 -> 129).  With three units
+// (1,360 sub-traces) one step 63 -> 58, in FP32 (2,048) 232 -> 168, RB7 462 -> 451.
+static bool split_step(const sim_ctx* c, int64_t n_steps, int32_t mode, int32_t n_wg) {
+  if (!((c->net == 1 || c->net >= 3) && mode != SIM_LAT_INJECT && c->split.cst &&
+        (int64_t)n_wg * MT >= c->n_sub && !capturing(c->stream)))
+    return false;
+  const int32_t units = split_shape(c, n_wg).units;
+  n_steps = std::min(n_steps, c->max_pos - c->steps_done);  // (a run's)
+  const bool brief = units == 2 && c->cfg.prec != SIM_FP32 && c->net != 5 &&
+                     n_steps < (c->net == 1 ? 3 : 2);
+  return units >= 2 && !brief;
 }
 
 // n_steps split steps (to the end at most): launch i finishes step i - 1 and
@@ -1437,7 +1448,7 @@ static int step_launch(sim_ctx* c, int64_t n_steps, int32_t mode, const int32_t*
   if (c->ran_to_end) return SIM_OK;  // every sub-trace has already finished
   if (n_steps == 0) return SIM_OK;   // checks only
   if (n_steps >= INT32_MAX) c->ran_to_end = true;
-  if (split_step(c, mode, c->n_wg)) {
+  if (split_step(c, n_steps, mode, c->n_wg)) {
     const hipError_t e = split_steps(c, n_steps, mode, table);
     if (e != hipSuccess) return hip_fail(c, e, "split step launch");
     count_steps(c, n_steps);
@@ -1466,7 +1477,7 @@ int sim_run(sim_ctx* c, int32_t mode, const int32_t* table, sim_result* res) {
   if (!res) return fail(c, SIM_EINVAL, "null result");
   hipError_t e = hipSuccess;
   // (RB7 and split steps run eagerly)
-  if (c->use_graph && !c->ran_to_end && c->net != 5 && !split_step(c, mode, c->n_wg)) {
+  if (c->use_graph && !c->ran_to_end && c->net != 5 && !split_step(c, INT32_MAX, mode, c->n_wg)) {
     // same checks as a step launch, then replay (rebuilt when its inputs change)
     int rc = step_launch(c, 0, mode, table);
     if (rc != SIM_OK) return rc;
@@ -1713,9 +1724,9 @@ int sim_autotune(sim_ctx* c, int32_t n_steps, int32_t lat_mode, const int32_t* l
   out->variant = first;
   for (int v = first; v < nv && rc == SIM_OK; ++v)
     for (int32_t nw : shapes)
-      if (!skip[v] && rc == SIM_OK && !split_step(c, lat_mode, nw)) trial(v, nw);
+      if (!skip[v] && rc == SIM_OK && !split_step(c, n_steps, lat_mode, nw)) trial(v, nw);
   for (int32_t nw : shapes)
-    if (rc == SIM_OK && split_step(c, lat_mode, nw)) trial(out->variant, nw);
+    if (rc == SIM_OK && split_step(c, n_steps, lat_mode, nw)) trial(out->variant, nw);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (rc != SIM_OK) return rc;

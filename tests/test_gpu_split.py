@@ -374,3 +374,18 @@ def test_autotune_times_a_split_shape_once(torch, sn, net, prec, n_sub):
             s.set_tuning(v, n)
             same(s.run(), want)
     s.close()
+
+
+@pytest.mark.parametrize("net", ["c3", "st"])
+def test_short_calls_on_many_tiles(torch, sn, net):
+    """Calls of one and two steps on 86 to 128 tiles (one workgroup per tile)
+    between longer ones (split), and a run with two steps left."""
+    start, length, warm = streams(1400, 3)
+    s = simulator(sn, torch, net, 1, start, length, warm)
+    want = s.run()
+    for calls in ((1, 3, 2, 1, 4, 2), (2, 1), (int((length + warm).max()) - 2,)):
+        s.reset()
+        for n in calls:
+            s.step(n)
+        same(s.run(), want)
+    s.close()
