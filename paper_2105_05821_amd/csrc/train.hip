@@ -784,7 +784,7 @@ __device__ __forceinline__ void dma16(const void* src, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
                    __builtin_amdgcn_readfirstlane(dst)),
                "v"(src)
-               : "memory", "m0");
+               : "memory");
 }
 template <int MODE, int T>
 struct DmaOp {
