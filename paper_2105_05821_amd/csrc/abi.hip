@@ -1816,10 +1816,11 @@ int predictor_bwd(sim_ctx* c, const void* x, const void* save, const float* dlog
   // trunk layer l's weight gradient, [c_out][input column] with
   // input column t*c_in + c (p*256 + c for the hidden layer), stored
   // straight into the parameters' layout ([c_out][c_in][2], [512][256][13]);
-  // its bias gradient (the column sums of dy, y [rows][c_out]) from the same
-  // product's row sums of dy^T where an LDS-direct kernel runs it (one list
-  // of partials per k-split for the final sum), else as a column sum.  In the
-  // group where it may join, else (windows not 8-byte aligned) by itself.
+  // its bias gradient the column sums of dy (y [rows][c_out]).  In the group
+  // where it may join, the bias from the same product's row sums of dy^T (one
+  // list of partials per k-split for the final sum), else (windows off an
+  // 8-byte boundary, a save buffer off a 16-byte one) by itself, the bias as a
+  // column sum.
   auto wgrad = [&](const GemmOperand& dyt, const GemmOperand& act, int l, int64_t c_out,
                    int64_t cols, int64_t c_in, int64_t taps, int64_t rows, const void* y) {
     GemmArgs g = gemm(dyt, act, dparams + T.woff[l], cols, c_out, cols, rows, beta);
@@ -1833,8 +1834,8 @@ int predictor_bwd(sim_ctx* c, const void* x, const void* save, const float* dlog
       return;
     }
     int64_t parts = 0;
-    if (e == hipSuccess) e = launch_gemm(g, bf, part, (int64_t)SPLITK_CAP, s, &parts);
-    if (e == hipSuccess && parts == 0)
+    run(g);
+    if (e == hipSuccess)
       e = launch_colsum_partial(y, bf, rows, c_out, c_out, csw_next, &parts, s);
     if (e == hipSuccess) sums(parts, c_out, dparams + T.boff[l]);
   };

@@ -11,14 +11,13 @@
 //                    stride-2 convolution is a GEMM over position pairs).
 //                    Operands in aligned rows go straight to LDS and are
 //                    transposed on their way out (gemm_bf16_dma_kernel,
-//                    gemm_f32_dma_kernel, which also sum their left operand's
-//                    rows: the trunk's bias gradients); operands of arbitrary
-//                    strides and alignment take gemm_bf16_kernel (128x128
-//                    tiles, rounded to BF16 in LDS) and gemm_kernel (FP32
-//                    MFMA, 64x64 tiles).
+//                    gemm_f32_dma_kernel); operands of arbitrary strides and
+//                    alignment take gemm_bf16_kernel (128x128 tiles, rounded
+//                    to BF16 in LDS) and gemm_kernel (FP32 MFMA, 64x64 tiles).
 //   gemm_group_kernel, group_reduce
-//                    all weight gradients of a pass in one launch, their
-//                    partials and the bias sums in another.
+//                    all weight gradients of a pass in one launch, with the
+//                    row sums of their left operands (the trunk's bias
+//                    gradients), their partials and the bias sums in another.
 //   reductions       split-K partials summed in order with the epilogue.
 //   loss_kernel      hybrid loss per window (400-bin cross-entropy + L1 on
 //                    log1p(latency) per latency type) and its gradient
@@ -779,7 +778,9 @@ __device__ __forceinline__ uint32_t lds_addr(T* p) {
 // 16 bytes per lane from src straight to LDS, at byte address dst (the same
 // in every lane) + 16 * lane.  In asm because the builtin makes the compiler
 // wait for every such load in flight before most LDS reads; nothing here
-// waits for it but dma_barrier (no register is written).
+// waits for it but dma_barrier (no register is written).  M0 is a reserved
+// register: the compiler keeps no value in it, sets it right before each use
+// of its own, and ignores it in a clobber list (with a warning).
 __device__ __forceinline__ void dma16(const void* src, uint32_t dst) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(
                    __builtin_amdgcn_readfirstlane(dst)),
@@ -1385,28 +1386,25 @@ static bool vector_epilogue(const GemmArgs& g) {
 }
 
 hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
-                       hipStream_t stream, int64_t* rowsum_parts) {
+                       hipStream_t stream) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (!rows_fit(g)) return hipErrorInvalidValue;
-  const int mode = dma_mode(g, bf16_mma);
-  const bool dma = mode != 0, b3 = mode == 3;
+  // (a left operand contiguous along the outer dimension, a weight gradient's,
+  // goes through launch_gemm_group where the LDS-direct kernels can take it)
+  const bool dma = dma_mode(g, bf16_mma) == 2 && g.amode == 1;
+  g.rowsum = nullptr;
   auto tiles_of = [&](int64_t tm, int64_t tn) {
     return ((g.M + tm - 1) / tm) * ((g.N + tn - 1) / tn);
   };
   // (64 x 64 tiles where 128 x 128 ones would not fill the chip and k is too
   // short to split)
-  const bool small = dma && !b3 && tiles_of(HB, HB) < 192 && !(part && g.K >= 4096);
-  const int TM = !bf16_mma ? GB : b3 || small ? 64 : HB;
-  const int TN = !bf16_mma ? GB : small ? 64 : HB;
-  const int64_t tiles = tiles_of(TM, TN);
+  const bool small = dma && tiles_of(HB, HB) < 192 && !(part && g.K >= 4096);
+  const int T = !bf16_mma ? GB : small ? 64 : HB;
+  const int64_t tiles = tiles_of(T, T);
   // split K when the output is too small to fill the chip, at least 8 k-steps
-  // each, within the partial buffer: two workgroups per CU, or one where the
-  // partials would cost more than the second hides (BF16, few tiles: conv3's
-  // weight gradient of 4,096 windows 28.6 us with 256 workgroups, 35.8 with
-  // 512; the hidden layer's 104 tiles 38.9 with 416, 42.3 with 208; FP32 74
-  // with 512, 89 with 256)
-  auto splits = [&](int64_t t, int64_t target, int64_t step) {
-    int64_t n = target / t;
+  // each, within the partial buffer: two workgroups per CU
+  auto splits = [&](int64_t t, int64_t step) {
+    int64_t n = 512 / t;
     const int64_t steps = g.K / (step * 8);
     if (n > steps) n = steps;
     if (n > part_cap / (g.M * g.N)) n = part_cap / (g.M * g.N);
@@ -1421,62 +1419,34 @@ hipError_t launch_gemm(GemmArgs g, int bf16_mma, float* part, int64_t part_cap,
     // themselves (two or three, k is short: a split's launch that adds its
     // partials costs more than it saves, 64 windows' step 114 us against 113,
     // 4,096 345 against 340).
-    if (part && tiles_of(HB, HB) < 128) ks = splits(tiles_of(HB, HB), 512, HK);
+    if (part && tiles_of(HB, HB) < 128) ks = splits(tiles_of(HB, HB), HK);
     if (small && ks > 1) {
       g.fold = (int32_t)(((g.K + ks - 1) / ks + HK - 1) / HK);
       ks = 1;
     }
   } else if (part && tiles < 128) {
-    ks = splits(tiles, dma && bf16_mma && !b3 && tiles < 64 ? 256 : 512,
-                bf16_mma || dma ? HK : GK);
+    ks = splits(tiles, bf16_mma || dma ? HK : GK);
   }
   g.ksplit = (int32_t)ks;
   g.part = part;
   g.evec = (bf16_mma || dma) && vector_epilogue(g);
-  const dim3 grid((unsigned)((g.N + TN - 1) / TN), (unsigned)((g.M + TM - 1) / TM), (unsigned)ks);
-  if (rowsum_parts) *rowsum_parts = dma && g.rowsum ? ks : 0;
-  if (!dma) g.rowsum = nullptr;
+  const dim3 grid((unsigned)((g.N + T - 1) / T), (unsigned)((g.M + T - 1) / T), (unsigned)ks);
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, g);
   };
-  if (dma && !bf16_mma) {
-    if (g.amode == 1)
-      b3             ? launch(gemm_f32_dma_kernel<1, 3>)
-      : g.bmode == 1 ? launch(gemm_f32_dma_kernel<1, 1>)
-                     : launch(gemm_f32_dma_kernel<1, 2>);
-    else
-      b3             ? launch(gemm_f32_dma_kernel<2, 3>)
-      : g.bmode == 1 ? launch(gemm_f32_dma_kernel<2, 1>)
-                     : launch(gemm_f32_dma_kernel<2, 2>);
-  } else if (b3) {
-    g.amode == 1 ? launch(gemm_bf16_dma_kernel<1, 3, 64, 128>)
-                 : launch(gemm_bf16_dma_kernel<2, 3, 64, 128>);
-  } else if (small && g.fold) {
-    if (g.amode == 1)
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64, true>)
-                   : launch(gemm_bf16_dma_kernel<1, 2, 64, 64, true>);
-    else
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, 64, 64, true>)
-                   : launch(gemm_bf16_dma_kernel<2, 2, 64, 64, true>);
-  } else if (small) {
-    if (g.amode == 1)
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64>)
-                   : launch(gemm_bf16_dma_kernel<1, 2, 64, 64>);
-    else
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, 64, 64>)
-                   : launch(gemm_bf16_dma_kernel<2, 2, 64, 64>);
-  } else if (dma) {
-    if (g.amode == 1)
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, HB, HB>)
-                   : launch(gemm_bf16_dma_kernel<1, 2, HB, HB>);
-    else
-      g.bmode == 1 ? launch(gemm_bf16_dma_kernel<2, 1, HB, HB>)
-                   : launch(gemm_bf16_dma_kernel<2, 2, HB, HB>);
-  } else if (bf16_mma) {
-    launch(gemm_bf16_kernel);
-  } else {
-    launch(gemm_kernel);
-  }
+  if (!dma)
+    bf16_mma ? launch(gemm_bf16_kernel) : launch(gemm_kernel);
+  else if (!bf16_mma)
+    g.bmode == 1 ? launch(gemm_f32_dma_kernel<1, 1>) : launch(gemm_f32_dma_kernel<1, 2>);
+  else if (!small)
+    g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, HB, HB>)
+                 : launch(gemm_bf16_dma_kernel<1, 2, HB, HB>);
+  else if (g.fold)
+    g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64, true>)
+                 : launch(gemm_bf16_dma_kernel<1, 2, 64, 64, true>);
+  else
+    g.bmode == 1 ? launch(gemm_bf16_dma_kernel<1, 1, 64, 64>)
+                 : launch(gemm_bf16_dma_kernel<1, 2, 64, 64>);
   if (ks > 1) {
     const int64_t MN = g.M * g.N;
     if (ks < 64 && g.N % 4 == 0 && perm_rows(g))
