@@ -125,3 +125,32 @@ def products(torch, sn, prec, B, shift, x_off=0, dz_off=0, dp_off=0):
     pred.backward(x, moved, dz, dp2, accumulate=True)
     assert torch.allclose(dp2 - 1, dp, rtol=0, atol=3e-7 * max(1.0, float(dp.abs().max())))
     pred.close()
+
+
+@pytest.mark.parametrize("B", [1024, 4096])
+def test_fp32_weight_gradient_sums_in_short_runs(torch, sn, B):
+    """The head's weight gradient dZ^T H against float64 on the same dZ and H:
+    its error is that of sums over runs of 128 products, however many windows a
+    workgroup takes.  Bar: an operation rounds by at most u / sqrt(3) rms
+    (u = 2^-24), the n partial sums of a chain grow as sqrt(n), so a chain errs
+    by sqrt(n / 2) of that: runs of 128, the B / 128 runs (in one or more
+    splits), and the product's own rounding."""
+    layers = synth.net_c3_hybrid()
+    ws, bs = synth.init_weights(3, layers, out_bias=None, out_gain=1.0)
+    pred = sn.Predictor(layers, sn.SIM_FP32)
+    pred.load_weights(layers, sn.flat_params(ws, bs))
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn((B, L, D), generator=gen, device="cuda")
+    z, save = pred.forward(x)
+    dz = torch.randn(z.shape, generator=gen, device="cuda")
+    dp = torch.empty(2_204_642, device="cuda")
+    pred.backward(x, save, dz, dp)
+    h = save[:pred.save_bytes(B)].view(torch.float32)[-B * 512:].view(B, 512).double()
+    want = dz.double().t() @ h
+    got = dp[-802 - 802 * 512:-802].view(802, 512).double()
+    # (against the size of the summed products: H is not negative, dZ of both signs)
+    size = torch.sqrt(dz.double().square().t() @ h.square())
+    err = float((got - want).norm() / size.norm())
+    bar = 2.0 ** -24 / np.sqrt(3.0) * np.sqrt(128 / 2 + B / 128 / 2 + 1)
+    assert err <= bar, (err, bar)
+    pred.close()
