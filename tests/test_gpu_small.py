@@ -120,3 +120,38 @@ def test_pieces_modes_and_refills_carry_the_state(torch, sn, prec, variant):
         for k in KEYS:
             np.testing.assert_array_equal(got[k], free[k], err_msg=k)
     s.close()
+
+
+@pytest.mark.parametrize("n_sub", [5, 65536, 65537])
+def test_results_however_they_are_copied(torch, sn, n_sub):
+    """Few sub-traces' results come in one copy, many straight to the caller's
+    arrays, and only the arrays asked for: the same numbers, and those of the
+    sub-traces in two halves."""
+    import ctypes as C
+    rng = np.random.default_rng(7)
+    length = rng.integers(1, 4, n_sub)
+    at = np.concatenate([[0], np.cumsum(length)])
+    table = np.stack([rng.integers(0, 4, at[-1]), rng.integers(0, 30, at[-1])], 1).astype(np.int32)
+
+    def run(lo, hi):
+        s = simulator(sn, torch, 1, True, length[lo:hi], 8)
+        dev = torch.from_numpy(table[at[lo]:at[hi]]).cuda()
+        return s, dev, s.run(sn.SIM_LAT_INJECT, dev)
+
+    s, dev, got = run(0, n_sub)
+    halves = [run(0, n_sub // 2)[2], run(n_sub // 2, n_sub)[2]]
+    for k in ("fetch", "drain", "final", "warm_tick"):
+        np.testing.assert_array_equal(got[k], np.concatenate([h[k] for h in halves]), err_msg=k)
+    assert got["total"] == int((got["final"] - got["warm_tick"]).sum())
+    fields = {"fetch": "fetch_cycles", "drain": "drain_cycles", "final": "final_tick",
+              "warm_tick": "warm_tick"}
+    for asked in ((), ("drain",), ("fetch", "warm_tick"), ("final",)):
+        s.reset()
+        res, out = sn.sim_result(), {k: np.full(n_sub, -1, np.int64) for k in asked}
+        for k in asked:
+            setattr(res, fields[k], out[k].ctypes.data_as(C.POINTER(C.c_int64)))
+        assert sn.lib().sim_run(s.ctx, sn.SIM_LAT_INJECT, dev.data_ptr(), C.byref(res)) == 0
+        assert res.total_cycles == got["total"] and res.measured_instr == at[-1]
+        for k in asked:
+            np.testing.assert_array_equal(out[k], got[k], err_msg=k)
+    s.close()
