@@ -1083,9 +1083,15 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
 // Against step_kernel<NetSmall, P>, which gathered the windows, streamed the
 // weights and updated the queues one thread per slot anew each step (us per
 // step over 120 steps, launch and results included; FP32, BF16, FP8): 3,000
-// sub-traces 7.9 -> 4.2, 4.3 -> 2.5, 6.5 -> 2.5; 16,384: 18.4 -> 11.5, 8.5 ->
-// 5.4, 13.5 -> 6.2.  Same products and sums in the same order as
+// sub-traces 5.8 -> 3.7, 3.9 -> 2.2, 4.6 -> 2.4; 16,384: 18.8 -> 11.2, 8.8 ->
+// 5.0, 13.0 -> 5.7.  Same products and sums in the same order as
 // predict_tile<NetSmall, P>, same state, work queue and results.
+// Sub-traces are claimed, and the run's counters added, once per workgroup:
+// atomics on one address take ~17 ns each on the whole chip, and with one per
+// wave (four times step_kernel's) runs of many short sub-traces were slower than
+// that kernel (us, 20,000 and 100,000 sub-traces of 8 instructions, injected
+// latencies: step_kernel 110, 320, one per wave 165, 501, one per workgroup 86,
+// 254; BF16 predicting 164, 526, 209, 551, 127, 418).
 template <class P>
 struct SmallTile {
   using T = typename P::T;
@@ -1098,7 +1104,14 @@ struct SmallTile {
   alignas(16) T x[MT * SX];
   alignas(16) T a1[QW][MT * SA];
   alignas(16) T out[MT * SO];
-  alignas(16) uint32_t live[2][QW];
+};
+
+// The waves' agreement on which slots take a sub-trace, and when.
+struct SmallClaims {
+  alignas(16) uint32_t left[QW];   // per wave: steps to its first sub-trace's end
+  alignas(16) uint32_t ended[QW];  // per wave: slots that take a sub-trace
+  uint32_t claimed;                // the first of the claim order they take
+  uint32_t counts[NCOUNTERS];      // the workgroup's run counters, at the end
 };
 
 template <class P, bool RUN_NET>
@@ -1110,7 +1123,8 @@ __global__ void __launch_bounds__(QW * 64, 2)
   constexpr int N1 = WV_C1 / 16, N2 = WV_C2 / 16, NS1 = P::SCALED ? N1 : 1,
                 NS2 = P::SCALED ? N2 : 1;
   constexpr int CPL = WV_C2 / 8;  // final-FC channels per lane and block
-  __shared__ S sm;
+  __shared__ S sm;  // (not there without the predictor)
+  __shared__ SmallClaims cl;
   const int tid = threadIdx.x, v = tid >> 6, lane = tid & 63;
   const int s = tid >> 4, j = tid & (QL - 1), W = p.W;  // slot, queue entry
   const int mr = lane & 15, g4 = lane >> 4;             // MFMA row (slot), k quarter
@@ -1165,19 +1179,29 @@ __global__ void __launch_bounds__(QW * 64, 2)
   }
 
   T* const xs = sm.x + s * S::SX;
-  // feature c of trace row `row`, dynamic columns zero, in storage precision
-  auto feature = [&](int64_t row, int c) -> T {
-    if (c == p.col_res || c == p.col_exe || c == p.col_sto) return P::cvt(0.f);
-    float f;
-    if (p.codes) {
-      f = code_feature(p.codes[row], c);
-    } else if constexpr (P::ID == 1) {
-      return p.feat16[row * staged_feat(D) + c];
+  // trace row tr to `row` in storage precision, dynamic columns zero (the few
+  // of them overwritten: a test per feature costs the kernel its scalar registers)
+  auto put_row = [&](int64_t tr, T* row) {
+    if (P::ID == 1 && !p.codes) {
+      const uint4* src = reinterpret_cast<const uint4*>(p.feat16 + tr * staged_feat(D));
+#pragma unroll
+      for (int q = 0; q < D / 8; ++q) reinterpret_cast<uint4*>(row)[q] = src[q];
     } else {
-      f = p.feat[row * D + c];
+      const uint32_t code = p.codes ? p.codes[tr] : 0u;
+#pragma unroll
+      for (int c = 0; c < D; c += 2) {
+        float2 f;
+        if (p.codes)
+          f = make_float2(code_feature(code, c), code_feature(code, c + 1));
+        else
+          f = *reinterpret_cast<const float2*>(p.feat + tr * D + c);
+        if constexpr (P::SCALED) f = make_float2(f.x * wt.x_inv[c], f.y * wt.x_inv[c + 1]);
+        const T e[2] = {P::cvt(f.x), P::cvt(f.y)};
+        store_run<2 * sizeof(T)>(row + c, e);
+      }
     }
-    if constexpr (P::SCALED) f *= wt.x_inv[c];
-    return P::cvt(f);
+    for (int c : {p.col_res, p.col_exe, p.col_sto})
+      if ((unsigned)c < (unsigned)D) row[c] = P::cvt(0.f);
   };
   // the current instruction's row: this lane's two features as they are in
   // the trace (or its code), requested a step ahead
@@ -1223,10 +1247,21 @@ __global__ void __launch_bounds__(QW * 64, 2)
   RowQueue q{};
   bool active = false;
   int k = st.slot_kid[slot];
-  if (k < 0) {
-    if (j == 0) k = claim_subtrace(st, p.n_sub);
-    k = __shfl(k, lane & ~(QL - 1));
-  }
+  // the slots with `take` set claim the next sub-traces, all at once
+  auto claim = [&](bool take) {
+    const uint64_t mine = __ballot(take && j == 0);
+    if (lane == 0) cl.ended[v] = (uint32_t)__popcll(mine);
+    lds_barrier();
+    const uint4 c = *reinterpret_cast<const uint4*>(cl.ended);
+    const uint32_t all = c.x + c.y + c.z + c.w;
+    if (tid == 0 && all > 0) cl.claimed = atomicAdd(st.next, all);
+    lds_barrier();
+    if (!take) return;
+    const uint32_t at = cl.claimed + (v > 0 ? c.x : 0) + (v > 1 ? c.y : 0) + (v > 2 ? c.z : 0) +
+                        (uint32_t)__popcll(mine & ((1ull << (lane & ~(QL - 1))) - 1));
+    k = at < (uint32_t)p.n_sub ? st.order[at] : -1;
+  };
+  claim(k < 0);
   // the slot's state, and its windows' rows but the current one's as step
   // `it` finds them (lane j: window slot j + 1)
   auto load = [&](int it) {
@@ -1239,8 +1274,7 @@ __global__ void __launch_bounds__(QW * 64, 2)
       T* row = xs + ((it - 1 - j) & (WV_L - 1)) * D;
       zero_row(row);
       if (active) {
-        if (j < q.count)
-          for (int c = 0; c < D; ++c) row[c] = feature(q.row - 1 - j, c);
+        if (j < q.count) put_row(q.row - 1 - j, row);
         request(q.row);
       }
     }
@@ -1248,149 +1282,163 @@ __global__ void __launch_bounds__(QW * 64, 2)
   load(0);
   StepCounts n;
 
-  for (int it = 0; it < p.n_steps; ++it) {
-    const int64_t rb = q.retire_bound(lane, W);
-    int32_t inj[2] = {0, 0};
-    if (p.lat_mode != 0 && active)
-      for (int o = 0; o < 2; ++o) inj[o] = p.lat_table[q.g * 2 + o];
-    float z[2] = {0.f, 0.f};
-    if constexpr (RUN_NET) {
-      if (active) {
-        commit(xs + (it & (WV_L - 1)) * D);
-        if (j < q.count) {
-          T* row = xs + ((it - 1 - j) & (WV_L - 1)) * D;
-          auto put = [&](int c, float u, float inv) {
-            if constexpr (P::SCALED) u *= inv;
-            if ((unsigned)c < (unsigned)D) row[c] = P::cvt(u);
-          };
-          put(p.col_res, (float)(q.cur - q.t), xr);
-          put(p.col_exe, (float)q.e, xe);
-          put(p.col_sto, 0.f, 1.f);
+  // up to the first end of a sub-trace in the workgroup, whose slots then take
+  // the next ones together
+  for (int it = 0; it < p.n_steps;) {
+    uint32_t first = active ? (uint32_t)(q.n_pos - q.pos) : UINT32_MAX;  // (below 2^31)
+    first = min(first, (uint32_t)__shfl_xor((int)first, 16));
+    first = min(first, (uint32_t)__shfl_xor((int)first, 32));
+    if (lane == 0) cl.left[v] = first;
+    lds_barrier();
+    const uint4 left = *reinterpret_cast<const uint4*>(cl.left);
+    first = min(min(left.x, left.y), min(left.z, left.w));
+    if (first == UINT32_MAX) break;  // (no slot has a sub-trace)
+    const int end = it + (int)min(first, (uint32_t)(p.n_steps - it));
+    for (; it < end; ++it) {
+      const int64_t rb = q.retire_bound(lane, W);
+      int32_t inj[2] = {0, 0};
+      if (p.lat_mode != 0 && active)
+        for (int o = 0; o < 2; ++o) inj[o] = p.lat_table[q.g * 2 + o];
+      float z[2] = {0.f, 0.f};
+      if constexpr (RUN_NET) {
+        if (active) {
+          commit(xs + (it & (WV_L - 1)) * D);
+          if (j < q.count) {
+            T* row = xs + ((it - 1 - j) & (WV_L - 1)) * D;
+            auto put = [&](int c, float u, float inv) {
+              if constexpr (P::SCALED) u *= inv;
+              if ((unsigned)c < (unsigned)D) row[c] = P::cvt(u);
+            };
+            put(p.col_res, (float)(q.cur - q.t), xr);
+            put(p.col_exe, (float)q.e, xe);
+            put(p.col_sto, 0.f, 1.f);
+          }
+          if (q.pos + 1 < q.n_pos) request(q.row + 1);
         }
-        if (q.pos + 1 < q.n_pos) request(q.row + 1);
-      }
-      if (lane == 0) sm.live[it & 1][v] = 0u;
-      if (active) sm.live[it & 1][v] = 1u;
-      lds_barrier();
-      const uint4 any = *reinterpret_cast<const uint4*>(sm.live[it & 1]);
-      if (!(any.x | any.y | any.z | any.w)) break;
-      // conv1 at positions 2v, 2v + 1
-      v4f acc[2][N1];
+        lds_barrier();
+        // conv1 at positions 2v, 2v + 1
+        v4f acc[2][N1];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int n = 0; n < N1; ++n) acc[i][n] = v4f{0.f, 0.f, 0.f, 0.f};
+          for (int n = 0; n < N1; ++n) acc[i][n] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int kg = 0; kg < KGS; ++kg) {
-        const int k0 = kg * P::KG + KQ * g4, tap = k0 / D, off = k0 % D;
+        for (int kg = 0; kg < KGS; ++kg) {
+          const int k0 = kg * P::KG + KQ * g4, tap = k0 / D, off = k0 % D;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const int row = (it - 2 * (2 * v + i) - tap) & (WV_L - 1);
-          const uint4 a = *reinterpret_cast<const uint4*>(sm.x + mr * S::SX + row * D + off);
+          for (int i = 0; i < 2; ++i) {
+            const int row = (it - 2 * (2 * v + i) - tap) & (WV_L - 1);
+            const uint4 a = *reinterpret_cast<const uint4*>(sm.x + mr * S::SX + row * D + off);
 #pragma unroll
-          for (int n = 0; n < N1; ++n) acc[i][n] = P::mma(acc[i][n], w1[kg][n], a);
+            for (int n = 0; n < N1; ++n) acc[i][n] = P::mma(acc[i][n], w1[kg][n], a);
+          }
         }
-      }
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int n = 0; n < N1; ++n) {
+          for (int n = 0; n < N1; ++n) {
+            T e[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              e[c] = to_storage_v<P>(activation_v<P>(acc[i][n][c], b1[n][c], s1[P::SCALED ? n : 0][c],
+                                                     relu_mask & 1u),
+                                     i1[P::SCALED ? n : 0][c]);
+            store_run<4 * sizeof(T)>(&sm.a1[v][mr * S::SA + i * WV_C1 + n * 16 + 4 * g4], e);
+          }
+        wave_lds_sync();
+        // conv2 at position v
+        v4f acc2[N2];
+#pragma unroll
+        for (int n = 0; n < N2; ++n) acc2[n] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kg = 0; kg < KGS; ++kg) {
+          const uint4 a = *reinterpret_cast<const uint4*>(
+              &sm.a1[v][mr * S::SA + kg * P::KG + KQ * g4]);
+#pragma unroll
+          for (int n = 0; n < N2; ++n) acc2[n] = P::mma(acc2[n], w2[kg][n], a);
+        }
+#pragma unroll
+        for (int n = 0; n < N2; ++n) {
           T e[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            e[c] = to_storage_v<P>(activation_v<P>(acc[i][n][c], b1[n][c], s1[P::SCALED ? n : 0][c],
-                                                   relu_mask & 1u),
-                                   i1[P::SCALED ? n : 0][c]);
-          store_run<4 * sizeof(T)>(&sm.a1[v][mr * S::SA + i * WV_C1 + n * 16 + 4 * g4], e);
+            e[c] = to_storage_v<P>(activation_v<P>(acc2[n][c], b2[n][c], s2[P::SCALED ? n : 0][c],
+                                                   relu_mask & 2u),
+                                   i2[P::SCALED ? n : 0][c]);
+          store_run<4 * sizeof(T)>(&sm.out[mr * S::SO + v * WV_C2 + n * 16 + 4 * g4], e);
         }
-      wave_lds_sync();
-      // conv2 at position v
-      v4f acc2[N2];
+        lds_barrier();
+        // final FC: 8 lanes per (slot, output)
+        float f = 0.f;
 #pragma unroll
-      for (int n = 0; n < N2; ++n) acc2[n] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < QW; ++b) {
+          alignas(16) T a[CPL];
+          __builtin_memcpy(a, __builtin_assume_aligned(
+                                  &sm.out[s * S::SO + b * WV_C2 + fsub * CPL], CPL * sizeof(T) < 16
+                                                                                   ? CPL * sizeof(T)
+                                                                                   : 16),
+                           sizeof a);
 #pragma unroll
-      for (int kg = 0; kg < KGS; ++kg) {
-        const uint4 a = *reinterpret_cast<const uint4*>(
-            &sm.a1[v][mr * S::SA + kg * P::KG + KQ * g4]);
-#pragma unroll
-        for (int n = 0; n < N2; ++n) acc2[n] = P::mma(acc2[n], w2[kg][n], a);
-      }
-#pragma unroll
-      for (int n = 0; n < N2; ++n) {
-        T e[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          e[c] = to_storage_v<P>(activation_v<P>(acc2[n][c], b2[n][c], s2[P::SCALED ? n : 0][c],
-                                                 relu_mask & 2u),
-                                 i2[P::SCALED ? n : 0][c]);
-        store_run<4 * sizeof(T)>(&sm.out[mr * S::SO + v * WV_C2 + n * 16 + 4 * g4], e);
-      }
-      lds_barrier();
-      // final FC: 8 lanes per (slot, output)
-      float f = 0.f;
-#pragma unroll
-      for (int b = 0; b < QW; ++b) {
-        alignas(16) T a[CPL];
-        __builtin_memcpy(a, __builtin_assume_aligned(
-                                &sm.out[s * S::SO + b * WV_C2 + fsub * CPL], CPL * sizeof(T) < 16
-                                                                                 ? CPL * sizeof(T)
-                                                                                 : 16),
-                         sizeof a);
-#pragma unroll
-        for (int c = 0; c < CPL; ++c) f = fmaf(P::val(a[c]), wl[b][c], f);
-      }
-      f += dpp<DPP_XOR1>(f);
-      f += dpp<DPP_XOR2>(f);
-      f += dpp<DPP_HALF_MIRROR>(f);  // (lanes of a quad hold the same by now)
-      f += lb;
-      if (relu_mask & 4u) f = fmaxf(f, 0.f);
-      const float other = dpp<DPP_ROR8>(f);
-      z[0] = fo ? other : f;
-      z[1] = fo ? f : other;
-      if (p.logits_out && active && fsub == 0) p.logits_out[q.g * 2 + fo] = f;
-    } else if (!__any(active)) {
-      break;
-    }
-    int32_t lat[2] = {0, 0};
-    const int32_t count = q.count;
-    StepCounts m;
-    if (RUN_NET) {
-#pragma unroll
-      for (int o = 0; o < 2; ++o) lat[o] = round_latency<true>(z[o], p.lat_max, m.clamped, m.nonfinite);
-    }
-    if (p.lat_mode != 0) {
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        if (RUN_NET && inj[o] != lat[o]) ++m.mismatch;
-        lat[o] = inj[o];
-      }
-    }
-    if (active) {
-      ++n.pred;
-      n.clamped += m.clamped;
-      n.nonfinite += m.nonfinite;
-      n.mismatch += m.mismatch;
-      const int kept = q.advance(lat[0], lat[1], rb, lane, j);
-      if constexpr (RUN_NET)
-        // rows that left the window: that of the entry one lane down now (a
-        // full queue's oldest is the next current row)
-        if (j >= kept && j < count) zero_row(xs + ((it - 1 - j) & (WV_L - 1)) * D);
-      if (q.pos == q.n_pos) {  // the slot takes the next sub-trace
-        if (j == 0) {
-          q.finish(st, k);
-          k = claim_subtrace(st, p.n_sub);
+          for (int c = 0; c < CPL; ++c) f = fmaf(P::val(a[c]), wl[b][c], f);
         }
-        k = __shfl(k, lane & ~(QL - 1));
-        load(it + 1);
+        f += dpp<DPP_XOR1>(f);
+        f += dpp<DPP_XOR2>(f);
+        f += dpp<DPP_HALF_MIRROR>(f);  // (lanes of a quad hold the same by now)
+        f += lb;
+        if (relu_mask & 4u) f = fmaxf(f, 0.f);
+        const float other = dpp<DPP_ROR8>(f);
+        z[0] = fo ? other : f;
+        z[1] = fo ? f : other;
+        if (p.logits_out && active && fsub == 0) p.logits_out[q.g * 2 + fo] = f;
+      }
+      int32_t lat[2] = {0, 0};
+      const int32_t count = q.count;
+      StepCounts m;
+      if (RUN_NET) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+          lat[o] = round_latency<true>(z[o], p.lat_max, m.clamped, m.nonfinite);
+      }
+      if (p.lat_mode != 0) {
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          if (RUN_NET && inj[o] != lat[o]) ++m.mismatch;
+          lat[o] = inj[o];
+        }
+      }
+      if (active) {
+        ++n.pred;
+        n.clamped += m.clamped;
+        n.nonfinite += m.nonfinite;
+        n.mismatch += m.mismatch;
+        const int kept = q.advance(lat[0], lat[1], rb, lane, j);
+        if constexpr (RUN_NET)
+          // rows that left the window: that of the entry one lane down now (a
+          // full queue's oldest is the next current row)
+          if (j >= kept && j < count) zero_row(xs + ((it - 1 - j) & (WV_L - 1)) * D);
       }
     }
+    const bool ended = active && q.pos == q.n_pos;
+    if (ended && j == 0) q.finish(st, k);
+    claim(ended);
+    if (ended) load(it);
   }
 
+  // (one atomic per counter and workgroup: those on one address take ~17 ns each)
+  static_assert(NCOUNTERS == 4, "StepCounts");
+  if (tid < NCOUNTERS) cl.counts[tid] = 0u;
+  lds_barrier();
   if (j == 0) {
     st.slot_kid[slot] = k;
-    n.add_to(st);
+    atomicAdd(&cl.counts[0], n.clamped);
+    atomicAdd(&cl.counts[1], n.nonfinite);
+    atomicAdd(&cl.counts[2], n.mismatch);
+    atomicAdd(&cl.counts[3], n.pred);
   }
   if (k >= 0) q.store(st, k, j, W);
+  lds_barrier();
+  if (tid < NCOUNTERS && cl.counts[tid])
+    atomicAdd(&st.counters[tid], (unsigned long long)cl.counts[tid]);
 }
 
 // Predictor over explicit windows x [B][L][D] -> logits [B][NOUT]; TRUNK:

@@ -155,3 +155,27 @@ def test_results_however_they_are_copied(torch, sn, n_sub):
         for k in asked:
             np.testing.assert_array_equal(out[k], got[k], err_msg=k)
     s.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+@pytest.mark.parametrize("codes", [False, True])
+def test_short_sub_traces_refill_the_slots(torch, sn, prec, codes):
+    """More sub-traces than slots, 1 to 9 instructions each (slots of a
+    workgroup end together and apart, the last ones find nothing left): run at
+    once, in pieces that stop between and at ends, and in 32 slots."""
+    length = np.random.default_rng(11).integers(1, 10, 17_000)
+    s = simulator(sn, torch, prec, codes, length, 4)
+    s.set_tuning(0, 1024)
+    z = [torch.full((s.n_pred, 2), np.nan, device="cuda") for _ in range(3)]
+    s.record_logits(z[0])
+    want = s.run()
+    for out, n_wg in ((z[1], 1024), (z[2], 2)):
+        s.set_tuning(0, n_wg)
+        s.record_logits(out)
+        for m in (1, 2, 5, 3):
+            s.step(m)
+        got = s.run()
+        for k in KEYS + ("n_clamped", "n_nonfinite"):
+            np.testing.assert_array_equal(got[k], want[k], err_msg=k)
+        assert torch.equal(out, z[0])
+    s.close()
