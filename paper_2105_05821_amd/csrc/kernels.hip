@@ -243,9 +243,9 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
 #pragma unroll
         for (int o = 0; o < Net::NLAT; ++o) {
           if constexpr (Net::HEAD == 1)
-            lat[o] = hybrid_latency<false>(z + o * HYB_PER_TYPE, p.lat_max, n_clamped, n_nonfinite);
+            lat[o] = hybrid_latency(z + o * HYB_PER_TYPE, p.lat_max, n_clamped, n_nonfinite);
           else
-            lat[o] = round_latency<false>(z[o], p.lat_max, n_clamped, n_nonfinite);
+            lat[o] = round_latency(z[o], p.lat_max, n_clamped, n_nonfinite);
         }
       }
       ++n_pred;  // positions advanced (the work a launch did)
@@ -605,7 +605,7 @@ __global__ void __launch_bounds__(64) wave_step_kernel(DevWeights wt, uint32_t r
       if (p.logits_out && lane == 0)
         for (int o = 0; o < 2; ++o) p.logits_out[g * 2 + o] = z[o];
 #pragma unroll
-      for (int o = 0; o < 2; ++o) lat[o] = round_latency<false>(z[o], p.lat_max, n_clamped, n_nonfinite);
+      for (int o = 0; o < 2; ++o) lat[o] = round_latency(z[o], p.lat_max, n_clamped, n_nonfinite);
     }
     ++n_pred;
     if (p.lat_mode != 0) {
@@ -1034,7 +1034,7 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
       if (p.logits_out && tid == 0)
         for (int o = 0; o < 2; ++o) p.logits_out[q.g * 2 + o] = z[o];
 #pragma unroll
-      for (int o = 0; o < 2; ++o) lat[o] = round_latency<true>(z[o], p.lat_max, n.clamped, n.nonfinite);
+      for (int o = 0; o < 2; ++o) lat[o] = round_latency(z[o], p.lat_max, n.clamped, n.nonfinite);
     }
     ++n.pred;
     if (p.lat_mode != 0) {
@@ -1397,7 +1397,7 @@ __global__ void __launch_bounds__(QW * 64, 2)
       if (RUN_NET) {
 #pragma unroll
         for (int o = 0; o < 2; ++o)
-          lat[o] = round_latency<true>(z[o], p.lat_max, m.clamped, m.nonfinite);
+          lat[o] = round_latency(z[o], p.lat_max, m.clamped, m.nonfinite);
       }
       if (p.lat_mode != 0) {
 #pragma unroll

@@ -867,38 +867,17 @@ __device__ __forceinline__ float dep_flag(uint2 m, uint2 c, int f) {
 }
 
 // Rounded latency in cycles: nearest, ties to even; non-finite -> 0;
-// clamped to [0, lat_max].  SELECT: by selects, where every lane rounds and
-// the result lies on the chain through every step (the small network's and the
-// split step); by branches where one lane of a slot updates it (step_kernel:
-// with selects the BF16 step came out 46 instructions longer and uneven runs of
-// packed codes, bound by their longest stream, 1 % slower: 198.0 -> 200.2 ms).
-template <bool SELECT>
+// clamped to [0, lat_max].
 __device__ __forceinline__ int32_t round_latency(float v, int32_t lat_max, uint32_t& clamped,
                                                  uint32_t& nonfinite) {
-  if constexpr (SELECT) {
-    const bool finite = isfinite(v);
-    const float r = rintf(v), top = (float)lat_max;
-    const bool low = finite && r < 0.f, high = finite && r > top;
-    nonfinite += !finite;
-    clamped += low || high;
-    const int32_t i = (int32_t)(finite && !low && !high ? r : 0.f);
-    return high ? lat_max : i;
-  } else {
-    if (!isfinite(v)) {
-      ++nonfinite;
-      return 0;
-    }
-    const float r = rintf(v);
-    if (r < 0.f) {
-      ++clamped;
-      return 0;
-    }
-    if (r > (float)lat_max) {
-      ++clamped;
-      return lat_max;
-    }
-    return (int32_t)r;
-  }
+  // (selects, not branches: this lies on the chain through every step)
+  const bool finite = isfinite(v);
+  const float r = rintf(v), top = (float)lat_max;
+  const bool low = finite && r < 0.f, high = finite && r > top;
+  nonfinite += !finite;
+  clamped += low || high;
+  const int32_t i = (int32_t)(finite && !low && !high ? r : 0.f);
+  return high ? lat_max : i;
 }
 
 // Execution and store latency (each at most 65535) in one 32-bit word.
@@ -909,7 +888,6 @@ __device__ __forceinline__ int32_t pack_es(int32_t e, int32_t s) {
 // Hybrid head (Sec. 2.3): the most probable class (the first of equal
 // scores; a NaN score never wins) is the latency, unless it is the last
 // class ("larger"), which takes the direct output z[HYB_CLASSES], rounded.
-template <bool SELECT>
 __device__ __forceinline__ int32_t hybrid_latency(const float* z, int32_t lat_max,
                                                   uint32_t& clamped, uint32_t& nonfinite) {
   int best = 0;
@@ -917,7 +895,7 @@ __device__ __forceinline__ int32_t hybrid_latency(const float* z, int32_t lat_ma
   for (int c = 1; c < HYB_CLASSES; ++c)
     if (z[c] > z[best]) best = c;
   if (best < HYB_CLASSES - 1) return best;
-  return round_latency<SELECT>(z[HYB_CLASSES], lat_max, clamped, nonfinite);
+  return round_latency(z[HYB_CLASSES], lat_max, clamped, nonfinite);
 }
 
 // Feature c of an instruction given as a packed code (trace encoding

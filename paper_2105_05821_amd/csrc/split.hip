@@ -223,9 +223,9 @@ __global__ void __launch_bounds__(Net::WAVES * 64)
 #pragma unroll
     for (int i = 0; i < Net::NLAT; ++i) {
       if constexpr (Net::HEAD == 1)
-        lat[i] = hybrid_latency<true>(o + i * HYB_PER_TYPE, p.lat_max, clamped, nonfinite);
+        lat[i] = hybrid_latency(o + i * HYB_PER_TYPE, p.lat_max, clamped, nonfinite);
       else
-        lat[i] = round_latency<true>(o[i], p.lat_max, clamped, nonfinite);
+        lat[i] = round_latency(o[i], p.lat_max, clamped, nonfinite);
     }
     if (p.lat_mode != 0 && act) {
 #pragma unroll
