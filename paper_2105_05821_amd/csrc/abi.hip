@@ -1181,7 +1181,7 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
     c->calibrated = false;
     int rc = upload_weights(c, SIM_FP32, host.data(), nullptr, &c->dev_w32, &c->w32);
     if (rc != SIM_OK) return rc;
-      c->weights = true;
+    c->weights = true;
     return sim_reset(c);
   }
   int rc = upload_weights(c, c->cfg.prec, host.data(), nullptr, &c->dev_weights, &c->w);

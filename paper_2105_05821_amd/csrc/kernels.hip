@@ -1090,8 +1090,8 @@ __global__ void __launch_bounds__(QW * 64) quad_step_kernel(DevWeights wt, uint3
 // atomics on one address take ~17 ns each on the whole chip, and with one per
 // wave (four times step_kernel's) runs of many short sub-traces were slower than
 // that kernel (us, 20,000 and 100,000 sub-traces of 8 instructions, injected
-// latencies: step_kernel 110, 320, one per wave 165, 501, one per workgroup 86,
-// 254; BF16 predicting 164, 526, 209, 551, 127, 418).
+// latencies: step_kernel 110, 320, one per wave 166, 501, one per workgroup 88,
+// 254; BF16 predicting 164, 526, 209, 551, 121, 418).
 template <class P>
 struct SmallTile {
   using T = typename P::T;

@@ -18,9 +18,9 @@
 // those of the one-workgroup step in the same order, so the results are
 // identical.
 //
-// Time per step, one workgroup per tile -> split (uniform sub-traces):
-// BF16 16 sub-traces 47 -> 16 us, 512 49 -> 21, 1,024 51 -> 27, 2,048 54 ->
-// 43; FP32 16 221 -> 36, 512 224 -> 51, 2,048 224 -> 138; a forward of one
+// Time per step, one workgroup per tile -> split (uniform sub-traces, 24 steps
+// a call): BF16 16 sub-traces 46 -> 16 us, 512 48 -> 20, 1,024 49 -> 26, 2,048 51
+// -> 42; FP32 16 218 -> 33, 512 220 -> 47, 2,048 220 -> 134; a forward of one
 // window BF16 47 -> 15, FP32 207 -> 28.  What bounds a small step now: ~6 us
 // to launch, add the sums and run the head and the update, then ~9 us of one
 // group's convolutions and its slice of the hidden layer, each layer waiting
