@@ -365,7 +365,8 @@ SIMNET_API int sim_loss_noalloc(sim_ctx* ctx, const float* logits, const int32_t
  * [B][111][50] float32, or NULL) receives the gradient with respect to the
  * window, zero in the slots no output depends on.  Gradients are computed
  * with the current parameters, in FP32 (BF16 form: from the BF16 saved
- * activations). */
+ * activations).  A save buffer off a 16-byte boundary is copied to one first
+ * (memory kept by the context). */
 SIMNET_API int predictor_bwd(sim_ctx* ctx, const void* x, const void* save, const float* dlogits,
                              int64_t B, float* dx, float* dparams, int32_t accumulate);
 

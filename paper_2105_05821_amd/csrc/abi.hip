@@ -33,6 +33,8 @@ struct TrainState {
   size_t perm_off[5] = {0};
   float* work = nullptr;
   int64_t work_B = 0;
+  void* save = nullptr;  // copy of a save buffer off a 16-byte boundary (backward)
+  int64_t save_B = 0;
   int2* inv = nullptr;  // per parameter: byte offsets in packed and perm (-1: none)
   size_t woff[5] = {0}, boff[5] = {0};
   size_t n_params = 0;
@@ -799,6 +801,13 @@ static int load_train_weights(sim_ctx* c, const sim_layer* layers, int32_t n_lay
   return SIM_OK;
 }
 
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
 // Backward workspace (floats): [0] per-window losses, [1] dH [B][512],
 // [2] dY3 [B*13][256], [3] dY2 [B*26][128], [4] dY1 [B*52][64], [5] the
 // five bias sums' chunk partials, [6] split-K partial products, [7] the
@@ -843,6 +852,34 @@ static SaveBlock save_block(const sim_ctx* c, void* save, int64_t B) {
   sb.a3 = p + (size_t)B * (52 * 64 + 26 * 128) * es;
   sb.h = p + (size_t)B * (52 * 64 + 26 * 128 + 13 * 256) * es;
   return sb;
+}
+
+// The activations on a 16-byte boundary, as the backward products' LDS-direct
+// kernels and grouped weight gradients read them: `save` itself, else a copy in
+// memory kept by the context (without that, or where there is none yet under
+// capture, `save`: the general kernels).  It holds as many windows as T.work and
+// so moves only when that does.  BF16 backward of 4,096 windows off the boundary
+// 500 us by the general kernels, 256 copied first (212 on it); 16 windows 177, 72.
+static const void* aligned_save(sim_ctx* c, const void* save, int64_t B, hipError_t* e) {
+  TrainState& T = c->tr;
+  if (reinterpret_cast<uintptr_t>(save) % 16 == 0) return save;
+  const int64_t per = save_bytes_per_window(c->cfg.prec);
+  if (T.save_B < B) {
+    if (capturing(c->stream)) return save;
+    if (T.save) {
+      (void)hipStreamSynchronize(c->stream);
+      (void)hipFree(T.save);
+      T.save_B = 0;
+    }
+    if (hipMalloc(&T.save, (size_t)(T.work_B * per)) != hipSuccess) {
+      (void)hipGetLastError();
+      T.save = nullptr;
+      return save;
+    }
+    T.save_B = T.work_B;
+  }
+  *e = hipMemcpyAsync(T.save, save, (size_t)(B * per), hipMemcpyDeviceToDevice, c->stream);
+  return T.save;
 }
 
 // Outputs per window of a network's inference head.
@@ -1204,13 +1241,6 @@ int sim_load_weights(sim_ctx* c, const sim_layer* layers, int32_t n_layers, cons
   }
   c->weights = true;
   return sim_reset(c);
-}
-
-static bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();
-  return true;
 }
 
 int sim_reset(sim_ctx* c) {
@@ -1810,7 +1840,9 @@ int predictor_bwd(sim_ctx* c, const void* x, const void* save, const float* dlog
   TrainState& T = c->tr;
   const int bf = c->cfg.prec == SIM_BF16;
   const int beta = accumulate ? 1 : 0;
-  const SaveBlock sb = save_block(c, const_cast<void*>(save), B);
+  hipError_t e = hipSuccess;
+  const SaveBlock sb = save_block(c, const_cast<void*>(aligned_save(c, save, B, &e)), B);
+  if (e != hipSuccess) return hip_fail(c, e, "copy of the save buffer");
   float* W = T.work;
   float* dH = W + train_work_off(B, 1);
   float* dY3 = W + train_work_off(B, 2);
@@ -1822,7 +1854,6 @@ int predictor_bwd(sim_ctx* c, const void* x, const void* save, const float* dlog
   // The input-gradient chain product by product, then all weight gradients
   // together (launch_gemm_group).
   hipStream_t s = c->stream;
-  hipError_t e = hipSuccess;
   auto run = [&](const GemmArgs& g) {
     if (e == hipSuccess) e = launch_gemm(g, bf, part, (int64_t)SPLITK_CAP, s);
   };
@@ -1841,8 +1872,8 @@ int predictor_bwd(sim_ctx* c, const void* x, const void* save, const float* dlog
   // its bias gradient the column sums of dy (y [rows][c_out]).  In the group
   // where it may join, the bias from the same product's row sums of dy^T (one
   // list of partials per k-split for the final sum), else (windows off an
-  // 8-byte boundary, a save buffer off a 16-byte one) by itself, the bias as a
-  // column sum.
+  // 8-byte boundary, a save buffer that could not be copied) by itself, the bias
+  // as a column sum.
   auto wgrad = [&](const GemmOperand& dyt, const GemmOperand& act, int l, int64_t c_out,
                    int64_t cols, int64_t c_in, int64_t taps, int64_t rows, const void* y) {
     GemmArgs g = gemm(dyt, act, dparams + T.woff[l], cols, c_out, cols, rows, beta);
@@ -1972,6 +2003,7 @@ void sim_destroy(sim_ctx* c) {
   if (c->tr.perm) (void)hipFree(c->tr.perm);
   if (c->tr.inv) (void)hipFree(c->tr.inv);
   if (c->tr.work) (void)hipFree(c->tr.work);
+  if (c->tr.save) (void)hipFree(c->tr.save);
   if (c->dev_block) (void)hipFree(c->dev_block);
   if (c->rb_trunk) (void)hipFree(c->rb_trunk);
   if (c->rb_active) (void)hipFree(c->rb_active);

@@ -154,3 +154,54 @@ def test_fp32_weight_gradient_sums_in_short_runs(torch, sn, B):
     bar = 2.0 ** -24 / np.sqrt(3.0) * np.sqrt(128 / 2 + B / 128 / 2 + 1)
     assert err <= bar, (err, bar)
     pred.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("shift", [4, 8])
+def test_save_buffer_off_its_boundary(torch, sn, prec, shift):
+    """A save buffer 4 or 8 bytes off a 16-byte boundary: copied in eager
+    calls (first use, a larger batch, a smaller one again), read where it is by
+    the general kernels in a call captured before any copy exists."""
+    layers = synth.net_c3_hybrid()
+    ws, bs = synth.init_weights(3, layers, out_bias=None, out_gain=1.0)
+    side = torch.cuda.Stream()
+    bar = 5e-6 if prec == 0 else 2.0 ** -8
+    with torch.cuda.stream(side):
+        pred = sn.Predictor(layers, prec)
+        pred.load_weights(layers, sn.flat_params(ws, bs))
+        gen = torch.Generator(device="cuda").manual_seed(9)
+
+        def inputs(B):
+            x = torch.randn((B, L, D), generator=gen, device="cuda")
+            y = torch.randint(0, 420, (B, 2), generator=gen, device="cuda").int()
+            z, save = pred.forward(x)
+            n = pred.save_bytes(B)
+            off = torch.empty(n + shift, dtype=torch.uint8, device="cuda")[shift:]
+            off.copy_(save[:n])
+            dz = pred.loss(z, y)[1]
+            want = torch.empty(2_204_642, device="cuda")
+            return x, off, dz, want, pred.backward(x, save, dz, want, want_dx=True)
+
+        def check(got, dx, want, want_dx):
+            side.synchronize()
+            for a, b in ((got, want), (dx, want_dx)):
+                assert float((a - b).norm() / b.norm()) <= bar
+
+        x, off, dz, want, want_dx = inputs(150)
+        got = torch.zeros_like(want)
+        side.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            dx = pred.backward(x, off, dz, got, want_dx=True)
+        for _ in range(3):
+            got.zero_()
+            graph.replay()
+            check(got, dx, want, want_dx)
+        for B in (150, 40):  # the copied save: the same bits as the aligned one
+            x, off, dz, want, want_dx = inputs(B)
+            dx = pred.backward(x, off, dz, got, want_dx=True)
+            assert torch.equal(got, want) and torch.equal(dx, want_dx)
+        x, off, dz, want, want_dx = inputs(260)
+        dx = pred.backward(x, off, dz, got, want_dx=True)
+        assert torch.equal(got, want) and torch.equal(dx, want_dx)
+        pred.close()
