@@ -1815,10 +1815,11 @@ hipError_t launch_forward_save(int prec, const DevWeights& w, uint32_t relu, con
 }
 
 // Every sub-trace back to its first instruction.  The rings and the last
-// retire times are left as they are: with no instruction in flight and
-// position 0 no entry is read before it is written.  (Clearing them took 63
-// of this kernel's 65 us at 1,000 sub-traces: 440 strided stores a thread.)
-__global__ void reset_kernel(DevState st, int32_t n_sub, int32_t n_slots) {
+// retire times need not be cleared: with no instruction in flight and
+// position 0 no entry is read before it is written, and clearing the rings
+// took 63 of this kernel's 65 us at 1,000 sub-traces (440 strided stores a
+// thread).  C: how many entries of each are cleared all the same (sim_reset).
+__global__ void reset_kernel(DevState st, int32_t n_sub, int32_t C, int32_t n_slots) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_slots) st.slot_kid[i] = -1;
   if (i == 0) *st.next = 0u;
@@ -1838,6 +1839,12 @@ __global__ void reset_kernel(DevState st, int32_t n_sub, int32_t n_slots) {
       st.m_count[i] = 0;
       st.m_inpq[i] = 0;
       st.x_prev[i] = 0;
+    }
+    for (int e = 0; e < C; ++e) {
+      st.q_idx[i * C + e] = 0;
+      st.q_e[i * C + e] = 0;
+      st.q_t[i * C + e] = 0;
+      st.q_r[i * C + e] = 0;
     }
   }
   if (i < NCOUNTERS) st.counters[i] = 0;
@@ -2010,12 +2017,13 @@ hipError_t launch_forward(int net, int prec, const DevWeights& w, uint32_t relu,
                   : launch_forward_n<NetC3>(prec, w, relu, x, B, logits, stream);
 }
 
-hipError_t launch_reset(const DevState& s, int32_t n_sub, int32_t n_slots, hipStream_t stream) {
+hipError_t launch_reset(const DevState& s, int32_t n_sub, int32_t C, int32_t n_slots,
+                        hipStream_t stream) {
   const int threads = 256;
   const int n = n_sub > n_slots ? n_sub : n_slots;
   const int blocks = (n + threads - 1) / threads;
   hipLaunchKernelGGL(reset_kernel, dim3(blocks > 0 ? blocks : 1), dim3(threads), 0, stream, s,
-                     n_sub, n_slots);
+                     n_sub, C, n_slots);
   return hipGetLastError();
 }
 

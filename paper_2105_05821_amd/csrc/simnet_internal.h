@@ -228,7 +228,8 @@ hipError_t launch_forward(int net, int prec, const DevWeights& w, uint32_t relu,
 hipError_t launch_calibrate(int net, const DevWeights& w, uint32_t relu, const DevState& s,
                             const StepParams& p, hipStream_t stream);
 int calibration_size(int net);
-hipError_t launch_reset(const DevState& s, int32_t n_sub, int32_t n_slots, hipStream_t stream);
+hipError_t launch_reset(const DevState& s, int32_t n_sub, int32_t C, int32_t n_slots,
+                        hipStream_t stream);
 hipError_t launch_total(const DevState& s, int32_t n_sub, int64_t* total, hipStream_t stream);
 // Training form (C3 trunk, hidden layer kept): activations saved by the
 // forward for the backward pass, per window, channels-last, in the form's
